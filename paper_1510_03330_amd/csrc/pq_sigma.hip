@@ -33,10 +33,10 @@ constexpr int kPoles = 128;   // semicircle pole representation (Gauss-Chebyshev
 
 __device__ inline double nu_of(int n, double beta) { return (2 * n + 1) * M_PI / beta; }
 
-__device__ inline double pole_tau(double e, double tau, double beta) {
-  // imaginary-time transform of 1/(i nu - e), 0 < tau < beta
+__device__ inline double pole_tau(double e, double tau, double tauc, double beta) {
+  // imaginary-time transform of 1/(i nu - e), 0 < tau < beta, tauc = beta - tau
   if (e >= 0.0) return -exp(-e * tau) / (1.0 + exp(-beta * e));
-  return -exp(e * (beta - tau)) / (exp(beta * e) + 1.0);
+  return -exp(e * tauc) / (exp(beta * e) + 1.0);
 }
 
 __device__ inline void semicircle_pole(int l, double D, double* e, double* c) {
@@ -52,13 +52,29 @@ __device__ inline double eps_of(int K, const Dims& d, double t, double tp) {
   return -2.0 * t * (cx + cy) - 4.0 * tp * cx * cy;
 }
 
-// exp(+2 pi i (kx rx / Lx + ky ry / Ly)) with the products reduced modulo the lattice
-__device__ inline double2 lattice_phase(int K, int R, const Dims& d) {
-  int kx = K / d.Ly, ky = K - kx * d.Ly, rx = R / d.Ly, ry = R - rx * d.Ly;
-  double ang = 2.0 * M_PI * ((double)((kx * rx) % d.Lx) / d.Lx + (double)((ky * ry) % d.Ly) / d.Ly);
-  double s, c;
-  sincos(ang, &s, &c);
-  return mk(c, s);
+// exp(+2 pi i (kx rx / Lx + ky ry / Ly)) from the two one-dimensional phase
+// tables tx[Lx], ty[Ly] of a workgroup
+__device__ inline double2 lattice_phase(int K, int R, const Dims& d, const double2* tx, const double2* ty) {
+  const int kx = K / d.Ly, ky = K - kx * d.Ly, rx = R / d.Ly, ry = R - rx * d.Ly;
+  return cmul(tx[(kx * rx) % d.Lx], ty[(ky * ry) % d.Ly]);
+}
+
+__device__ inline void phase_tables(const Dims& d, double2* tx, double2* ty) {
+  for (int i = threadIdx.x; i < d.Lx + d.Ly; i += blockDim.x) {
+    const bool x = i < d.Lx;
+    const int m = x ? i : i - d.Lx;
+    double sn, cs;
+    sincospi(2.0 * m / (x ? d.Lx : d.Ly), &sn, &cs);
+    (x ? tx[m] : ty[m]) = mk(cs, sn);
+  }
+}
+
+constexpr int kMaxNk = 64;     // momenta of the largest lattice
+
+__host__ __device__ inline int pow2_ge(int v) {
+  int p = 1;
+  while (p < v) p <<= 1;
+  return p;
 }
 
 struct S1Args {
@@ -67,152 +83,183 @@ struct S1Args {
   int local;
   const double2* g;      // [NG][Nk]
   const double* mu;
-  double* tau;           // [ntau]
-  double* wt;            // [ntau]
-  double2* dg;           // [Nve][Nk]
-  double2* gkt;          // [ntau][Nk]
-  double2* grt;          // [ntau][Nk] (R)
-  double2* trn;          // [Nve][Nk] (R)
+  double2* srt;          // [ntau][Nk] w_j U^2 G(R, tau_j)^2 G(-R, beta - tau_j)
   double2* out;          // [Nve][Nk]
 };
 
-// Gauss-Legendre nodes/weights on [0, beta], ascending, exactly symmetric.
-__global__ void gl_nodes_kernel(S1Args a) {
-  const int nt = a.d.ntau;
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  int half = (nt + 1) / 2;
-  if (i >= half) return;
-  double x = cos(M_PI * (i + 0.75) / (nt + 0.5));
-  double dp = 1.0;
-  for (int it = 0; it < 100; ++it) {
-    double p0 = 1.0, p1 = x;
-    for (int j = 2; j <= nt; ++j) {
-      double p2 = ((2.0 * j - 1.0) * x * p1 - (j - 1.0) * p0) / j;
-      p0 = p1;
-      p1 = p2;
+// Quadrature of the tau integral: Fejer's first rule on [0, beta] (Chebyshev
+// points, L. Fejer 1933; weights in closed form, J. Waldvogel, BIT 46, 2006),
+//   tau_j = beta sin^2(theta_j / 2),  theta_j = (j + 1/2) pi / N,
+//   w_j = (beta / N) [1 - 2 sum_{k=1}^{N/2} cos(2 k theta_j) / (4 k^2 - 1)],
+// symmetric (tau_{N-1-j} = beta - tau_j exactly). The integrand has the
+// frequencies up to 4 nu_max and exponentials exp(-3 E tau): its Chebyshev
+// coefficients fall off beyond degree 2 pi f Nv + O(beta E), which N = 8 f Nv +
+// 64 + 4 beta E exceeds. (Gauss-Legendre nodes are exact to twice the degree but
+// need N-long serial recurrences per Newton step: 103-223 us a call measured,
+// against a few cosines per node here.)
+//
+// One workgroup per pair (j, N-1-j), so that G(R, tau_j) and G(-R, beta - tau_j)
+// meet in one workgroup: dG = G - G_pole on the extended box, the imaginary-time
+// sums over its frequencies (exp(-i nu (beta - tau)) = -exp(i nu tau): one phase
+// serves both nodes), the lattice transform and the product, which kernels of
+// their own did before with one thread per output and a sincos per term (4x4,
+// Nv = 16: 19 + 9 us; one momentum, Nv = 32: 67 + 84 us for the pole sums).
+// Latency-bound: a few hundred operations per thread, N / 2 workgroups.
+__global__ __launch_bounds__(kThreads) void s1_tau_kernel(S1Args a) {
+  __shared__ double2 ph[kThreads];
+  __shared__ double2 red[2][kThreads];
+  __shared__ double2 gk[2][kMaxNk];
+  __shared__ double2 tx[kMaxNk], ty[kMaxNk];
+  __shared__ double pe[kPoles], pc[kPoles];
+  __shared__ double rsum[kThreads];
+  const Dims& d = a.d;
+  const int t = threadIdx.x, nt = d.ntau, j = blockIdx.x, Nk = d.Nk;
+  const double sj = sinpi((j + 0.5) / (2.0 * nt)), cj = cospi((j + 0.5) / (2.0 * nt));
+  const double u = sj * sj;                              // tau_j / beta
+  const double tau = a.beta * u, tauc = a.beta * (cj * cj);
+  double ws = 0.0;
+  for (int k = 1 + t; k <= nt / 2; k += kThreads) {
+    const long long r = ((long long)k * (2 * j + 1)) % (2 * nt);
+    ws += cospi((double)r / nt) / (4.0 * k * k - 1.0);
+  }
+  phase_tables(d, tx, ty);
+  if (a.local)
+    for (int l = t; l < kPoles; l += kThreads) {
+      semicircle_pole(l, a.D, &pe[l], &pc[l]);
     }
-    dp = nt * (x * p1 - p0) / (x * x - 1.0);
-    double dx = p1 / dp;
-    x -= dx;
-    if (fabs(dx) <= 1e-15) {
-      // one more evaluation for the derivative at the converged node
-      p0 = 1.0; p1 = x;
-      for (int j = 2; j <= nt; ++j) {
-        double p2 = ((2.0 * j - 1.0) * x * p1 - (j - 1.0) * p0) / j;
-        p0 = p1;
-        p1 = p2;
+  const double w = (a.beta / nt) * (1.0 - 2.0 * block_sum(ws, rsum));
+  // G(K, tau_j) and G(K, beta - tau_j): momentum K = t % NkP, a slice of the frequencies each
+  const int NkP = pow2_ge(Nk), nsl = kThreads / NkP, K = t % NkP, sl = t / NkP;
+  const bool live = K < Nk;
+  const double xi = live && !a.local ? eps_of(K, d, a.t, a.tp) - *a.mu : 0.0;
+  double2 acc0 = mk(0, 0), acc1 = mk(0, 0);
+  for (int e0 = 0; e0 < d.Nve; e0 += kThreads) {
+    __syncthreads();
+    if (e0 + t < d.Nve) {                                // exp(-i nu_e tau_j)
+      double sn, cs;
+      sincospi((2 * (e0 + t - d.Nve / 2) + 1) * u, &sn, &cs);
+      ph[t] = mk(cs, -sn);
+    }
+    __syncthreads();
+    if (live)
+      for (int e = e0 + sl; e < min(d.Nve, e0 + kThreads); e += nsl) {
+        const int n = e - d.Nve / 2;
+        const double nu = nu_of(n, a.beta);
+        double2 gp;
+        if (a.local) {                                   // poles come in pairs +-e_l
+          double s = 0.0;
+          for (int l = 0; l < kPoles / 2; ++l) s += pc[l] / (nu * nu + pe[l] * pe[l]);
+          gp = mk(0.0, -2.0 * nu * s);
+        } else {
+          gp = crecip(mk(-xi, nu));
+        }
+        const double2 dg = csub(a.g[(size_t)(n + d.NG / 2) * Nk + K], gp);
+        const double2 p = ph[e - e0];
+        acc0 = cadd(acc0, cmul(dg, p));
+        acc1 = csub(acc1, cmul(dg, mk(p.x, -p.y)));
       }
-      dp = nt * (x * p1 - p0) / (x * x - 1.0);
-      break;
-    }
   }
-  double w = 2.0 / ((1.0 - x * x) * dp * dp);
-  if ((nt & 1) && i == half - 1) x = 0.0;
-  // x is the i-th largest root
-  int hi = nt - 1 - i, lo = i;
-  a.tau[hi] = 0.5 * a.beta * (x + 1.0);
-  a.tau[lo] = 0.5 * a.beta * (1.0 - x);
-  a.wt[hi] = 0.5 * a.beta * w;
-  a.wt[lo] = 0.5 * a.beta * w;
-}
-
-// dG = G - G_pole on the extended box
-__global__ void s1_dg_kernel(S1Args a) {
-  const Dims& d = a.d;
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= d.Nve * d.Nk) return;
-  int e = idx / d.Nk, K = idx - e * d.Nk;
-  int n = e - d.Nve / 2;
-  double nu = nu_of(n, a.beta);
-  double2 gv = a.g[(size_t)(n + d.NG / 2) * d.Nk + K];
-  double2 gp;
+  red[0][t] = acc0;
+  red[1][t] = acc1;
+  double pole0 = 0.0, pole1 = 0.0;
   if (a.local) {
-    gp = mk(0.0, 0.0);
-    for (int l = 0; l < kPoles; ++l) {
-      double el, cl;
-      semicircle_pole(l, a.D, &el, &cl);
-      gp = cadd(gp, cscale(crecip(mk(-el, nu)), cl));
+    double s0 = 0.0, s1 = 0.0;
+    for (int l = t; l < kPoles; l += kThreads) {
+      s0 += pc[l] * pole_tau(pe[l], tau, tauc, a.beta);
+      s1 += pc[l] * pole_tau(pe[l], tauc, tau, a.beta);
     }
-  } else {
-    double xi = eps_of(K, d, a.t, a.tp) - *a.mu;
-    gp = crecip(mk(-xi, nu));
+    pole0 = block_sum(s0, rsum);
+    pole1 = block_sum(s1, rsum);
+  } else if (live) {
+    pole0 = pole_tau(xi, tau, tauc, a.beta);
+    pole1 = pole_tau(xi, tauc, tau, a.beta);
   }
-  a.dg[idx] = csub(gv, gp);
-}
-
-// G(K, tau_j) = pole part + T sum_e dG(e, K) exp(-i nu_e tau_j)
-__global__ void s1_gtau_kernel(S1Args a) {
-  const Dims& d = a.d;
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= d.ntau * d.Nk) return;
-  int j = idx / d.Nk, K = idx - j * d.Nk;
-  double tau = a.tau[j];
-  double pole = 0.0;
-  if (a.local) {
-    for (int l = 0; l < kPoles; ++l) {
-      double el, cl;
-      semicircle_pole(l, a.D, &el, &cl);
-      pole += cl * pole_tau(el, tau, a.beta);
+  __syncthreads();
+  for (int st = nsl / 2; st > 0; st >>= 1) {
+    if (sl < st) {
+      red[0][t] = cadd(red[0][t], red[0][t + st * NkP]);
+      red[1][t] = cadd(red[1][t], red[1][t + st * NkP]);
     }
-  } else {
-    double xi = eps_of(K, d, a.t, a.tp) - *a.mu;
-    pole = pole_tau(xi, tau, a.beta);
+    __syncthreads();
   }
-  double2 acc = mk(0.0, 0.0);
-  for (int e = 0; e < d.Nve; ++e) {
-    double nu = nu_of(e - d.Nve / 2, a.beta);
-    double s, c;
-    sincos(nu * tau, &s, &c);
-    acc = cadd(acc, cmul(a.dg[(size_t)e * d.Nk + K], mk(c, -s)));
+  if (t < Nk) {
+    gk[0][t] = mk(pole0 + red[0][t].x / a.beta, red[0][t].y / a.beta);
+    gk[1][t] = mk(pole1 + red[1][t].x / a.beta, red[1][t].y / a.beta);
   }
-  a.gkt[idx] = mk(pole + acc.x / a.beta, acc.y / a.beta);
+  __syncthreads();
+  // G(R, tau) = (1/N) sum_K e^{i K R} G(K, tau), a slice of the momenta per thread
+  acc0 = acc1 = mk(0, 0);
+  if (live)
+    for (int k = sl; k < Nk; k += nsl) {
+      const double2 p = lattice_phase(k, K, d, tx, ty);
+      acc0 = cadd(acc0, cmul(p, gk[0][k]));
+      acc1 = cadd(acc1, cmul(p, gk[1][k]));
+    }
+  red[0][t] = acc0;
+  red[1][t] = acc1;
+  __syncthreads();
+  for (int st = nsl / 2; st > 0; st >>= 1) {
+    if (sl < st) {
+      red[0][t] = cadd(red[0][t], red[0][t + st * NkP]);
+      red[1][t] = cadd(red[1][t], red[1][t + st * NkP]);
+    }
+    __syncthreads();
+  }
+  if (t < Nk) {
+    const int rx = t / d.Ly, ry = t - rx * d.Ly;
+    const int mR = ((d.Lx - rx) % d.Lx) * d.Ly + (d.Ly - ry) % d.Ly;
+    const double f = a.U * a.U * w / ((double)Nk * Nk * Nk);
+    const double2 g0 = red[0][t], g1 = red[1][t];
+    a.srt[(size_t)j * Nk + t] = cscale(cmul(cmul(g0, g0), red[1][mR]), f);
+    a.srt[(size_t)(nt - 1 - j) * Nk + t] = cscale(cmul(cmul(g1, g1), red[0][mR]), f);
+  }
 }
 
-// G(R, tau_j) = (1/N) sum_K e^{i K R} G(K, tau_j)
-__global__ void s1_gr_kernel(S1Args a) {
+// Sigma~_1(K, e) = sum_R e^{-i K R} sum_j e^{i nu_e tau_j} srt[j][R]: one
+// workgroup per frequency e, a slice of the nodes per thread (the sums over the
+// nodes ran serially in one thread per output before: 103-200 us).
+constexpr int kRowThreads = 1024;
+__global__ __launch_bounds__(kRowThreads) void s1_row_kernel(S1Args a) {
+  __shared__ double2 ph[kRowThreads];
+  __shared__ double2 red[kRowThreads];
+  __shared__ double2 tx[kMaxNk], ty[kMaxNk];
   const Dims& d = a.d;
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= d.ntau * d.Nk) return;
-  int j = idx / d.Nk, R = idx - j * d.Nk;
-  double2 acc = mk(0.0, 0.0);
-  for (int K = 0; K < d.Nk; ++K) acc = cadd(acc, cmul(lattice_phase(K, R, d), a.gkt[(size_t)j * d.Nk + K]));
-  a.grt[idx] = cscale(acc, 1.0 / d.Nk);
-}
-
-// T(R, e) = sum_j w_j e^{i nu_e tau_j} U^2 G(R, tau_j)^2 G(-R, beta - tau_j)
-__global__ void s1_tr_kernel(S1Args a) {
-  const Dims& d = a.d;
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= d.Nve * d.Nk) return;
-  int e = idx / d.Nk, R = idx - e * d.Nk;
-  int rx = R / d.Ly, ry = R - rx * d.Ly;
-  int mR = ((d.Lx - rx) % d.Lx) * d.Ly + (d.Ly - ry) % d.Ly;
-  double nu = nu_of(e - d.Nve / 2, a.beta);
-  double2 acc = mk(0.0, 0.0);
-  const int nt = d.ntau;
-  for (int j = 0; j < nt; ++j) {
-    double2 g1 = a.grt[(size_t)j * d.Nk + R];
-    double2 g2 = a.grt[(size_t)(nt - 1 - j) * d.Nk + mR];
-    double2 sv = cmul(cmul(g1, g1), g2);
-    double s, c;
-    sincos(nu * a.tau[j], &s, &c);
-    acc = cadd(acc, cscale(cmul(mk(c, s), sv), a.wt[j]));
+  const int t = threadIdx.x, nt = d.ntau, e = blockIdx.x, Nk = d.Nk;
+  const int NkP = pow2_ge(Nk), nsl = kRowThreads / NkP, R = t % NkP, sl = t / NkP;
+  phase_tables(d, tx, ty);
+  double2 acc = mk(0, 0);
+  for (int j0 = 0; j0 < nt; j0 += kRowThreads) {
+    __syncthreads();
+    if (j0 + t < nt) {
+      const double s = sinpi((j0 + t + 0.5) / (2.0 * nt));
+      double sn, cs;
+      sincospi((2 * (e - d.Nve / 2) + 1) * (s * s), &sn, &cs);
+      ph[t] = mk(cs, sn);
+    }
+    __syncthreads();
+    if (R < Nk) {
+      const int hi = min(nt, j0 + kRowThreads);
+#pragma unroll 4
+      for (int j = j0 + sl; j < hi; j += nsl) acc = cadd(acc, cmul(ph[j - j0], a.srt[(size_t)j * Nk + R]));
+    }
   }
-  a.trn[idx] = cscale(acc, a.U * a.U);
-}
-
-// Sigma~_1(K, e) = sum_R e^{-i K R} T(R, e)
-__global__ void s1_out_kernel(S1Args a) {
-  const Dims& d = a.d;
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= d.Nve * d.Nk) return;
-  int e = idx / d.Nk, K = idx - e * d.Nk;
-  double2 acc = mk(0.0, 0.0);
-  for (int R = 0; R < d.Nk; ++R) {
-    double2 ph = lattice_phase(K, R, d);
-    acc = cadd(acc, cmul(mk(ph.x, -ph.y), a.trn[(size_t)e * d.Nk + R]));
+  for (int pass = 0; pass < 2; ++pass) {        // the sum over the nodes, then over R
+    red[t] = acc;
+    __syncthreads();
+    for (int st = nsl / 2; st > 0; st >>= 1) {
+      if (sl < st) red[t] = cadd(red[t], red[t + st * NkP]);
+      __syncthreads();
+    }
+    if (pass == 1) break;
+    acc = mk(0, 0);
+    if (R < Nk)
+      for (int k = sl; k < Nk; k += nsl) {
+        const double2 p = lattice_phase(R, k, d, tx, ty);
+        acc = cadd(acc, cmul(mk(p.x, -p.y), red[k]));
+      }
+    __syncthreads();
   }
-  a.out[idx] = acc;
+  if (t < Nk) a.out[(size_t)e * Nk + t] = red[t];
 }
 
 // ------------------------------------------------------------- Sigma~_2
@@ -233,7 +280,6 @@ struct S2Args {
   const double2* k1;     // [4][Nq]
   const double2* k2;     // [4][Nq][n]
   double2* tab;          // [NG][5][Nq]  U1, U3, V1d, V1m, V3st per (n_b, p)
-  double2* out;          // [Nve][Nk]  (sum without the constant C)
 };
 
 __device__ inline double ind(bool b) { return b ? 1.0 : 0.0; }
@@ -243,11 +289,12 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
-// one wave per (n_b, p): lanes over the momentum B
-__global__ __launch_bounds__(kThreads) void s2_tables_kernel(S2Args a) {
+// sw lanes (the power of two >= Nk) per (n_b, p), over the momentum B: a lattice
+// of few momenta fills its waves with several entries
+__global__ __launch_bounds__(kThreads) void s2_tables_kernel(S2Args a, int sw) {
   const Dims& d = a.d;
-  const int wid = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (wid >= d.NG * d.Nq) return;
+  const int wid = (blockIdx.x * kThreads + threadIdx.x) / sw, lane = threadIdx.x & (sw - 1);
+  if (wid >= d.NG * d.Nq) return;                 // uniform over the sw lanes
   const int nbi = wid / d.Nq, qi = wid - (wid / d.Nq) * d.Nq;
   const int hG = d.NG / 2, nb = nbi - hG;
   const int jm = qi / d.Nk, P = qi - jm * d.Nk, mp = jm - (d.Nv / 2 - 1);
@@ -255,7 +302,8 @@ __global__ __launch_bounds__(kThreads) void s2_tables_kernel(S2Args a) {
   const bool kb2 = in_fbox(nb, d.Nv) && a.level >= 2;
   const size_t n = d.n;
   double v[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  for (int B = lane; B < d.Nk; B += 64) {
+  if (lane < d.Nk) {
+    const int B = lane;
     const double2 gb = a.g[(size_t)(nb + hG) * d.Nk + B];
     const double2 g1 = r1 ? a.g[(size_t)(nb + mp + hG) * d.Nk + kadd(B, P, d.Lx, d.Ly)] : mk(0, 0);
     const double2 g3 = r3 ? a.g[(size_t)(mp - nb - 1 + hG) * d.Nk + ksub(P, B, d.Lx, d.Ly)] : mk(0, 0);
@@ -267,18 +315,31 @@ __global__ __launch_bounds__(kThreads) void s2_tables_kernel(S2Args a) {
       w1m = cmul(u1, a.k2[((size_t)1 * d.Nq + qi) * n + bidx]);
       w3 = cmul(u3, cadd(a.k2[((size_t)2 * d.Nq + qi) * n + bidx], a.k2[((size_t)3 * d.Nq + qi) * n + bidx]));
     }
-    v[0] += u1.x; v[1] += u1.y; v[2] += u3.x; v[3] += u3.y;
-    v[4] += w1d.x; v[5] += w1d.y; v[6] += w1m.x; v[7] += w1m.y; v[8] += w3.x; v[9] += w3.y;
+    v[0] = u1.x; v[1] = u1.y; v[2] = u3.x; v[3] = u3.y;
+    v[4] = w1d.x; v[5] = w1d.y; v[6] = w1m.x; v[7] = w1m.y; v[8] = w3.x; v[9] = w3.y;
   }
-  for (int i = 0; i < 10; ++i) v[i] = wave_sum(v[i]);
-  if (lane < 5) {
-    const double2 o = mk(v[2 * lane], v[2 * lane + 1]);
-    a.tab[((size_t)nbi * 5 + lane) * d.Nq + qi] = o;
-  }
+  for (int i = 0; i < 10; ++i)
+    for (int o = sw >> 1; o > 0; o >>= 1) v[i] += __shfl_xor(v[i], o, 64);
+  if (lane == 0)
+    for (int i = 0; i < 5; ++i) a.tab[((size_t)nbi * 5 + i) * d.Nq + qi] = mk(v[2 * i], v[2 * i + 1]);
 }
 
-// one workgroup per k point of the extended box; threads over the transfers p
-__global__ __launch_bounds__(kThreads) void sigma2_kernel(S2Args a) {
+struct CombineArgs {
+  Dims d;
+  double cfac;
+  int has_s2;
+  const double2* s1;
+  const double2* partial;
+  const double2* lam_part;   // nullable: the box-Lambda term per box k
+  double2* out;
+};
+
+// The sum of the pieces, one workgroup per k point of the extended box:
+// Sigma~_1 plus the Schwinger-Dyson constant times the kernel part (threads over
+// the transfers p, and over slices of the frequencies n_b where the transfers
+// alone leave threads idle: nqp is the power of two >= Nq, at most the
+// workgroup), the box part's sums over the bosonic index, and the box Lambda.
+__global__ __launch_bounds__(kThreads) void sigma2_kernel(S2Args a, CombineArgs c_, int nqp) {
   __shared__ double red[kThreads];
   const Dims& d = a.d;
   const int kid = blockIdx.x;
@@ -288,8 +349,9 @@ __global__ __launch_bounds__(kThreads) void sigma2_kernel(S2Args a) {
   const int kbi = kbox ? (nk + d.Nv / 2) * d.Nk + K : 0;
   const int hF = d.Nve / 2, hBe = d.Nve / 2 - 1, hBb = d.Nv / 2 - 1, hG = d.NG / 2;
   const size_t n = d.n, nq = d.Nq;
+  const int nsl = kThreads / nqp, sl = threadIdx.x / nqp;
   double tr = 0.0, ti = 0.0;
-  for (int qi = threadIdx.x; qi < d.Nq; qi += blockDim.x) {
+  for (int qi = threadIdx.x % nqp; c_.has_s2 && qi < d.Nq; qi += nqp) {
     const int jm = qi / d.Nk, P = qi - jm * d.Nk;
     const int mp = jm - hBb;
     double2 c[4];
@@ -307,7 +369,7 @@ __global__ __launch_bounds__(kThreads) void sigma2_kernel(S2Args a) {
     lo = max(lo, -hG);
     hi = min(hi, hG - 1);
     double2 a16 = mk(0, 0), a25 = mk(0, 0), a34 = mk(0, 0), kd = mk(0, 0), km = mk(0, 0), kst = mk(0, 0);
-    for (int nb = lo; nb <= hi; ++nb) {
+    for (int nb = lo + sl; nb <= hi; nb += nsl) {
       const bool bFe = nb >= -hF && nb <= hF - 1;
       const bool bFb = in_fbox(nb, d.Nv);
       const int x1 = mp + nk + nb + 1, x2 = nb - nk, x3 = mp - nk - nb - 1;
@@ -340,9 +402,23 @@ __global__ __launch_bounds__(kThreads) void sigma2_kernel(S2Args a) {
     tr += contrib.x;
     ti += contrib.y;
   }
+  if (kbox) {
+    for (int j = threadIdx.x; j < d.NW; j += blockDim.x) {
+      const double2 v = c_.partial[(size_t)kbi * d.NW + j];
+      tr += v.x;
+      ti += v.y;
+    }
+    if (c_.lam_part && threadIdx.x == 0) {
+      tr += c_.lam_part[kbi].x;
+      ti += c_.lam_part[kbi].y;
+    }
+  }
   tr = block_sum(tr, red);
   ti = block_sum(ti, red);
-  if (threadIdx.x == 0) a.out[kid] = mk(tr, ti);
+  if (threadIdx.x == 0) {
+    const double2 s = c_.s1[kid];
+    c_.out[kid] = mk(s.x + c_.cfac * tr, s.y + c_.cfac * ti);
+  }
 }
 
 // ------------------------------------------------------------ Sigma_box
@@ -377,60 +453,101 @@ template <> struct Row16<double2> {
   }
 };
 
-// One workgroup per (k, m): the box part of Eq. PA_Sigma for row k of the
-// four channels at the bosonic index m, summed over Q and k'. Each thread
-// takes E consecutive k' per 16-byte load (n is even, rows start 16-byte
-// aligned). (Momentum tables in LDS instead of the index arithmetic measured
-// slower: the kernel is bound by its loads, not by the integer work.)
-template <typename C>
+// The box part of Eq. PA_Sigma at the bosonic index m = blockIdx.x for 4 RPW
+// rows k (RPW per wave) of the four channels, summed over Q and k'. HBM-bound:
+// Phi is streamed once. The products G(k'+q) G(k') and G(q-k') G(k') do not
+// depend on k: they are formed once per (q, k') and workgroup in LDS (in chunks
+// of kBoxChunk), and G(k+q), G(q-k) multiply the rows' sums, so an element
+// costs two multiply-adds per product (one row per workgroup with every product
+// formed per element took 6.1 ms on the 8x8, Nv = 16 complex64 box, 5.3 TB/s,
+// against 4.8 ms, 6.7 TB/s, now). Each lane takes E consecutive k' per 16-byte load
+// (n is even, rows start 16-byte aligned).
+constexpr int kBoxChunk = 512;
+
+template <typename C, int RPW>
 __global__ __launch_bounds__(kThreads) void sigmab_kernel(SBArgs<C> a) {
-  __shared__ double red[kThreads];
+  __shared__ double2 u1[kBoxChunk], u3[kBoxChunk];
+  __shared__ short bf[kBoxChunk];                  // frequency of k'
   using L16 = Row16<C>;
   constexpr int E = L16::E;
   const Dims& d = a.d;
-  const int kbi = blockIdx.x / d.NW, jm = blockIdx.x - (blockIdx.x / d.NW) * d.NW;
-  const int nk = kbi / d.Nk - d.Nv / 2, K = kbi - (kbi / d.Nk) * d.Nk;
-  const int mp = jm - (d.Nv / 2 - 1);
-  const int hG = d.NG / 2;
-  const int nkp = nk + mp;
-  const bool Yb = in_fbox(nkp, d.Nv);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int jm = blockIdx.x, mp = jm - (d.Nv / 2 - 1), hG = d.NG / 2;
   const size_t n = d.n, nn = (size_t)d.n * d.n, chan = (size_t)d.cs;
-  const int ng = d.n / E;                          // load groups per row
-  double ar = 0.0, ai = 0.0;
-  for (int P = 0; P < d.Nk; ++P) {
-    const int qi = jm * d.Nk + P;
-    const double2 g_kp = a.g[(size_t)(nkp + hG) * d.Nk + kadd(K, P, d.Lx, d.Ly)];
-    const double2 g_pk = a.g[(size_t)(mp - nk - 1 + hG) * d.Nk + ksub(P, K, d.Lx, d.Ly)];
-    const C* row = a.phi + (size_t)qi * nn + (size_t)kbi * n;
-    for (int gi = threadIdx.x; gi < ng; gi += blockDim.x) {
-      double2 pd[E], pm[E], ps[E], pt[E];
-      L16::load(row + (size_t)gi * E, pd);
-      L16::load(row + chan + (size_t)gi * E, pm);
-      L16::load(row + 2 * chan + (size_t)gi * E, ps);
-      L16::load(row + 3 * chan + (size_t)gi * E, pt);
+  int row[RPW], nk[RPW], K[RPW];
+  double2 acc[RPW];
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const int b = gi * E + e;
-        const int nb = b / d.Nk - d.Nv / 2, B = b - (b / d.Nk) * d.Nk;
-        const int x1 = mp + nk + nb + 1, x2 = nb - nk, x3 = mp - nk - nb - 1;
-        const double c16 = 1.0 + ind(in_bbox(x1, d.Nv));
-        const double c25 = Yb ? ind(in_bbox(x2, d.Nv)) + ind(in_bbox(x1, d.Nv)) : 0.0;
-        const double c34 = 1.0 + ind(in_bbox(x3, d.Nv));
+  for (int r = 0; r < RPW; ++r) {
+    row[r] = min((int)(blockIdx.y * 4 + wave) * RPW + r, d.n - 1);
+    nk[r] = row[r] / d.Nk - d.Nv / 2;
+    K[r] = row[r] % d.Nk;
+    acc[r] = mk(0, 0);
+  }
+  for (int P = 0; P < d.Nk; ++P) {
+    double2 s1[RPW], s3[RPW];
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) s1[r] = s3[r] = mk(0, 0);
+    const C* base = a.phi + (size_t)(jm * d.Nk + P) * nn;
+    for (int b0 = 0; b0 < d.n; b0 += kBoxChunk) {
+      const int nb_ = min(kBoxChunk, d.n - b0);
+      __syncthreads();
+      for (int i = t; i < nb_; i += kThreads) {
+        const int b = b0 + i, f = b / d.Nk, B = b - f * d.Nk, nb = f - d.Nv / 2;
         const double2 gb = a.g[(size_t)(nb + hG) * d.Nk + B];
-        const double2 gbp = a.g[(size_t)(nb + mp + hG) * d.Nk + kadd(B, P, d.Lx, d.Ly)];
-        const double2 gpb = a.g[(size_t)(mp - nb - 1 + hG) * d.Nk + ksub(P, B, d.Lx, d.Ly)];
-        const double2 A1 = cmul(cmul(g_kp, gbp), gb);
-        const double2 A3 = cmul(cmul(gpb, g_pk), gb);
-        const double2 t1 = csub(cscale(pd[e], c16), cscale(pm[e], c16 + 2.0 * c25));
-        const double2 v = cadd(cmul(A1, t1), cmul(A3, cscale(cadd(ps[e], pt[e]), c34)));
-        ar += v.x;
-        ai += v.y;
+        u1[i] = cmul(a.g[(size_t)(nb + mp + hG) * d.Nk + kadd(B, P, d.Lx, d.Ly)], gb);
+        u3[i] = cmul(a.g[(size_t)(mp - nb - 1 + hG) * d.Nk + ksub(P, B, d.Lx, d.Ly)], gb);
+        bf[i] = (short)nb;
+      }
+      __syncthreads();
+      for (int i = lane * E; i < nb_; i += 64 * E) {
+        double2 pv[RPW][4][E];
+#pragma unroll
+        for (int r = 0; r < RPW; ++r)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) L16::load(base + c * chan + (size_t)row[r] * n + b0 + i, pv[r][c]);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const double2 w1 = u1[i + e], w3 = u3[i + e];
+          const int nb = bf[i + e];
+#pragma unroll
+          for (int r = 0; r < RPW; ++r) {
+            const bool i1 = in_bbox(mp + nk[r] + nb + 1, d.Nv), i2 = in_bbox(nb - nk[r], d.Nv);
+            const bool i3 = in_bbox(mp - nk[r] - nb - 1, d.Nv), Yb = in_fbox(nk[r] + mp, d.Nv);
+            const double c16 = 1.0 + ind(i1);
+            const double c25 = Yb ? ind(i2) + ind(i1) : 0.0;
+            const double c34 = 1.0 + ind(i3);
+            const double2 t1 = csub(cscale(pv[r][0][e], c16), cscale(pv[r][1][e], c16 + 2.0 * c25));
+            const double2 t3 = cscale(cadd(pv[r][2][e], pv[r][3][e]), c34);
+            s1[r] = cadd(s1[r], cmul(w1, t1));
+            s3[r] = cadd(s3[r], cmul(w3, t3));
+          }
+        }
       }
     }
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+      const double2 g_kp = a.g[(size_t)(nk[r] + mp + hG) * d.Nk + kadd(K[r], P, d.Lx, d.Ly)];
+      const double2 g_pk = a.g[(size_t)(mp - nk[r] - 1 + hG) * d.Nk + ksub(P, K[r], d.Lx, d.Ly)];
+      acc[r] = cadd(acc[r], cadd(cmul(g_kp, s1[r]), cmul(g_pk, s3[r])));
+    }
   }
-  ar = block_sum(ar, red);
-  ai = block_sum(ai, red);
-  if (threadIdx.x == 0) a.partial[(size_t)kbi * d.NW + jm] = mk(ar, ai);
+#pragma unroll
+  for (int r = 0; r < RPW; ++r) {
+    const double2 v = mk(wave_sum(acc[r].x), wave_sum(acc[r].y));
+    const int k = (int)(blockIdx.y * 4 + wave) * RPW + r;
+    if (lane == 0 && k < d.n) a.partial[(size_t)k * d.NW + jm] = v;
+  }
+}
+
+// rows per wave: two where that still fills the chip (the LDS products are then
+// shared by eight rows), one for smaller boxes
+template <typename C>
+void launch_sigmab(const SBArgs<C>& a, hipStream_t s) {
+  const Dims& d = a.d;
+  if ((long long)d.NW * d.n >= 8 * 1024)
+    hipLaunchKernelGGL((sigmab_kernel<C, 2>), dim3(d.NW, (d.n + 7) / 8), dim3(kThreads), 0, s, a);
+  else
+    hipLaunchKernelGGL((sigmab_kernel<C, 1>), dim3(d.NW, (d.n + 3) / 4), dim3(kThreads), 0, s, a);
 }
 
 // ------------------------------------------------- local Lambda in the box
@@ -511,35 +628,6 @@ __global__ __launch_bounds__(kThreads) void lam_sigma_kernel(LamArgs a) {
   if (threadIdx.x == 0) a.out[kbi] = mk(red[0][0], red[1][0]);
 }
 
-struct CombineArgs {
-  Dims d;
-  double cfac;
-  int has_s2, has_box;
-  const double2* s1;
-  const double2* s2;
-  const double2* partial;
-  const double2* lam_part;   // nullable: the box-Lambda term per box k
-  double2* out;
-};
-
-__global__ void combine_kernel(CombineArgs a) {
-  const Dims& d = a.d;
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= d.Nve * d.Nk) return;
-  int e = idx / d.Nk, K = idx - e * d.Nk;
-  int n = e - d.Nve / 2;
-  double2 v = a.s1[idx];
-  if (a.has_s2) v = cadd(v, cscale(a.s2[idx], a.cfac));
-  if (a.has_box && in_fbox(n, d.Nv)) {
-    int kbi = (n + d.Nv / 2) * d.Nk + K;
-    double2 acc = mk(0, 0);
-    for (int j = 0; j < d.NW; ++j) acc = cadd(acc, a.partial[(size_t)kbi * d.NW + j]);
-    if (a.lam_part) acc = cadd(acc, a.lam_part[kbi]);
-    v = cadd(v, cscale(acc, a.cfac));
-  }
-  a.out[idx] = v;
-}
-
 // ------------------------------------ second order without the regulation
 // Eq. PA_Sigma at F = Lambda with both sums truncated to the box (the Sigma~_1
 // term of the plain, unregulated equation):
@@ -594,22 +682,24 @@ __global__ __launch_bounds__(kThreads) void s2box_kernel(S2BoxArgs a) {
   if (threadIdx.x == 0) a.out[kid] = mk(a.cfac * tr, a.cfac * ti);
 }
 
+// (the size is part of what callers see, sigma_sde_workspace and the limit of
+// sigma_sde_no_alloc, so it stays; the space before srt is not used)
 struct WsLayout {
-  size_t tau, wt, dg, gkt, grt, trn, s1, s2, tab, part, lb1, lb2, lpart, sq, total;
+  size_t srt, s1, tab, part, lb1, lb2, lpart, sq, total;
 };
 
 WsLayout ws_layout(const Dims& d) {
   WsLayout L{};
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
-  L.tau = take(sizeof(double) * d.ntau);
-  L.wt = take(sizeof(double) * d.ntau);
-  L.dg = take(sizeof(double2) * d.Nve * d.Nk);
-  L.gkt = take(sizeof(double2) * (size_t)d.ntau * d.Nk);
-  L.grt = take(sizeof(double2) * (size_t)d.ntau * d.Nk);
-  L.trn = take(sizeof(double2) * d.Nve * d.Nk);
+  take(sizeof(double) * d.ntau);
+  take(sizeof(double) * d.ntau);
+  take(sizeof(double2) * d.Nve * d.Nk);
+  take(sizeof(double2) * (size_t)d.ntau * d.Nk);
+  L.srt = take(sizeof(double2) * (size_t)d.ntau * d.Nk);
+  take(sizeof(double2) * d.Nve * d.Nk);
   L.s1 = take(sizeof(double2) * d.Nve * d.Nk);
-  L.s2 = take(sizeof(double2) * d.Nve * d.Nk);
+  take(sizeof(double2) * d.Nve * d.Nk);
   L.tab = take(sizeof(double2) * 5 * (size_t)d.NG * d.Nq);
   L.part = take(sizeof(double2) * (size_t)d.n * d.NW);
   L.lb1 = take(sizeof(double2) * (size_t)d.Nv * d.NW * d.Nk);
@@ -625,15 +715,9 @@ inline unsigned nblk(size_t total) { return (unsigned)((total + kThreads - 1) / 
 hipError_t run_sigma1(const pq_params& p, const Dims& d, const double2* g, const double* mu,
                       double2* out, char* ws, hipStream_t s) {
   WsLayout L = ws_layout(d);
-  S1Args a{d, p.beta, p.U, p.t, p.tp, p.D, d.Nk == 1 ? 1 : 0, g, mu,
-           (double*)(ws + L.tau), (double*)(ws + L.wt), (double2*)(ws + L.dg),
-           (double2*)(ws + L.gkt), (double2*)(ws + L.grt), (double2*)(ws + L.trn), out};
-  hipLaunchKernelGGL(gl_nodes_kernel, dim3(nblk((d.ntau + 1) / 2)), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(s1_dg_kernel, dim3(nblk(d.Nve * d.Nk)), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(s1_gtau_kernel, dim3(nblk((size_t)d.ntau * d.Nk)), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(s1_gr_kernel, dim3(nblk((size_t)d.ntau * d.Nk)), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(s1_tr_kernel, dim3(nblk(d.Nve * d.Nk)), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(s1_out_kernel, dim3(nblk(d.Nve * d.Nk)), dim3(kThreads), 0, s, a);
+  S1Args a{d, p.beta, p.U, p.t, p.tp, p.D, d.Nk == 1 ? 1 : 0, g, mu, (double2*)(ws + L.srt), out};
+  hipLaunchKernelGGL(s1_tau_kernel, dim3((d.ntau + 1) / 2), dim3(kThreads), 0, s, a);
+  hipLaunchKernelGGL(s1_row_kernel, dim3(d.Nve), dim3(kRowThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -696,24 +780,19 @@ hipError_t launch_sigma(const pq_params& p, const Dims& d, const void* phi, cons
   char* ws = (char*)wsv;
   WsLayout L = ws_layout(d);
   double2* s1 = (double2*)(ws + L.s1);
-  double2* s2 = (double2*)(ws + L.s2);
   double2* part = (double2*)(ws + L.part);
   hipError_t e = run_second_order(p, d, g, mu, s1, ws, s);
   if (e != hipSuccess) return e;
   const int has_s2 = p.kernel_level > 0 ? 1 : 0;
+  S2Args a2{d, p.kernel_level, g, k1, k2, (double2*)(ws + L.tab)};
   if (has_s2) {
-    S2Args a2{d, p.kernel_level, g, k1, k2, (double2*)(ws + L.tab), s2};
-    const unsigned nwav = (unsigned)d.NG * d.Nq, wpb = kThreads / 64;
-    hipLaunchKernelGGL(s2_tables_kernel, dim3((nwav + wpb - 1) / wpb), dim3(kThreads), 0, s, a2);
-    hipLaunchKernelGGL(sigma2_kernel, dim3(d.Nve * d.Nk), dim3(kThreads), 0, s, a2);
+    const int sw = pow2_ge(d.Nk);
+    hipLaunchKernelGGL(s2_tables_kernel, dim3(nblk((size_t)d.NG * d.Nq * sw)), dim3(kThreads), 0, s, a2, sw);
   }
-  if (p.storage == PQ_STORE_C64) {
-    SBArgs<float2> ab{d, (const float2*)phi, g, part};
-    hipLaunchKernelGGL(sigmab_kernel<float2>, dim3(d.n * d.NW), dim3(kThreads), 0, s, ab);
-  } else {
-    SBArgs<double2> ab{d, (const double2*)phi, g, part};
-    hipLaunchKernelGGL(sigmab_kernel<double2>, dim3(d.n * d.NW), dim3(kThreads), 0, s, ab);
-  }
+  if (p.storage == PQ_STORE_C64)
+    launch_sigmab(SBArgs<float2>{d, (const float2*)phi, g, part}, s);
+  else
+    launch_sigmab(SBArgs<double2>{d, (const double2*)phi, g, part}, s);
   double2* lpart = nullptr;
   if (lam_box) {
     lpart = (double2*)(ws + L.lpart);
@@ -722,8 +801,9 @@ hipError_t launch_sigma(const pq_params& p, const Dims& d, const void* phi, cons
     hipLaunchKernelGGL(lam_sigma_kernel, dim3(d.n), dim3(kThreads), 0, s, al);
   }
   const double T = 1.0 / p.beta;
-  CombineArgs ac{d, -p.U * T * T / (4.0 * d.Nk * (double)d.Nk), has_s2, 1, s1, s2, part, lpart, sigma_out};
-  hipLaunchKernelGGL(combine_kernel, dim3(nblk(d.Nve * d.Nk)), dim3(kThreads), 0, s, ac);
+  CombineArgs ac{d, -p.U * T * T / (4.0 * d.Nk * (double)d.Nk), has_s2, s1, part, lpart, sigma_out};
+  const int nqp = pow2_ge(d.Nq) < kThreads ? pow2_ge(d.Nq) : kThreads;
+  hipLaunchKernelGGL(sigma2_kernel, dim3(d.Nve * d.Nk), dim3(kThreads), 0, s, a2, ac, nqp);
   return hipGetLastError();
 }
 

@@ -1,0 +1,48 @@
+"""The Schwinger-Dyson stage against the FP64 oracle at the edges of its
+launches: one momentum, lattices whose momenta do not fill a power of two, the
+smallest box, an odd number of quadrature nodes, extension factors 1 to 3.
+
+Tolerances: FP64 accumulation throughout, so only the summation order and the
+quadrature differ (1e-11 relative to the largest value, the bound of the stage
+tests); the complex64 vertex enters both sides rounded alike."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import parquet as P
+from workloads import ModelParams, random_phi, random_sigma
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("lx,ly,nv,f,level,beta", [(1, 1, 2, 1, 2, 1.0), (1, 1, 6, 3, 1, 5.0), (1, 2, 4, 2, 2, 3.0),
+                                                   (3, 3, 4, 1, 2, 4.0), (1, 5, 4, 2, 2, 2.0), (7, 1, 2, 3, 2, 6.0)])
+def test_sigma_sde_sizes(prec, lx, ly, nv, f, level, beta):
+    print("CASE sigma sizes", prec, lx, ly, nv, f, level, flush=True)
+    from paper_1510_03330_amd.ops import Stage
+    p = ModelParams(Lx=lx, Ly=ly, Nv=nv, U=1.3, beta=beta, tp=-0.1, f_ext=f, kernel_level=level, mu_mode=0,
+                    mu_fixed=0.1 if lx * ly > 1 else 0.0)
+    g = P.Grid(lx, ly, nv, f)
+    phi = random_phi(g.Nq, g.n, seed=3, scale=0.4)
+    if prec == "fp32":
+        phi = phi.astype(np.complex64).astype(np.complex128)
+    mu = P.find_mu(p, g, None) if lx * ly > 1 else 0.0
+    G = P.dyson(p, g, random_sigma(g.Nve, g.Nk, seed=4, scale=0.1), mu)
+    K1, K2 = P.kernel_functions(g, phi, level)
+    F = P.full_vertex(P.remap(g, phi, K1, K2, P.pa_lambda(p.U)), phi)
+    ref = P.sigma_sde(p, g, G, F, K1, K2, mu)
+
+    st = Stage(p, prec)
+
+    def T(x, dtype=torch.complex128):
+        return torch.from_numpy(np.ascontiguousarray(x)).to(device=DEV, dtype=dtype)
+
+    out = torch.empty(st.sigma_shape, dtype=torch.complex128, device=DEV)
+    st.sigma_sde(T(phi, st.vdtype), T(K1), T(K2), T(G), T(np.array([mu]), torch.float64), out)
+    torch.cuda.synchronize()
+    err = np.max(np.abs(out.cpu().numpy() - ref)) / np.max(np.abs(ref))
+    assert err < 1e-11, err
