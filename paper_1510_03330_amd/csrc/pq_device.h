@@ -87,6 +87,28 @@ __device__ inline int ksub(int a, int b, int Lx, int Ly) {
 }
 
 // ------------------------------------------------------ reductions
+// Sum over each group of L = 16, 32 or 64 lanes of a wave, left in the group's
+// last lane: row shifts and row broadcasts on the vector unit (a shuffle per
+// step goes through the LDS crossbar, several times the latency). All lanes
+// must be active.
+template <int CTRL, int ROWS>
+__device__ inline double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+template <int L>
+__device__ inline double group_total(double v) {
+  static_assert(L == 16 || L == 32 || L == 64, "rows of 16 lanes");
+  v = dpp_add<0x111, 0xf>(v);                   // row_shr 1, 2, 4, 8
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  if (L >= 32) v = dpp_add<0x142, 0xa>(v);      // row_bcast 15 into rows 1 and 3
+  if (L >= 64) v = dpp_add<0x143, 0xc>(v);      // row_bcast 31 into rows 2 and 3
+  return v;
+}
+
 // Deterministic block reduction of doubles (fixed tree). blockDim.x must be a
 // power of two <= 1024; `red` is LDS of blockDim.x doubles.
 __device__ inline double block_sum(double v, double* red) {

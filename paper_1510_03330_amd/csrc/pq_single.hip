@@ -12,7 +12,7 @@ namespace pq {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kMaxNk = 1024;
+constexpr int kMaxNk = 64;          // momenta of the largest lattice (one wave)
 
 struct DysonArgs {
   Dims d;
@@ -47,57 +47,117 @@ __device__ inline double2 g_lattice(const DysonArgs& a, const double* eps, doubl
   return crecip(z);
 }
 
-// Total density per spin at mu: 1/2 + T/N sum Re G + the exact tail beyond the grid.
-__device__ double density(const DysonArgs& a, const double* eps, double mu, double* red) {
-  const Dims& d = a.d;
-  const double T = 1.0 / a.beta;
-  double acc = 0.0;
-  for (int idx = threadIdx.x; idx < d.NG * d.Nk; idx += blockDim.x) {
-    int gi = idx / d.Nk, K = idx - gi * d.Nk;
-    acc += g_lattice(a, eps, mu, gi, K).x;
-  }
-  double sre = block_sum(acc, red);
-  double tail = 0.0;
-  for (int K = threadIdx.x; K < d.Nk; K += blockDim.x) {
-    double xi = eps[K] - mu;
-    double partial = 0.0;
-    for (int n = 0; n < d.NG / 2; ++n) {
-      double nu = nu_of(n, a.beta);
-      partial += 1.0 / (nu * nu + xi * xi);
-    }
-    double full = fabs(xi) < 1e-300 ? a.beta * a.beta / 8.0
-                                    : a.beta * tanh(a.beta * xi / 2.0) / (4.0 * xi);
-    tail += -xi * (full - partial);
-  }
-  double stail = block_sum(tail, red);
-  return 0.5 + (T / d.Nk) * sre + 2.0 * (T / d.Nk) * stail;
+// 1 / v of a normal v: the hardware estimate and two Newton steps (about 1 ulp)
+__device__ inline double rcp_nr(double v) {
+  double r = __builtin_amdgcn_rcp(v);
+  r = fma(r, fma(-v, r, 1.0), r);
+  return fma(r, fma(-v, r, 1.0), r);
 }
 
-__global__ __launch_bounds__(kThreads) void dyson_kernel(DysonArgs a) {
-  __shared__ double red[kThreads];
+// One value of the self-energy as the density needs it: a = eps + Re Sigma and
+// y^2 = (nu - Im Sigma)^2, with eps and nu^2 of the same G without Sigma. Beyond
+// 1e75 the value is held at 1e75 (its part of the density is zero there in any
+// case, and the products of density_term stay finite); NaN stays NaN.
+struct DElem {
+  double a, y2, e, nu2;
+};
+__device__ inline DElem d_elem(const DysonArgs& p, const double* eps, int idx) {
+  const int row = idx / p.d.Nk, K = idx - row * p.d.Nk;
+  const double nu = nu_of(row - p.d.Nve / 2, p.beta);
+  const double2 s = p.sigma[idx];
+  DElem v;
+  v.e = eps[K];
+  v.nu2 = nu * nu;
+  v.a = v.e + s.x;
+  v.a = v.a > 1e75 ? 1e75 : (v.a < -1e75 ? -1e75 : v.a);
+  const double y = nu - s.y, y2 = y * y;
+  v.y2 = y2 > 1e150 ? 1e150 : y2;
+  return v;
+}
+
+// Re [G - G(Sigma = 0)] at mu, with x = mu - a and z = mu - eps:
+// x / (x^2 + y^2) - z / (z^2 + nu^2) over one common denominator
+__device__ inline double density_term(const DElem& v, double mu) {
+  const double x = mu - v.a, z = mu - v.e;
+  const double d1 = fma(x, x, v.y2), d2 = fma(z, z, v.nu2);
+  return fma(x, d2, -z * d1) * rcp_nr(d1 * d2);
+}
+
+// Dyson equation in one workgroup. The filling is a chain of about 52 bisection
+// steps, so the kernel is bound by the latency of one density, not by its work.
+// The density per spin is that of Sigma = 0, (1/N) sum_K f(xi_K) in closed form,
+// plus T/N sum Re (G - G_0) over the extended box (Sigma is zero beyond it), one
+// reciprocal per value; the values stay in registers. 2^LV - 1 points of the
+// bisection tree below the present bracket are evaluated at once, each by LP
+// lanes, and the path through them is the one bisection takes: LV steps per
+// pass. A pass costs the values of every point plus a fixed part per wave (the
+// Fermi function, the sum, the barrier), so few values take many points on few
+// lanes, many values one point on every lane. Measured before (256 threads, one
+// point at a time, three divisions per value of the whole grid, tail sums per
+// step): 213 us at 4x4, Nv = 8, 490 us at 8x8, Nv = 16; now 26 and 45 us.
+constexpr int dyson_threads(int lv, int lp) { return (((1 << lv) - 1) * lp + 63) / 64 * 64; }
+
+template <int LV, int LP, int RE>
+__global__ __launch_bounds__(dyson_threads(LV, LP)) void dyson_kernel(DysonArgs a) {
+  constexpr int NC = (1 << LV) - 1;                  // points per pass
+  constexpr int LG = LP < 64 ? LP : 64;              // lanes of one partial sum
+  constexpr int W = LP / LG;                         // partial sums per point
   __shared__ double eps[kMaxNk];
+  __shared__ double part[2][NC * W];
   const Dims& d = a.d;
-  for (int K = threadIdx.x; K < d.Nk; K += blockDim.x) eps[K] = a.local ? 0.0 : eps_of(K, d, a.t, a.tp);
+  const int t = threadIdx.x, lane = t & 63;
+  if (t < d.Nk) eps[t] = a.local ? 0.0 : eps_of(t, d, a.t, a.tp);
   __syncthreads();
   double mu = a.mu_fixed;
   if (!a.local && a.mu_mode == 1) {
-    double emin = 1e300, emax = -1e300;
-    for (int K = threadIdx.x; K < d.Nk; K += blockDim.x) {
-      emin = fmin(emin, eps[K]);
-      emax = fmax(emax, eps[K]);
+    double emin = eps[min(lane, d.Nk - 1)], emax = emin;
+    for (int o = 32; o > 0; o >>= 1) {
+      emin = fmin(emin, __shfl_xor(emin, o, 64));
+      emax = fmax(emax, __shfl_xor(emax, o, 64));
     }
-    emin = -block_max(-emin, red);
-    emax = block_max(emax, red);
+    const int c = t / LP + 1, pl = t % LP;           // this lane's point (heap index) and place in it
+    const int total = d.Nve * d.Nk, cnt = (total + LP - 1) / LP;
+    DElem v[RE];
+#pragma unroll
+    for (int q = 0; q < RE; ++q) {
+      const int idx = q * LP + pl;
+      if (q < cnt && idx < total) v[q] = d_elem(a, eps, idx);
+      else v[q] = DElem{0.0, 1.0, 0.0, 1.0};        // contributes zero
+    }
+    const double tn = 1.0 / (a.beta * d.Nk);
     double lo = emin - 10.0 - fabs(a.U), hi = emax + 10.0 + fabs(a.U);
-    for (int it = 0; it < 200; ++it) {
-      double mid = 0.5 * (lo + hi);
-      double nn = 2.0 * density(a, eps, mid, red);
-      if (nn > a.filling) hi = mid; else lo = mid;
-      if (hi - lo < 1e-14) break;
+    bool done = false;
+    for (int it = 0, pass = 0; it < 200 && !done; ++pass) {
+      double l = lo, h = hi, m = 0.5 * (l + h);     // the point of heap index c below the bracket
+      for (int b = 30 - __clz(c); b >= 0; --b) {
+        if ((c >> b) & 1) l = m; else h = m;
+        m = 0.5 * (l + h);
+      }
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < RE; ++q) s += density_term(v[q], m);
+      for (int idx = RE * LP + pl; idx < total; idx += LP) s += density_term(d_elem(a, eps, idx), m);
+      s *= tn;
+      for (int K = pl; K < d.Nk; K += LP) s += 1.0 / (d.Nk * (exp(a.beta * (eps[K] - m)) + 1.0));
+      s = group_total<LG>(s);
+      if (c <= NC && lane % LG == LG - 1) part[pass & 1][t / LG] = s;
+      __syncthreads();
+      // bit i: the density at point i + 1 is above the filling
+      double nn = 0.0;
+      for (int w = 0; w < W; ++w) nn += part[pass & 1][(lane % NC) * W + w];
+      const unsigned long long above = __ballot(2.0 * nn > a.filling);
+      int node = 1;
+      for (int k = 0; k < LV && it < 200 && !done; ++k, ++it) {
+        const double mid = 0.5 * (lo + hi);
+        const bool ab = (above >> (node - 1)) & 1;
+        if (ab) hi = mid; else lo = mid;
+        node = 2 * node + (ab ? 0 : 1);
+        done = hi - lo < 1e-14;
+      }
     }
     mu = 0.5 * (lo + hi);
   }
-  for (int idx = threadIdx.x; idx < d.NG * d.Nk; idx += blockDim.x) {
+  for (int idx = t; idx < d.NG * d.Nk; idx += blockDim.x) {
     int gi = idx / d.Nk, K = idx - gi * d.Nk;
     double2 gv;
     if (a.local) {
@@ -113,7 +173,7 @@ __global__ __launch_bounds__(kThreads) void dyson_kernel(DysonArgs a) {
     }
     a.g[idx] = gv;
   }
-  if (threadIdx.x == 0) *a.mu_out = a.local ? 0.0 : mu;
+  if (t == 0) *a.mu_out = a.local ? 0.0 : mu;
 }
 
 struct BubbleArgs {
@@ -226,7 +286,21 @@ hipError_t launch_dyson(const pq_params& p, const Dims& d, const double2* sigma,
   if (d.Nk > kMaxNk) return hipErrorInvalidValue;
   DysonArgs a{d, p.beta, p.t, p.tp, p.D, p.filling, p.mu_fixed, p.U, p.mu_mode, d.Nk == 1 ? 1 : 0,
               sigma, g, mu_out};
-  hipLaunchKernelGGL(dyson_kernel, dim3(1), dim3(kThreads), 0, s, a);
+  // points per pass and lanes per point by the number of self-energy values, the
+  // shape whose pass costs least per bisection step (256 values: 16 lanes
+  // per point 26 us, a wave per point 33; 1024: 3 steps on 128 lanes per point 48,
+  // 2 on 256 lanes 35; 2048: 2 on 256 lanes 58, 1 on 1024 lanes 50, on 512 45)
+  const int values = d.Nve * d.Nk;
+#define PQ_DYSON(LV, LP, RE) \
+  hipLaunchKernelGGL((dyson_kernel<LV, LP, RE>), dim3(1), dim3(dyson_threads(LV, LP)), 0, s, a)
+  if (values <= 16 * 8) PQ_DYSON(4, 16, 8);
+  else if (values <= 16 * 16) PQ_DYSON(4, 16, 16);
+  else if (values <= 128 * 4) PQ_DYSON(2, 128, 4);
+  else if (values <= 256 * 4) PQ_DYSON(2, 256, 4);
+  else if (values <= 512 * 4) PQ_DYSON(1, 512, 4);
+  else if (values <= 1024 * 4) PQ_DYSON(1, 1024, 4);
+  else PQ_DYSON(1, 1024, 8);
+#undef PQ_DYSON
   return hipGetLastError();
 }
 
