@@ -27,96 +27,296 @@ namespace {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kGT = 64;          // C tile edge of one workgroup (2 x 2 waves of 32 x 32)
-constexpr int kGK = 32;          // K depth staged per LDS round (two 16-deep matrix-core steps)
-constexpr int kLd = kGK + 8;     // LDS row stride in bf16 (80 bytes: rows stay 16-byte aligned)
+// ---- products -------------------------------------------------------------
+// At the sizes of the warm start (batches of tens to hundreds, widths of a few
+// hundred) a product is latency: one 32 x 32 tile per workgroup, whose eight
+// waves bring kKC of K into LDS at once (an activation or gradient as hi + lo, a
+// weight as its bf16 value) in the matrix cores' operand order; one wave then
+// runs the chain of products over K in order (two per 16 of K: about 0.5 us for
+// 512), so every output is one FP32 accumulation over ascending k. The weight
+// gradient (K is the batch, both operands FP32, lo x lo dropped) reads its
+// operands straight into registers, a tile per wave. 64 x 512 x 512 forward:
+// 6.3 us, against 59 us with 64 x 64 tiles staged 32 of K at a time (8
+// workgroups, two barriers per round); the whole step at batch 64 63 us
+// against 520, at batch 65536 20 ms against 112.
+constexpr int kSW = 8;                       // waves per workgroup
+constexpr int kSThreads = 64 * kSW;
+constexpr int kKG = 64, kKC = 8 * kKG;       // K staged at a time, in groups of 8
+constexpr int kGU = 2;                       // steps in flight of the weight gradient
 
-// C[m][n] = sum_k A(m, k) B(k, n) (+ bias[n]); epilogue 1: tanh; epilogue 2:
-// multiply by (1 - E[m][n]^2) (tanh backward). A(m, k) = A[m sam + k sak] is
-// FP32 and enters as hi + lo; B(k, n) = B[k sbk + n sbn] is the bf16 weight
-// array (BSPLIT false, one term) or FP32 (BSPLIT true, hi + lo; the lo x lo
-// product is dropped). A 64 x 64 tile per workgroup, LDS rounds of 32 in k,
-// zero-filled outside the matrix.
-template <bool BSPLIT>
-__global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, const float* A, long sam, long sak,
-                                                        const void* Bv, long sbk, long sbn, float* C, long scm,
-                                                        const float* bias, int epi, const float* E) {
-  __shared__ __attribute__((aligned(16))) __bf16 Ahi[kGT][kLd];
-  __shared__ __attribute__((aligned(16))) __bf16 Alo[kGT][kLd];
-  __shared__ __attribute__((aligned(16))) __bf16 Bhi[kGT][kLd];     // stored [n][k]
-  __shared__ __attribute__((aligned(16))) __bf16 Blo[BSPLIT ? kGT : 1][kLd];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = w & 1, wn = w >> 1;
-  const int m0 = blockIdx.y * kGT, n0 = blockIdx.x * kGT;
-  const bool a_kfast = sak == 1, b_kfast = sbk == 1;
+// this lane's 8 consecutive k of one row or column; VEC: k contiguous, K a
+// multiple of 8 and 16-byte aligned rows; values past K (or of a row past the
+// matrix, ok = false) are zero
+template <bool VEC>
+__device__ inline void load8(const float* p, long sk, int k, int K, bool ok, float (&v)[8]) {
+  if constexpr (VEC) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    f4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+    if (ok && k < K) {
+      a = *(const f4*)(p + k);
+      b = *(const f4*)(p + k + 4);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = a[e];
+      v[4 + e] = b[e];
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = ok && k + e < K ? p[(long)(k + e) * sk] : 0.f;
+  }
+}
+template <bool VEC>
+__device__ inline bf16x8 load8(const __bf16* p, long sk, int k, int K, bool ok) {
+  bf16x8 v;
+  if constexpr (VEC) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = (__bf16)0.f;
+    if (ok && k < K) v = *(const bf16x8*)(p + k);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = ok && k + e < K ? p[(long)(k + e) * sk] : (__bf16)0.f;
+  }
+  return v;
+}
+
+__device__ inline void split(const float (&v)[8], bf16x8& hi, bf16x8& lo) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    hi[e] = (__bf16)v[e];
+    lo[e] = (__bf16)(v[e] - (float)hi[e]);
+  }
+}
+
+// The gradient at the outputs, d = 2 (y - t) / count, formed where it is read
+// (t = nullptr: p holds d itself).
+struct GradSrc {
+  const float* p;
+  const float* t;
+  float count;
+  __device__ float at(size_t i) const {
+    const float v = p[i];
+    return t ? 2.f * (v - t[i]) / count : v;
+  }
+  // 8 consecutive values of a row of n from column k (VEC as in load8)
+  template <bool VEC>
+  __device__ void row8(size_t row, int k, int n, bool ok, float (&v)[8]) const {
+    load8<VEC>(p + row, 1, k, n, ok, v);
+    if (t) {
+      float u[8];
+      load8<VEC>(t + row, 1, k, n, ok, u);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = 2.f * (v[e] - u[e]) / count;
+    }
+  }
+};
+
+// The staged operands of a 32 x 32 tile: row or column r, k group g
+struct Stage {
+  bf16x8 ah[32][kKG + 1], al[32][kKG + 1], b[32][kKG + 1];
+};
+
+// C[m][n] = sum_k A(m, k) B(k, n) over the staged operands, by the first wave;
+// la(row, k, v[8]) and lb(col, k) give 8 consecutive k (zero outside the
+// matrices), f(row, col, sum) takes the elements, spread over the workgroup.
+template <class LA, class LB, class F>
+__device__ inline void tile_product(Stage& st, float (*out)[64], int K, LA la, LB lb, F f) {
+  constexpr int GPT = 32 * kKG / kSThreads;  // groups per thread and operand
+  const int t = threadIdx.x, lane = t & 63;
   floatx16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += kGK) {
+  for (int k0 = 0; k0 < K; k0 += kKC) {
+    float av[GPT][8];
+    bf16x8 bv[GPT];
 #pragma unroll
-    for (int i = 0; i < kGT * kGK / 256; ++i) {
-      const int e = tid + 256 * i;
-      const int am = a_kfast ? e / kGK : e % kGT, ak = a_kfast ? e % kGK : e / kGT;
-      float av = 0.f;
-      if (m0 + am < M && k0 + ak < K) av = A[(long)(m0 + am) * sam + (long)(k0 + ak) * sak];
-      const __bf16 h = (__bf16)av;
-      Ahi[am][ak] = h;
-      Alo[am][ak] = (__bf16)(av - (float)h);
-      const int bn = b_kfast ? e / kGK : e % kGT, bk = b_kfast ? e % kGK : e / kGT;
-      const bool in = n0 + bn < N && k0 + bk < K;
-      const long bi = (long)(k0 + bk) * sbk + (long)(n0 + bn) * sbn;
-      if constexpr (BSPLIT) {
-        const float bv = in ? ((const float*)Bv)[bi] : 0.f;
-        const __bf16 hb = (__bf16)bv;
-        Bhi[bn][bk] = hb;
-        Blo[bn][bk] = (__bf16)(bv - (float)hb);
-      } else {
-        Bhi[bn][bk] = in ? ((const __bf16*)Bv)[bi] : (__bf16)0.f;
-      }
+    for (int i = 0; i < GPT; ++i) {
+      const int e = t + i * kSThreads, r = e / kKG, k = k0 + 8 * (e % kKG);
+      la(r, k, av[i]);
+      bv[i] = lb(e, k0);
+    }
+    if (k0 > 0) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < GPT; ++i) {
+      const int e = t + i * kSThreads, r = e / kKG, g = e % kKG;
+      split(av[i], st.ah[r][g], st.al[r][g]);
+      lb.put(st, e, bv[i]);
     }
     __syncthreads();
-    const int ar = wm * 32 + (lane & 31), br = wn * 32 + (lane & 31), kk = 8 * (lane >> 5);
-#pragma unroll
-    for (int ks = 0; ks < kGK; ks += 16) {
-      const bf16x8 ah = *(const bf16x8*)&Ahi[ar][ks + kk];
-      const bf16x8 al = *(const bf16x8*)&Alo[ar][ks + kk];
-      const bf16x8 bh = *(const bf16x8*)&Bhi[br][ks + kk];
-      if constexpr (BSPLIT) {
-        const bf16x8 bl = *(const bf16x8*)&Blo[br][ks + kk];
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
+    if (t < 64) {
+      const int steps = (min(K - k0, kKC) + 15) / 16;
+#pragma unroll 4
+      for (int s = 0; s < steps; ++s) {
+        const int r = lane & 31, g = 2 * s + (lane >> 5);
+        const bf16x8 b = st.b[r][g];
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st.al[r][g], b, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st.ah[r][g], b, acc, 0, 0, 0);
       }
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
     }
-    __syncthreads();
   }
-  // accumulator element v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
-  const int n = n0 + wn * 32 + (lane & 31);
-  if (n >= N) return;
-  const float b = bias ? bias[n] : 0.f;
+  if (t < 64)
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int m = m0 + wm * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-    if (m < M) {
-      float val = acc[v] + b;
-      if (epi == 1) val = tanhf(val);
-      if (epi == 2) {
-        const float e = E[(long)m * scm + n];
-        val *= 1.f - e * e;
-      }
-      C[(long)m * scm + n] = val;
-    }
+    for (int v = 0; v < 16; ++v) out[v][lane] = acc[v];
+  __syncthreads();
+  for (int e = t; e < 1024; e += kSThreads) {
+    const int v = e >> 6, l = e & 63;
+    f(8 * (v >> 2) + 4 * (l >> 5) + (v & 3), l & 31, out[v][l]);
   }
 }
 
-// db[o] = sum_b d[b][o]
-__global__ __launch_bounds__(256) void colsum_kernel(int B, int O, const float* d, float* db) {
-  const int o = blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= O) return;
-  float s = 0.f;
-  for (int b = 0; b < B; ++b) s += d[(size_t)b * O + o];
-  db[o] = s;
+// weights as the forward product reads them: column n = output o, k along the row W[o][k]
+template <bool VEC>
+struct WRows {
+  const __bf16* W;
+  int n0, out, in;
+  __device__ bf16x8 operator()(int e, int k0) const {
+    const int n = n0 + e / kKG;
+    return load8<VEC>(W + (size_t)min(n, out - 1) * in, 1, k0 + 8 * (e % kKG), in, n < out);
+  }
+  __device__ void put(Stage& st, int e, bf16x8 v) const { st.b[e / kKG][e % kKG] = v; }
+};
+// and as the input gradient reads them: column n = input i, k = output o down the
+// rows; lanes take neighbouring i of one group of rows
+struct WCols {
+  const __bf16* W;
+  int n0, out, in;
+  __device__ bf16x8 operator()(int e, int k0) const {
+    const int n = n0 + e % 32;
+    return load8<false>(W + min(n, in - 1), in, k0 + 8 * (e / 32), out, n < in);
+  }
+  __device__ void put(Stage& st, int e, bf16x8 v) const { st.b[e % 32][e / 32] = v; }
+};
+
+// y[b][o] = act(sum_i h[b][i] W[o][i] + bias[o])
+template <bool VEC>
+__global__ __launch_bounds__(kSThreads) void mlp_forward_kernel(int B, int out, int in, const float* h,
+                                                                const __bf16* W, const float* bias, float* y,
+                                                                int tanh_act) {
+  __shared__ Stage st;
+  __shared__ float res[16][64];
+  const unsigned nt = (out + 31) / 32;
+  const int m0 = (int)(blockIdx.x / nt) * 32, n0 = (int)(blockIdx.x % nt) * 32;
+  tile_product(
+      st, res, in,
+      [&](int r, int k, float (&v)[8]) {
+        load8<VEC>(h + (size_t)min(m0 + r, B - 1) * in, 1, k, in, m0 + r < B, v);
+      },
+      WRows<VEC>{W, n0, out, in},
+      [&](int r, int c, float s) {
+        const int b = m0 + r, o = n0 + c;
+        if (b < B && o < out) {
+          s += bias[o];
+          y[(size_t)b * out + o] = tanh_act ? tanhf(s) : s;
+        }
+      });
 }
+
+// One layer of the backward pass in one launch, by workgroup index:
+//   [0, ndn):  dn[b][i] = (sum_o d[b][o] W[o][i]) (1 - hin[b][i]^2), a 32 x 32 tile each
+//   [ndn, ndn + ngw): gW[o][i] = sum_b d[b][o] hin[b][i], eight 32 x 32 tiles (one per
+//              wave, 32 outputs x 256 inputs) each
+//   [ndn + ngw, + ngb): gb[o] = sum_b d[b][o], one output per thread
+//   the last one (d.t given): loss = mean (y - t)^2
+template <bool VEC>
+__global__ __launch_bounds__(kSThreads) void mlp_backward_kernel(int B, int out, int in, GradSrc d, const float* hin,
+                                                                 const __bf16* W, float* gW, float* gb, float* dn,
+                                                                 float* loss, int ndn, int ngw, int ngb) {
+  __shared__ Stage st;
+  __shared__ float res[16][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int id = blockIdx.x;
+  if (id < ndn) {
+    const int nt = (in + 31) / 32, m0 = (id / nt) * 32, n0 = (id - (id / nt) * nt) * 32;
+    tile_product(
+        st, res, out,
+        [&](int r, int k, float (&v)[8]) {
+          d.row8<VEC>((size_t)min(m0 + r, B - 1) * out, k, out, m0 + r < B, v);
+        },
+        WCols{W, n0, out, in},
+        [&](int r, int c, float s) {
+          const int b = m0 + r, i = n0 + c;
+          if (b < B && i < in) {
+            const float e = hin[(size_t)b * in + i];
+            dn[(size_t)b * in + i] = s * (1.f - e * e);
+          }
+        });
+    return;
+  }
+  id -= ndn;
+  if (id < ngw) {
+    const int l32 = lane & 31, kk = 8 * (lane >> 5);
+    const int nt = (in + 32 * kSW - 1) / (32 * kSW), m0 = (id / nt) * 32;
+    const int n0 = ((id - (id / nt) * nt) * kSW + w) * 32;
+    if (n0 >= in) return;                         // no barrier below
+    const int m = m0 + l32, n = n0 + l32;
+    const bool mok = m < out, nok = n < in;
+    const int mc = mok ? m : 0, nc = nok ? n : 0;
+    floatx16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    for (int k0 = 0; k0 < B; k0 += 16 * kGU) {
+      float av[kGU][8], bv[kGU][8];
+#pragma unroll
+      for (int u = 0; u < kGU; ++u) {
+        const int k = k0 + 16 * u + kk;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const bool in_b = k + e < B;
+          av[u][e] = mok && in_b ? d.at((size_t)(k + e) * out + mc) : 0.f;
+          bv[u][e] = nok && in_b ? hin[(size_t)(k + e) * in + nc] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kGU; ++u) {
+        bf16x8 ah, al, bh, bl;
+        split(av[u], ah, al);
+        split(bv[u], bh, bl);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int o = m0 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+      if (o < out && nok) gW[(size_t)o * in + n] = acc[v];
+    }
+    return;
+  }
+  id -= ngw;
+  if (id < ngb) {
+    const int o = id * kSThreads + (int)threadIdx.x;
+    if (o >= out) return;
+    float s = 0.f;
+#pragma unroll 8
+    for (int b = 0; b < B; ++b) s += d.at((size_t)b * out + o);
+    gb[o] = s;
+    return;
+  }
+  // the loss
+  const int cnt = B * out;
+  float part[8] = {};
+  for (int i0 = threadIdx.x; i0 < cnt; i0 += 8 * kSThreads) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = min(i0 + u * kSThreads, cnt - 1);
+      const float e = i0 + u * kSThreads < cnt ? d.p[i] - d.t[i] : 0.f;
+      part[u] += e * e;
+    }
+  }
+  float* rs = &res[0][0];
+  rs[threadIdx.x] = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
+  __syncthreads();
+  for (int st_ = kSThreads / 2; st_ > 0; st_ >>= 1) {
+    if (threadIdx.x < st_) rs[threadIdx.x] += rs[threadIdx.x + st_];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *loss = rs[0] / d.count;
+}
+
+constexpr size_t kSLoss = 65536;             // loss terms one workgroup sums beside the last layer
+
+inline bool vec8(const void* p, int K) { return K % 8 == 0 && (uintptr_t)p % 16 == 0; }
 
 // d = 2 (y - t) / count and loss = mean (y - t)^2, in two passes with a fixed
 // summation order (deterministic): each workgroup of the first pass sums a
@@ -298,8 +498,6 @@ inline unsigned stream_blocks(size_t len) {
   return (unsigned)std::max<size_t>(1, std::min<size_t>(8192, (len + 255) / 256));
 }
 
-inline dim3 gemm_grid(int M, int N) { return dim3((N + kGT - 1) / kGT, (M + kGT - 1) / kGT); }
-
 }  // namespace
 
 size_t mlp_count(const int32_t* w, int nl) {
@@ -315,10 +513,11 @@ hipError_t launch_mlp_forward(const int32_t* w, int nl, const void* pb, const fl
   for (int l = 0; l < nl; ++l) {
     const int in = w[l], out = w[l + 1];
     float* y = acts + aoff;
-    // y[b][o] = sum_i h[b][i] W[o][i] + bias[o]
-    hipLaunchKernelGGL((gemm_mfma_kernel<false>), gemm_grid(B, out), dim3(256), 0, s, B, out, in, h, (long)in, 1L,
-                       (const void*)((const __bf16*)pb + off), 1L, (long)in, y, (long)out,
-                       p + off + (size_t)out * in, l < nl - 1 ? 1 : 0, (const float*)nullptr);
+    const __bf16* W = (const __bf16*)pb + off;
+    const unsigned tiles = (unsigned)((out + 31) / 32) * (unsigned)((B + 31) / 32);
+    auto kernel = vec8(h, in) && vec8(W, in) ? mlp_forward_kernel<true> : mlp_forward_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kSThreads), 0, s, B, out, in, h, W, p + off + (size_t)out * in, y,
+                       l < nl - 1 ? 1 : 0);
     off += (size_t)out * in + out;
     aoff += (size_t)B * out;
     h = y;
@@ -341,27 +540,26 @@ hipError_t launch_mlp_backward(const int32_t* w, int nl, const void* pb, const f
   float* d = scratch;
   float* dn = scratch + (size_t)B * maxw;
   const size_t nout = (size_t)B * w[nl];
-  // the partial sums of the loss live in dn, which the layer loop below
-  // writes only after the final pass has read them
-  const int nparts = (int)std::min<size_t>({(size_t)1024, (nout + 255) / 256, (size_t)B * maxw});
-  hipLaunchKernelGGL(mse_partial_kernel, dim3(nparts), dim3(256), 0, s, nout, acts + aoff[nl - 1], target, d, dn);
-  hipLaunchKernelGGL(mse_final_kernel, dim3(1), dim3(256), 0, s, nparts, (const float*)dn, nout, loss);
+  GradSrc g{acts + aoff[nl - 1], target, (float)nout};
+  if (nout > kSLoss) {                          // more than one workgroup's worth of loss terms
+    const int np = (int)std::min<size_t>({(size_t)1024, (nout + 255) / 256, (size_t)B * maxw});
+    hipLaunchKernelGGL(mse_partial_kernel, dim3(np), dim3(256), 0, s, nout, acts + aoff[nl - 1], target, d, dn);
+    hipLaunchKernelGGL(mse_final_kernel, dim3(1), dim3(256), 0, s, np, (const float*)dn, nout, loss);
+    g = GradSrc{d, nullptr, 0.f};
+  }
   for (int l = nl - 1; l >= 0; --l) {
     const int in = w[l], out = w[l + 1];
-    const float* hin = l == 0 ? x : acts + aoff[l - 1];
+    const int ndn = l > 0 ? (B + 31) / 32 * ((in + 31) / 32) : 0;
+    const int ngw = (out + 31) / 32 * ((in + 32 * kSW - 1) / (32 * kSW));
     float* gW = grad + poff[l];
-    // gW[o][i] = sum_b d[b][o] hin[b][i]
-    hipLaunchKernelGGL((gemm_mfma_kernel<true>), gemm_grid(out, in), dim3(256), 0, s, out, in, B, d, 1L,
-                       (long)out, (const void*)hin, (long)in, 1L, gW, (long)in, (const float*)nullptr, 0,
-                       (const float*)nullptr);
-    hipLaunchKernelGGL(colsum_kernel, dim3((out + 255) / 256), dim3(256), 0, s, B, out, d, gW + (size_t)out * in);
-    if (l > 0) {
-      // dn[b][i] = (sum_o d[b][o] W[o][i]) (1 - hin[b][i]^2)
-      hipLaunchKernelGGL((gemm_mfma_kernel<false>), gemm_grid(B, in), dim3(256), 0, s, B, in, out, d, (long)out,
-                         1L, (const void*)((const __bf16*)pb + poff[l]), (long)in, 1L, dn, (long)in,
-                         (const float*)nullptr, 2, hin);
-      std::swap(d, dn);
-    }
+    const float* hin = l == 0 ? x : acts + aoff[l - 1];
+    const bool vec = vec8(g.p, out) && (!g.t || vec8(g.t, out));
+    auto kernel = vec ? mlp_backward_kernel<true> : mlp_backward_kernel<false>;
+    const int ngb = (out + kSThreads - 1) / kSThreads;
+    hipLaunchKernelGGL(kernel, dim3(ndn + ngw + ngb + (g.t ? 1 : 0)), dim3(kSThreads), 0, s, B, out, in, g, hin,
+                       (const __bf16*)pb + poff[l], gW, gW + (size_t)out * in, dn, loss, ndn, ngw, ngb);
+    g = GradSrc{dn, nullptr, 0.f};
+    std::swap(d, dn);
   }
   return hipGetLastError();
 }
