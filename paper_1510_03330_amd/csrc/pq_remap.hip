@@ -23,7 +23,7 @@ namespace pq {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kRemapThreads = 512;
+constexpr int kDirectNk = 12;
 
 // ------------------------------------------------------- kernel functions
 template <typename C>
@@ -35,12 +35,24 @@ struct KxArgs {
   double2* k2;
 };
 
-__device__ inline double wave_sum(double v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// Row means over the momenta of the edge columns: LPR lanes (a power of two, at
+// most 16) read a row's strip of Nk values, 64 / LPR rows per wave at a time and
+// kXU of those in flight, so that the strips stream at memory rate whatever the
+// lattice; the lanes' sums meet on the vector unit. (One wave per row, one row in
+// flight and shuffles through the LDS crossbar: 1.3 ms on the 8x8, Nv = 16
+// complex64 box, 216 us at 5x7, Nv = 10 complex128; now 0.45 ms and 106 us.)
+constexpr int kXU = 4;
+
+template <int LPR>
+__device__ inline double row_total(double v) {       // in the last lane of each group of LPR
+  if (LPR >= 2) v = dpp_add<0x111, 0xf>(v);
+  if (LPR >= 4) v = dpp_add<0x112, 0xf>(v);
+  if (LPR >= 8) v = dpp_add<0x114, 0xf>(v);
+  if (LPR >= 16) v = dpp_add<0x118, 0xf>(v);
   return v;
 }
 
-template <typename C>
+template <typename C, int LPR>
 __global__ __launch_bounds__(kThreads) void kernel_extract_kernel(KxArgs<C> a) {
   extern __shared__ double2 srow[];   // [2][n]
   const Dims& d = a.d;
@@ -65,39 +77,39 @@ __global__ __launch_bounds__(kThreads) void kernel_extract_kernel(KxArgs<C> a) {
     e0 = m > 0 ? bot : top;
   }
   const C* blk = a.phi + (size_t)r * d.cs + (size_t)qi * n * n;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+  constexpr int RPB = kThreads / LPR;                 // rows the workgroup reads at a time
+  const int row = threadIdx.x / LPR, l = threadIdx.x % LPR;
   for (int ei = 0; ei < ne; ++ei) {
     const int e = ei == 0 ? e0 : e1;
-    const size_t col0 = (size_t)(e + d.Nv / 2) * d.Nk;
-    for (int k = wave; k < d.n; k += nw) {
-      double sr = 0.0, si = 0.0;
-      for (int K = lane; K < d.Nk; K += 64) {
-        double2 v = to_d(blk[(size_t)k * n + col0 + K]);
-        sr += v.x;
-        si += v.y;
+    const C* col = blk + (size_t)(e + d.Nv / 2) * d.Nk;
+    for (int k0 = 0; k0 < d.n; k0 += RPB * kXU) {
+      double2 sum[kXU];
+#pragma unroll
+      for (int u = 0; u < kXU; ++u) sum[u] = mk(0, 0);
+      for (int K = l; K < d.Nk; K += LPR)
+#pragma unroll
+        for (int u = 0; u < kXU; ++u)
+          sum[u] = cadd(sum[u], to_d(col[(size_t)min(k0 + u * RPB + row, d.n - 1) * n + K]));
+#pragma unroll
+      for (int u = 0; u < kXU; ++u) {
+        const double2 v = mk(row_total<LPR>(sum[u].x), row_total<LPR>(sum[u].y));
+        const int k = k0 + u * RPB + row;
+        if (l == LPR - 1 && k < d.n) srow[ei * n + k] = mk(v.x / d.Nk, v.y / d.Nk);
       }
-      sr = wave_sum(sr);
-      si = wave_sum(si);
-      if (lane == 0) srow[ei * n + k] = mk(sr / d.Nk, si / d.Nk);
     }
   }
   __syncthreads();
   __shared__ double2 k1s;
-  if (threadIdx.x == 0) {
-    double kr = 0.0, ki = 0.0;
-    for (int ei = 0; ei < ne; ++ei) {
-      const int e = ei == 0 ? e0 : e1;
-      double sr = 0.0, si = 0.0;
-      for (int K = 0; K < d.Nk; ++K) {
-        double2 v = srow[ei * n + (size_t)(e + d.Nv / 2) * d.Nk + K];
-        sr += v.x;
-        si += v.y;
-      }
-      kr += sr / d.Nk;
-      ki += si / d.Nk;
+  if (threadIdx.x < 64) {                             // Nk <= 64: a lane per momentum of the edge rows
+    double2 s = mk(0, 0);
+    if (threadIdx.x < d.Nk)
+      for (int ei = 0; ei < ne; ++ei)
+        s = cadd(s, srow[ei * n + (size_t)((ei == 0 ? e0 : e1) + d.Nv / 2) * d.Nk + threadIdx.x]);
+    const double2 v = mk(group_total<64>(s.x), group_total<64>(s.y));
+    if (threadIdx.x == 63) {
+      k1s = mk(v.x / d.Nk / ne, v.y / d.Nk / ne);
+      a.k1[ko] = k1s;
     }
-    k1s = mk(kr / ne, ki / ne);
-    a.k1[ko] = k1s;
   }
   __syncthreads();
   const double2 K1v = k1s;
@@ -122,7 +134,6 @@ struct RemapArgs {
   const double2* k1;
   const double2* k2;
   C* gamma;
-  int xcd_spread;
 };
 
 template <typename C> __device__ inline C czero();
@@ -141,6 +152,14 @@ __device__ inline void st_stream(double2* p, double2 v) {
   __builtin_nontemporal_store(w, (v2*)p);
 }
 
+// Whether Gamma goes out with streaming stores: not for complex64 rows that
+// start inside a 64-byte sector whose parts the caches
+// must join first (5x7, Nv = 10: 0.98 ms streaming, 0.78 not; complex128 the
+// other way round, 1.41 and 1.44)
+template <typename C> __device__ inline bool stream_rows(int Nk) {
+  return sizeof(C) > sizeof(float2) || Nk * sizeof(C) % 64 == 0;
+}
+
 template <typename C, typename R>
 __device__ inline C axpy(C acc, R c, C v) {
   acc.x += c * v.x;
@@ -156,26 +175,28 @@ __constant__ float kCoef[2][4][2] = {
     {{-0.5f, -0.5f}, {-1.5f, 0.5f}, {0.5f, -0.5f}, {1.5f, 0.5f}},
     {{0.5f, -0.5f}, {-1.5f, -0.5f}, {0.5f, 0.5f}, {-1.5f, 0.5f}}};
 
-// One workgroup per (k, m) output plane walks the Nv x 2 x 4 (n', pass, term)
-// source tiles in a fixed order. The permutation of each geometry depends only
-// on (K, Q, K'), so its LDS offsets are tabulated once per workgroup; a
-// kernel-filled tile is written into LDS across all its columns so that the
-// same offsets apply. The next tile's global loads are issued before the
-// current tile is consumed from LDS, so one tile per workgroup is always in
-// flight.
-template <typename C, int EPT>
-__global__ __launch_bounds__(kRemapThreads) void remap_kernel(RemapArgs<C> a) {
+// One workgroup of NT threads per (k, m) output plane walks the Nv x 2 x 4 (n',
+// pass, term) source tiles in a fixed order, TPS of them (1, the two channels of
+// a geometry, or the four terms of a pass) per step. The permutation of each
+// geometry depends only on (K, Q, K'), so its LDS offsets are tabulated once per
+// workgroup; a kernel-filled tile is written into LDS across all its columns so
+// that the same offsets apply. The next step's global loads are issued before
+// the current tiles are consumed from LDS, so TPS tiles per workgroup are always
+// in flight; small tiles need several per step to cover the two barriers and the
+// memory latency (5x7, Nv = 10: 1.57 -> 1.30 ms complex128, complex64 with the
+// kernel functions 1.22 -> 0.81 ms; 8x8, Nv = 16, complex64 stays at one tile per
+// step, 12.6 ms).
+template <typename C, int EPT, int NT, int TPS>
+__global__ __launch_bounds__(NT) void remap_kernel(RemapArgs<C> a) {
   extern __shared__ __align__(16) unsigned char smem[];
   using R = decltype(C().x);
   const Dims& d = a.d;
   const int Nk = d.Nk, Nk2 = Nk * Nk, ld = Nk + 1;
-  C* tile = (C*)smem;                                              // Nk rows, padded stride ld
-  unsigned short* offs = (unsigned short*)(smem + sizeof(C) * Nk * ld);   // [4][Nk2]
+  C* tile = (C*)smem;                                              // TPS x Nk rows, padded stride ld
+  unsigned short* offs = (unsigned short*)(smem + sizeof(C) * TPS * Nk * ld);   // [4][Nk2]
 
   // block -> (k, m); consecutive logical blocks (same k) stay on one XCD
-  const int total = gridDim.x;
-  int lin = blockIdx.x;
-  if (a.xcd_spread) lin = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
+  const int lin = xcd_linear();
   const int kbi = lin / d.NW, jm = lin - (lin / d.NW) * d.NW;
   const int nk = kbi / Nk - d.Nv / 2, K = kbi - (kbi / Nk) * Nk;
   const int m = jm - (d.Nv / 2 - 1);
@@ -184,7 +205,7 @@ __global__ __launch_bounds__(kRemapThreads) void remap_kernel(RemapArgs<C> a) {
 
   // output element e = Q Nk + K' reads source (Qp, Kb):
   //   g0 ph-bar: (K'-K, K+Q)  g1 pp: (K+K'+Q, K')  g2 st-1: (K'-K, Q-K')  g3 st-2: (Q-K-K', K')
-  for (int e = t; e < Nk2; e += kRemapThreads) {
+  for (int e = t; e < Nk2; e += NT) {
     const int Q = e / Nk, Kp = e - (e / Nk) * Nk;
     const int Lx = d.Lx, Ly = d.Ly;
     const int kpk = ksub(Kp, K, Lx, Ly);
@@ -194,7 +215,7 @@ __global__ __launch_bounds__(kRemapThreads) void remap_kernel(RemapArgs<C> a) {
     offs[3 * Nk2 + e] = (unsigned short)(ksub(ksub(Q, K, Lx, Ly), Kp, Lx, Ly) * ld + Kp);
   }
 
-  // step s = (n' index, pass, term) -> source tile
+  // tile index s = (n' index, pass, term) -> source tile
   auto info = [&](int s, int& geo, int& src, int& jmp, int& nb, bool& valid) {
     const int in2 = s >> 3, pass = (s >> 2) & 1, term = s & 3;
     const int n2 = in2 - d.Nv / 2;
@@ -208,44 +229,52 @@ __global__ __launch_bounds__(kRemapThreads) void remap_kernel(RemapArgs<C> a) {
     valid = in_bbox(mp, d.Nv);
     jmp = mp + d.Nv / 2 - 1;
   };
-  C buf[EPT];
+  const bool lines = stream_rows<C>(Nk);
+  C buf[TPS][EPT];
   auto fetch = [&](int s) {
-    int geo, src, jmp, nb;
-    bool valid;
-    info(s, geo, src, jmp, nb, valid);
-    if (!valid) return;
-    if (in_fbox(nb, d.Nv)) {
-      const C* base = a.phi + src * chan + (size_t)kbi * n + (size_t)(nb + d.Nv / 2) * Nk;
 #pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        const int idx = min(t + i * kRemapThreads, Nk2 - 1);
-        const int Qp = idx / Nk, Kb = idx - (idx / Nk) * Nk;
-        buf[i] = base[(size_t)(jmp * Nk + Qp) * nn + Kb];
-      }
-    } else {
+    for (int j = 0; j < TPS; ++j) {
+      int geo, src, jmp, nb;
+      bool valid;
+      info(s * TPS + j, geo, src, jmp, nb, valid);
+      if (!valid) continue;
+      if (in_fbox(nb, d.Nv)) {
+        const C* base = a.phi + src * chan + (size_t)kbi * n + (size_t)(nb + d.Nv / 2) * Nk;
 #pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        const int idx = min(t + i * kRemapThreads, Nk2 - 1);
-        const size_t qo = (size_t)src * d.Nq + jmp * Nk + idx / Nk;
-        buf[i] = from_d<C>(cadd(a.k1[qo], a.k2[qo * n + kbi]));
+        for (int i = 0; i < EPT; ++i) {
+          const int idx = min(t + i * NT, Nk2 - 1);
+          const int Qp = idx / Nk, Kb = idx - (idx / Nk) * Nk;
+          buf[j][i] = base[(size_t)(jmp * Nk + Qp) * nn + Kb];
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+          const int idx = min(t + i * NT, Nk2 - 1);
+          const size_t qo = (size_t)src * d.Nq + jmp * Nk + idx / Nk;
+          buf[j][i] = from_d<C>(cadd(a.k1[qo], a.k2[qo * n + kbi]));
+        }
       }
     }
   };
-  const int nsteps = d.Nv * 8;
+  const int nsteps = d.Nv * 8 / TPS;
   fetch(0);
   C acc0[EPT], acc1[EPT];
   for (int s = 0; s < nsteps; ++s) {
-    int geo, src, jmp, nb;
-    bool valid;
-    info(s, geo, src, jmp, nb, valid);
-    const int pass = (s >> 2) & 1, term = s & 3;
-    if (term == 0) {
+    bool valid[TPS], any = false;
+#pragma unroll
+    for (int j = 0; j < TPS; ++j) {
+      int geo, src, jmp, nb;
+      info(s * TPS + j, geo, src, jmp, nb, valid[j]);
+      any = any || valid[j];
+    }
+    const int in2 = s * TPS >> 3, pass = (s * TPS >> 2) & 1, term0 = s * TPS & 3;
+    if (term0 == 0) {
       // Lambda of the two output channels at (m; n, n'): constant over the
       // momentum plane, since the fully irreducible vertex is local
       C l0 = czero<C>(), l1 = czero<C>();
       if (a.lam_box) {
         const size_t cs = (size_t)d.NW * d.Nv * d.Nv;
-        const size_t li = ((size_t)jm * d.Nv + kbi / Nk) * d.Nv + (s >> 3);
+        const size_t li = ((size_t)jm * d.Nv + kbi / Nk) * d.Nv + in2;
         const double2 v0 = a.lam_box[(size_t)(2 * pass) * cs + li];
         const double2 v1 = a.lam_box[(size_t)(2 * pass + 1) * cs + li];
         l0.x = (R)v0.x;
@@ -262,76 +291,165 @@ __global__ __launch_bounds__(kRemapThreads) void remap_kernel(RemapArgs<C> a) {
         acc1[i] = l1;
       }
     }
-    if (valid) {                                   // uniform across the block
+    if (any) {                                     // uniform across the block
       __syncthreads();
 #pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        const int idx = t + i * kRemapThreads;
-        if (idx < Nk2) tile[(idx / Nk) * ld + idx % Nk] = buf[i];
-      }
+      for (int j = 0; j < TPS; ++j)
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+          const int idx = t + i * NT;
+          if (valid[j] && idx < Nk2) tile[j * Nk * ld + (idx / Nk) * ld + idx % Nk] = buf[j][i];
+        }
       __syncthreads();
     }
-    if (s + 1 < nsteps) fetch(s + 1);              // in flight while this tile is consumed
-    if (valid) {
+    if (s + 1 < nsteps) fetch(s + 1);              // in flight while these tiles are consumed
+#pragma unroll
+    for (int j = 0; j < TPS; ++j) {
+      if (!valid[j]) continue;
+      const int term = term0 + j;
       const R c0 = (R)kCoef[pass][term][0], c1 = (R)kCoef[pass][term][1];
-      const unsigned short* og = offs + geo * Nk2;
+      const unsigned short* og = offs + (pass * 2 + (term >> 1)) * Nk2;
 #pragma unroll
       for (int i = 0; i < EPT; ++i) {
-        const int e = min(t + i * kRemapThreads, Nk2 - 1);
-        const C v = tile[og[e]];
+        const int e = min(t + i * NT, Nk2 - 1);
+        const C v = tile[j * Nk * ld + og[e]];
         acc0[i] = axpy(acc0[i], c0, v);
         acc1[i] = axpy(acc1[i], c1, v);
       }
     }
-    if (term == 3) {
-      const int in2 = s >> 3;
+    if (term0 + TPS == 4) {
       C* o0 = a.gamma + (size_t)(2 * pass) * chan;
       C* o1 = a.gamma + (size_t)(2 * pass + 1) * chan;
 #pragma unroll
       for (int i = 0; i < EPT; ++i) {
-        const int e = t + i * kRemapThreads;
+        const int e = t + i * NT;
         if (e < Nk2) {
           const int Q = e / Nk, Kp = e - (e / Nk) * Nk;
           const size_t off = (size_t)(jm * Nk + Q) * nn + (size_t)kbi * n + (size_t)in2 * Nk + Kp;
-          st_stream(o0 + off, acc0[i]);                // written once, read by a later stage
-          st_stream(o1 + off, acc1[i]);
+          if (lines) {                                 // written once, read by a later stage
+            st_stream(o0 + off, acc0[i]);
+            st_stream(o1 + off, acc1[i]);
+          } else {
+            o0[off] = acc0[i];
+            o1[off] = acc1[i];
+          }
         }
       }
     }
   }
 }
 
-template <typename C, int EPT>
-hipError_t run_remap(const Dims& d, const double lam[4], const double2* lam_box, const void* phi,
-                     const double2* k1, const double2* k2, void* gamma, hipStream_t s) {
-  RemapArgs<C> a;
-  a.d = d;
-  for (int i = 0; i < 4; ++i) a.lam[i] = lam[i];
-  a.lam_box = lam_box;
-  a.phi = (const C*)phi;
-  a.k1 = k1;
-  a.k2 = k2;
-  a.gamma = (C*)gamma;
-  const int blocks = d.n * d.NW;
-  a.xcd_spread = (blocks % 8 == 0) ? 1 : 0;
-  size_t lds = sizeof(C) * d.Nk * (d.Nk + 1) + 4 * sizeof(unsigned short) * d.Nk * d.Nk;
-  lds = align256(lds);
+// The remap of a lattice of few momenta, without the LDS tiles: one workgroup
+// per (k, m) as above, a thread per output (n', Q, K') with K' fastest, its eight
+// source values gathered straight from memory. The tile of a term is then at
+// most a few KB, which L1 holds, and all Nv tiles of all terms are in flight at
+// once, where the tiled kernel walks its 8 Nv tiles with two barriers each and
+// Nk^2 of its 512 threads busy. The sums run in the tiled kernel's order (same
+// bits). One momentum, Nv = 32: 307 -> 6 us.
+template <typename C>
+__global__ __launch_bounds__(kThreads) void remap_direct_kernel(RemapArgs<C> a) {
+  using R = decltype(C().x);
+  const Dims& d = a.d;
+  const int Nk = d.Nk, Lx = d.Lx, Ly = d.Ly, hv = d.Nv / 2;
+  const int lin = xcd_linear();
+  const int kbi = lin / d.NW, jm = lin - (lin / d.NW) * d.NW;
+  const int nk = kbi / Nk - hv, K = kbi - (kbi / Nk) * Nk;
+  const int m = jm - (hv - 1);
+  const size_t n = d.n, nn = (size_t)d.n * d.n, chan = (size_t)d.cs, row = (size_t)kbi * n;
+  const size_t lcs = (size_t)d.NW * d.Nv * d.Nv;
+  const int total = d.Nv * Nk * Nk;
+  const bool lines = stream_rows<C>(Nk);
+  for (int i = threadIdx.x; i < total; i += kThreads) {
+        const int r_ = i / Nk, Kp = i - r_ * Nk, in2 = r_ / Nk, Q = r_ - in2 * Nk, n2 = in2 - hv;
+    // geometries: ph-bar, pp, st-1, st-2
+    const int kpk = ksub(Kp, K, Lx, Ly), kq = kadd(K, Q, Lx, Ly);
+    const int mp[4] = {n2 - nk, nk + n2 + m + 1, n2 - nk, m - nk - n2 - 1};
+    const int nb[4] = {nk + m, n2, m - n2 - 1, n2};
+    const int P[4] = {kpk, kadd(kq, Kp, Lx, Ly), kpk, ksub(ksub(Q, K, Lx, Ly), Kp, Lx, Ly)};
+    const int B[4] = {kq, Kp, ksub(Q, Kp, Lx, Ly), Kp};
+    C v[4][2];
+    bool ok[4], in[4];
+    size_t p[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {                 // clamped addresses: every load is in bounds
+      ok[g] = in_bbox(mp[g], d.Nv);
+      in[g] = in_fbox(nb[g], d.Nv);
+      p[g] = ok[g] ? (size_t)((mp[g] + hv - 1) * Nk + P[g]) : 0;
+      const C* src = a.phi + (g == 1 ? 2 * chan : 0) + p[g] * nn + row + (in[g] ? (nb[g] + hv) * Nk + B[g] : 0);
+      v[g][0] = src[0];
+      v[g][1] = src[chan];
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      if (ok[g] && !in[g]) {                      // (ph-bar and st-1 only)
+        const size_t q0 = (g == 1 ? 2 * d.Nq : 0) + p[g], q1 = q0 + d.Nq;
+        v[g][0] = from_d<C>(cadd(a.k1[q0], a.k2[q0 * n + kbi]));
+        v[g][1] = from_d<C>(cadd(a.k1[q1], a.k2[q1 * n + kbi]));
+      }
+    }
+    C* out = a.gamma + (size_t)(jm * Nk + Q) * nn + row + (size_t)in2 * Nk + Kp;
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+      C acc[2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        acc[c] = czero<C>();
+        if (a.lam_box) {
+          const double2 l = a.lam_box[(size_t)(2 * pass + c) * lcs + ((size_t)jm * d.Nv + kbi / Nk) * d.Nv + in2];
+          acc[c].x = (R)l.x;
+          acc[c].y = (R)l.y;
+        } else {
+          acc[c].x = (R)a.lam[2 * pass + c];
+        }
+#pragma unroll
+        for (int term = 0; term < 4; ++term) {
+          const int g = 2 * pass + (term >> 1);
+          if (ok[g]) acc[c] = axpy(acc[c], (R)kCoef[pass][term][c], v[g][term & 1]);
+        }
+        C* o = out + (size_t)(2 * pass + c) * chan;
+        if (lines) st_stream(o, acc[c]);
+        else *o = acc[c];
+      }
+    }
+  }
+}
+
+template <typename C, int EPT, int NT, int TPS>
+hipError_t run_remap(const RemapArgs<C>& a, hipStream_t s) {
+  const Dims& d = a.d;
+  const size_t lds = align256(sizeof(C) * TPS * d.Nk * (d.Nk + 1) + 4 * sizeof(unsigned short) * d.Nk * d.Nk);
   if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)remap_kernel<C, EPT>,
+    hipError_t e = hipFuncSetAttribute((const void*)remap_kernel<C, EPT, NT, TPS>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((remap_kernel<C, EPT>), dim3(blocks), dim3(kRemapThreads), lds, s, a);
+  hipLaunchKernelGGL((remap_kernel<C, EPT, NT, TPS>), dim3(d.n * d.NW), dim3(NT), lds, s, a);
   return hipGetLastError();
 }
 
 template <typename C>
 hipError_t dispatch_remap(const Dims& d, const double lam[4], const double2* lam_box, const void* phi,
                           const double2* k1, const double2* k2, void* gamma, hipStream_t s) {
-  const int need = (d.Nk * d.Nk + kRemapThreads - 1) / kRemapThreads;
-  if (need <= 1) return run_remap<C, 1>(d, lam, lam_box, phi, k1, k2, gamma, s);
-  if (need <= 2) return run_remap<C, 2>(d, lam, lam_box, phi, k1, k2, gamma, s);
-  if (need <= 8) return run_remap<C, 8>(d, lam, lam_box, phi, k1, k2, gamma, s);
+  const RemapArgs<C> a{d, {lam[0], lam[1], lam[2], lam[3]}, lam_box, (const C*)phi, k1, k2, (C*)gamma};
+  const int Nk2 = d.Nk * d.Nk;
+  constexpr bool c64 = sizeof(C) == sizeof(float2);
+  // Up to 12 momenta gather directly (2x3, Nv = 16, complex128 with the kernel
+  // functions: 32 us, tiled 75; 3x4, Nv = 24, complex64: 645 against 674); at 16
+  // the tiles win (4x4, Nv = 16, complex64: 271 against 314, start 655). The
+  // tiles per step are what the LDS of two workgroups or more holds.
+  if (d.Nk <= kDirectNk) {
+    hipLaunchKernelGGL(remap_direct_kernel<C>, dim3(d.n * d.NW), dim3(kThreads), 0, s, a);
+    return hipGetLastError();
+  }
+  if (Nk2 <= 256) return run_remap<C, 1, 256, 4>(a, s);
+  if (Nk2 <= 2 * 256) return run_remap<C, 2, 256, 4>(a, s);
+  if (Nk2 <= 3 * 256) return run_remap<C, 3, 256, 4>(a, s);
+  if (Nk2 <= 4 * 256) return run_remap<C, 4, 256, c64 ? 4 : 2>(a, s);
+  if (Nk2 <= 3 * 512) return run_remap<C, 3, 512, c64 ? 4 : 2>(a, s);
+  if (Nk2 <= 4 * 512) return run_remap<C, 4, 512, c64 ? 2 : 1>(a, s);
+  if (Nk2 <= 5 * 512) return run_remap<C, 5, 512, c64 ? 2 : 1>(a, s);
+  if (Nk2 <= 6 * 512) return run_remap<C, 6, 512, c64 ? 2 : 1>(a, s);
+  if (Nk2 <= 8 * 512) return run_remap<C, 8, 512, 1>(a, s);
   return hipErrorInvalidValue;
 }
 
@@ -346,17 +464,24 @@ __global__ __launch_bounds__(kThreads) void lambda_fill_kernel(double2* lam, siz
 
 }  // namespace
 
+template <typename C>
+static void run_extract(const KxArgs<C>& a, size_t lds, hipStream_t s) {
+  const dim3 grid(4 * a.d.Nq);
+  if (a.d.Nk > 8) hipLaunchKernelGGL((kernel_extract_kernel<C, 16>), grid, dim3(kThreads), lds, s, a);
+  else if (a.d.Nk > 4) hipLaunchKernelGGL((kernel_extract_kernel<C, 8>), grid, dim3(kThreads), lds, s, a);
+  else if (a.d.Nk > 2) hipLaunchKernelGGL((kernel_extract_kernel<C, 4>), grid, dim3(kThreads), lds, s, a);
+  else if (a.d.Nk > 1) hipLaunchKernelGGL((kernel_extract_kernel<C, 2>), grid, dim3(kThreads), lds, s, a);
+  else hipLaunchKernelGGL((kernel_extract_kernel<C, 1>), grid, dim3(kThreads), lds, s, a);
+}
+
 hipError_t launch_kernel_extract(const pq_params& p, const Dims& d, const void* phi, double2* k1,
                                  double2* k2, hipStream_t s) {
   size_t lds = 2 * sizeof(double2) * (size_t)d.n;
   if (lds > 64 * 1024) return hipErrorInvalidValue;
-  if (p.storage == PQ_STORE_C64) {
-    KxArgs<float2> a{d, p.kernel_level, p.edge_rule, (const float2*)phi, k1, k2};
-    hipLaunchKernelGGL(kernel_extract_kernel<float2>, dim3(4 * d.Nq), dim3(kThreads), lds, s, a);
-  } else {
-    KxArgs<double2> a{d, p.kernel_level, p.edge_rule, (const double2*)phi, k1, k2};
-    hipLaunchKernelGGL(kernel_extract_kernel<double2>, dim3(4 * d.Nq), dim3(kThreads), lds, s, a);
-  }
+  if (p.storage == PQ_STORE_C64)
+    run_extract(KxArgs<float2>{d, p.kernel_level, p.edge_rule, (const float2*)phi, k1, k2}, lds, s);
+  else
+    run_extract(KxArgs<double2>{d, p.kernel_level, p.edge_rule, (const double2*)phi, k1, k2}, lds, s);
   return hipGetLastError();
 }
 
