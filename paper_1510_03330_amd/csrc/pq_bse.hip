@@ -7,10 +7,9 @@
 // (B = Gamma) with panel width NB (128 for complex64, 64 for complex128),
 // batched over all q blocks of a channel: every step is one kernel launch over
 // (q block, tile) grids. A forward sweep over the panels J = 0, 1, ...:
-//   (a) bse_pivot:  P = A_JJ^-1 by Gauss-Jordan on the NB x NB diagonal block,
-//                   held in registers (one column per thread and a slice of its
-//                   rows), pivot rows and columns broadcast through LDS, stored
-//                   transposed (k-major);
+//   (a) bse_pivot:  P = A_JJ^-1 of the NB x NB diagonal block by blocked
+//                   Gauss-Jordan on the matrix cores, one workgroup per block,
+//                   stored transposed (k-major);
 //   (b) bse_panel:  pivot rows R_JK = P A_JK for every column right of the
 //                   panel in A and every column of B (in place);
 //   (c) bse_update: A_IK -= A_IJ R_JK, B_I -= A_IJ R_JB for the rows I below
@@ -391,22 +390,79 @@ __device__ void copy_multipliers(const BseCtx<T>& a, int blk, int j0, int i0,
 }
 
 // ------------------------------------------------------------------ pivot
-// P = A_JJ^-1 by in-place Gauss-Jordan on the diagonal block (identity outside
-// the jb x jb part for a ragged last panel). Thread t holds column j = t % NB
-// of the block for the RPT rows r0 .. r0 + RPT - 1 (r0 = RPT t / NB; a wave
-// lies inside one row group, so r0 is wave-uniform) in registers (RPT = 32 for
-// NB = 128 with 512 threads, 16 for NB = 64). Step c publishes the pivot column
-// and row through LDS (double buffered, one barrier per step), then every
-// thread updates its entries:
-//   row c:           x <- x / p            (column c: x <- 1 / p)
-//   other rows r:    x <- x - D[r][c] D[c][j] / p   (column c: x <- -D[r][c] / p)
-// Column c is cleared by its owner once published, so one fused multiply-add
-// form covers every column; row c is overwritten afterwards by the one wave
-// pair that holds it, through a wave-uniform register index.
-template <int NB> constexpr int pivot_threads() { return NB >= 128 ? 512 : 256; }
+// P = A_JJ^-1 on the diagonal block (identity outside the jb x jb part for a
+// ragged last panel) by blocked Gauss-Jordan with 16-wide steps on the matrix
+// cores. Wave w holds the tile column w (NB / 16 tiles of 16 x 16) in
+// accumulators; step s, with D = A_ss:
+//   R_j = D^-1 A_sj;   A_ij -= A_is R_j (i != s),  A_sj = R_j,
+// where column s itself enters as the identity (R_s = D^-1, A_is = -A_is D^-1).
+// An accumulator of the 16 x 16 x 4 product, read as its second operand, holds
+// four rows k of the same column if the k of step q is taken as crow(g, q) (lane
+// group g, register q); so A_sj and R_j are used in place, and only column s and
+// D^-1 go through LDS, in double buffers with one barrier per step. The wave that
+// owns column s + 1 updates its diagonal tile first and inverts it (in
+// registers, below) while the others run their products. The tile row of a step
+// is always register tile 0: the tiles rotate by one per step.
+// Four real products per complex product; bound by the matrix cores (128 x 128
+// complex64: 65k cycles per block and CU) and, with one block per CU, by the chain
+// of 16 x 16 inversions. One pivot at a time on the vector unit with a barrier
+// each (before): 226 us for 240 complex64 blocks, 588 for 960; complex128 64 x 64:
+// 52 us for 31 blocks, 211 for 896. Now 82 and 237, 27 and 120 us.
+template <int NB> constexpr int pivot_threads() { return 4 * NB; }
 
-// 1 / z for a pivot. complex64: z scaled by a power of two so that |z|^2 can
-// neither overflow nor underflow, then one hardware reciprocal (<= 1 ulp).
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+template <typename T> struct Mma16;
+template <> struct Mma16<float> {
+  using acc_t = floatx4;
+  static constexpr int LD = 18;                          // LDS row stride (conflict-free operand reads)
+  __device__ static constexpr int crow(int g, int v) { return 4 * g + v; }
+  static constexpr int g_of(int row) { return row >> 2; }
+  static constexpr int v_of(int row) { return row & 3; }
+  __device__ static acc_t mma(float a, float b, acc_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+};
+template <> struct Mma16<double> {
+  using acc_t = doublex4;
+  static constexpr int LD = 17;
+  __device__ static constexpr int crow(int g, int v) { return g + 4 * v; }
+  static constexpr int g_of(int row) { return row & 3; }
+  static constexpr int v_of(int row) { return row >> 2; }
+  __device__ static acc_t mma(double a, double b, acc_t c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+};
+
+// lane LN of each row of 16 to the whole row
+template <int LN>
+__device__ inline float row_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + LN, 0xf, 0xf, true));
+}
+template <int LN>
+__device__ inline double row_bcast(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + LN, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + LN, 0xf, 0xf, true));
+}
+// row G of 16 lanes to all four rows: the half that holds it to both halves, then
+// its row to both rows of each half
+template <int G>
+__device__ inline unsigned rows_bcast(unsigned v) {
+  const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  const unsigned y = G >= 2 ? h[1] : h[0];
+  const auto r = __builtin_amdgcn_permlane16_swap(y, y, false, false);
+  return (G & 1) ? r[1] : r[0];
+}
+template <int G>
+__device__ inline float rows_bcast(float v) { return __uint_as_float(rows_bcast<G>(__float_as_uint(v))); }
+template <int G>
+__device__ inline double rows_bcast(double v) {
+  return __hiloint2double((int)rows_bcast<G>((unsigned)__double2hiint(v)),
+                          (int)rows_bcast<G>((unsigned)__double2loint(v)));
+}
+
+// 1 / z for a pivot: z scaled by a power of two so that |z|^2 can neither
+// overflow nor underflow, then one reciprocal (complex64: the hardware's, <= 1
+// ulp; complex128: its estimate and two Newton steps).
 __device__ inline float2 pivot_recip(float2 z) {
   int e;
   (void)frexpf(fmaxf(fabsf(z.x), fabsf(z.y)), &e);
@@ -414,116 +470,171 @@ __device__ inline float2 pivot_recip(float2 z) {
   const float r = __builtin_amdgcn_rcpf(fmaf(a, a, b * b));
   return make_float2(ldexpf(a * r, -e), ldexpf(-b * r, -e));
 }
-__device__ inline double2 pivot_recip(double2 z) { return crecip(z); }
+__device__ inline double2 pivot_recip(double2 z) {
+  int e;
+  (void)frexp(fmax(fabs(z.x), fabs(z.y)), &e);
+  const double a = ldexp(z.x, -e), b = ldexp(z.y, -e);
+  const double d = fma(a, a, b * b);
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(r, fma(-d, r, 1.0), r);
+  r = fma(r, fma(-d, r, 1.0), r);
+  return make_double2(ldexp(a * r, -e), ldexp(-b * r, -e));
+}
+
+// One Gauss-Jordan step (pivot c) of the 16 x 16 inversion in one wave. The
+// registers are the accumulator layout of D (lane l: column l % 16, rows
+// crow(l / 16, q)), read here as the rows of E = D^T: E[l % 16][crow(l / 16, q)].
+// E^-1 = (D^-1)^T, so D^-1 comes out in the accumulator layout, and the pivots
+// are those of D.
+template <typename T, int c>
+__device__ __forceinline__ void invert_step(T (&xr)[4], T (&xi)[4], typename cplx_of<T>::type& pv) {
+  using C = typename cplx_of<T>::type;
+  using M = Mma16<T>;
+  constexpr int G = M::g_of(c), V = M::v_of(c);
+  const int r = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
+  const T pcr = rows_bcast<G>(xr[V]), pci = rows_bcast<G>(xi[V]);     // E[r][c]
+  C p;
+  p.x = row_bcast<c>(pcr);
+  p.y = row_bcast<c>(pci);
+  pv = r == c ? p : pv;                                             // lane c: pivot c
+  const C ip = pivot_recip(p);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const T rr = row_bcast<c>(xr[q]), ri = row_bcast<c>(xi[q]);       // E[c][own column]
+    const bool pcol = q == V && g == G;
+    const T ur = pcol ? ip.x : rr * ip.x - ri * ip.y;
+    const T ui = pcol ? ip.y : rr * ip.y + ri * ip.x;
+    const T x0 = pcol ? (T)0 : xr[q], x1 = pcol ? (T)0 : xi[q];
+    const T nr = fma(-pcr, ur, fma(pci, ui, x0)), ni = fma(-pcr, ui, fma(-pci, ur, x1));
+    xr[q] = r == c ? ur : nr;
+    xi[q] = r == c ? ui : ni;
+  }
+  if constexpr (c + 1 < 16) invert_step<T, c + 1>(xr, xi, pv);
+}
 
 template <typename T, int NB>
-__global__ __launch_bounds__(pivot_threads<NB>()) __attribute__((amdgpu_waves_per_eu(NB >= 128 ? 4 : 3)))
+__global__ __launch_bounds__(pivot_threads<NB>()) __attribute__((amdgpu_waves_per_eu(NB >= 128 ? 4 : 2)))
 void bse_pivot_kernel(BseCtx<T> a, int j0) {
   using C = typename cplx_of<T>::type;
-  constexpr int NT = pivot_threads<NB>();
-  constexpr int RPT = NB * NB / NT;
-  static_assert(NB % 64 == 0, "a wave must lie inside one row group");
-  __shared__ C colbuf[2][NB];
-  __shared__ C rowbuf[2][NB];
+  using M = Mma16<T>;
+  using acc_t = typename M::acc_t;
+  constexpr int NT = pivot_threads<NB>(), TN = NB / 16;
+  __shared__ __align__(16) C cp[2][NB][M::LD];       // column s
+  __shared__ __align__(16) C dinv[2][16][M::LD];     // D^-1
   __shared__ C pv[NB];
   if (inactive(a, (int)blockIdx.y)) return;
   const int blk = blockIdx.y, t = threadIdx.x, n = a.n;
-  const int j = t % NB;
-  const int r0 = __builtin_amdgcn_readfirstlane(t / NB) * RPT;
-  const int jb = min(NB, n - j0);
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int col = t & 15, g = (t >> 4) & 3;
+  const int jb = min(NB, n - j0), steps = (jb + 15) / 16;
   const C* A = a.A + (size_t)blk * n * n;
-  T xr[RPT], xi[RPT];
+  acc_t re[TN], im[TN];                              // tile p: rows 16 ((s + p) % TN) ..
 #pragma unroll
-  for (int q = 0; q < RPT; ++q) {
-    const int r = r0 + q;
-    const int ri = j0 + min(r, jb - 1), ci = j0 + min(j, jb - 1);
-    const C v = j0 == 0 ? system_elem(a, blk, ri, ci) : A[(size_t)ri * n + ci];
-    const bool in = r < jb && j < jb;
-    xr[q] = in ? v.x : (r == j ? (T)1 : (T)0);
-    xi[q] = in ? v.y : (T)0;
+  for (int p = 0; p < TN; ++p)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * p + M::crow(g, v), j = 16 * w + col;
+      const int ri = j0 + min(r, jb - 1), ci = j0 + min(j, jb - 1);
+      const C x = j0 == 0 ? system_elem(a, blk, ri, ci) : A[(size_t)ri * n + ci];
+      const bool in = r < jb && j < jb;
+      re[p][v] = in ? x.x : (r == j ? (T)1 : (T)0);
+      im[p][v] = in ? x.y : (T)0;
+    }
+  // D^-1 of a diagonal tile to LDS, by the wave that owns it
+  auto publish_inverse = [&](const acc_t& dr, const acc_t& di, int s, int b) __attribute__((always_inline)) {
+    T xr[4], xi[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      xr[v] = dr[v];
+      xi[v] = di[v];
+    }
+    __builtin_amdgcn_s_setprio(2);                   // the chain the other waves wait for
+    C piv = cz<C>();
+    invert_step<T, 0>(xr, xi, piv);
+    __builtin_amdgcn_s_setprio(0);
+    if ((t & 63) < 16) pv[16 * s + col] = piv;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      C x;
+      x.x = xr[v];
+      x.y = xi[v];
+      dinv[b][M::crow(g, v)][col] = x;
+    }
+  };
+  auto publish_column = [&](int s, int b) {          // tile p holds the rows of tile row s + p
+#pragma unroll
+    for (int p = 0; p < TN; ++p)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        C x;
+        x.x = re[p][v];
+        x.y = im[p][v];
+        cp[b][16 * ((s + p) % TN) + M::crow(g, v)][col] = x;
+      }
+  };
+  // c -= (sub) or = m b, m a 16 x 16 LDS tile in the first operand's layout
+  auto product = [&](const C (*m)[M::LD], const acc_t& br, const acc_t& bi, acc_t& cr, acc_t& ci, bool sub) {
+    C x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = m[col][M::crow(g, q)];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const T ar = sub ? -x[q].x : x[q].x, ai = sub ? -x[q].y : x[q].y;
+      cr = M::mma(ar, br[q], cr);
+      ci = M::mma(ar, bi[q], ci);
+      cr = M::mma(-ai, bi[q], cr);
+      ci = M::mma(ai, br[q], ci);
+    }
+  };
+  if (w == 0) {
+    publish_inverse(re[0], im[0], 0, 0);
+    publish_column(0, 0);
   }
-  for (int c = 0; c < jb; ++c) {
-    const int bf = c & 1;
-    const int cr = c - r0;                                 // wave-uniform
-    const bool own_row = (unsigned)cr < (unsigned)RPT;     // wave-uniform
-    if (j == c) {
-#pragma unroll
-      for (int q = 0; q < RPT; ++q) {
-        C v;
-        v.x = xr[q];
-        v.y = xi[q];
-        colbuf[bf][r0 + q] = v;
-        xr[q] = (T)0;
-        xi[q] = (T)0;
-      }
-    }
-    if (own_row) {
-      C v;
-      if constexpr (sizeof(T) == 4) {
-        v.x = xr[cr];
-        v.y = xi[cr];
-      } else {   // (a dynamic index would put the complex128 block in scratch)
-        v = cz<C>();
-#pragma unroll
-        for (int q = 0; q < RPT; ++q)
-          if (q == cr) {
-            v.x = xr[q];
-            v.y = xi[q];
-          }
-      }
-      rowbuf[bf][j] = v;
-    }
+  for (int s = 0; s < steps; ++s) {
+    const int b = s & 1;
     __syncthreads();
-    const C piv = colbuf[bf][c];
-    if (t == 0) pv[c] = piv;
-    const C p = pivot_recip(piv);
-    const C rv = rowbuf[bf][j];
-    C u;
-    u.x = j == c ? p.x : rv.x * p.x - rv.y * p.y;
-    u.y = j == c ? p.y : rv.x * p.y + rv.y * p.x;
-    // the pivot column is read in chunks of 16 entries (wide broadcast reads
-    // issued together), then applied
+    if (w == s) {                                    // wave-uniform
 #pragma unroll
-    for (int q0 = 0; q0 < RPT; q0 += 16) {
-      C cv[16];
+      for (int p = 0; p < TN; ++p)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) cv[q] = colbuf[bf][r0 + q0 + q];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        xr[q0 + q] = fma(-cv[q].x, u.x, fma(cv[q].y, u.y, xr[q0 + q]));
-        xi[q0 + q] = fma(-cv[q].x, u.y, fma(-cv[q].y, u.x, xi[q0 + q]));
-      }
+        for (int v = 0; v < 4; ++v) {
+          re[p][v] = p == 0 && M::crow(g, v) == col ? (T)1 : (T)0;
+          im[p][v] = (T)0;
+        }
     }
-    if (own_row) {
-      if constexpr (sizeof(T) == 4) {
-        xr[cr] = u.x;
-        xi[cr] = u.y;
-      } else {
+    acc_t rr, ri;
 #pragma unroll
-        for (int q = 0; q < RPT; ++q)
-          if (q == cr) {
-            xr[q] = u.x;
-            xi[q] = u.y;
-          }
-      }
+    for (int v = 0; v < 4; ++v) rr[v] = ri[v] = (T)0;
+    product(dinv[b], re[0], im[0], rr, ri, false);
+    const bool next = w == s + 1 && s + 1 < steps;
+#pragma unroll
+    for (int p = 1; p < TN; ++p) {
+      product(&cp[b][16 * ((s + p) % TN)], rr, ri, re[p], im[p], true);
+      if (p == 1 && next) publish_inverse(re[1], im[1], s + 1, b ^ 1);
     }
+#pragma unroll
+    for (int p = 0; p + 1 < TN; ++p) {
+      re[p] = re[p + 1];
+      im[p] = im[p + 1];
+    }
+    re[TN - 1] = rr;
+    im[TN - 1] = ri;
+    if (next) publish_column(s + 1, b ^ 1);
   }
   C* PT = a.PI + (size_t)blk * NB * NB;     // stored transposed: column j of P is row j of PT
-#pragma unroll
-  for (int q = 0; q < RPT; ++q) {
-    C v;
-    v.x = xr[q];
-    v.y = xi[q];
-    PT[(size_t)j * NB + r0 + q] = v;
-  }
-  // pivot monitor: largest |entry|^2 of P (read back from this thread's own
-  // stores, which keeps the register-resident block free of extra live
-  // values), smallest and largest |pivot|, non-finite pivots
   T xm2 = (T)0;
-  for (int q = 0; q < RPT; ++q) {
-    const C v = PT[(size_t)j * NB + r0 + q];
-    xm2 = fmax(xm2, v.x * v.x + v.y * v.y);
-  }
+#pragma unroll
+  for (int p = 0; p < TN; ++p)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      C x;
+      x.x = re[p][v];
+      x.y = im[p][v];
+      PT[(size_t)(16 * w + col) * NB + 16 * ((steps + p) % TN) + M::crow(g, v)] = x;
+      xm2 = fmax(xm2, x.x * x.x + x.y * x.y);
+    }
+  // pivot monitor: largest |entry|^2 of P, smallest and largest |pivot|,
+  // non-finite pivots
   __syncthreads();                                  // pv complete
   double pmin = DBL_MAX, pmax = 0.0, bad = 0.0;
   if (t < jb) {
