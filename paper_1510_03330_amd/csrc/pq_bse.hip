@@ -1739,7 +1739,6 @@ constexpr int panel_width() { return sizeof(T) == 4 ? 128 : 64; }
 //            so |E v_p|^2 averages |E|_F^2),
 // and decides the flag (est2 > tol); otherwise the screen stands.
 // S: every index for n <= 256, else two contiguous chunks of 64 at n/4 and 3n/4.
-constexpr int kProbeRows = 4;      // rows per wave, loaded together
 constexpr double kDefaultBseTol = 2e-5;
 constexpr double kScreen = 2.0;    // margin of the sampled screen
 constexpr double kAmp2 = 4.0;      // |A^-1|_F^2 / n above which the probes are evaluated exactly
@@ -1781,141 +1780,176 @@ __device__ inline void cfma(double2& acc, double2 a, double2 b) {
 // and one probe's |E v| / |E|_F fluctuates like an exponential variable).
 constexpr int kNpScreen = 2, kNpRefine = 8;
 
-template <bool REFINE> __device__ inline bool probe_col(int n, int j) { return REFINE || probe_in(n, j); }
-
-// y_p = F^ v_p on every row. Screen: the sampled columns of every block;
-// refined: every column of the blocks with pst[6] = 2. One wave per RPW rows,
-// lanes across the columns; grid (ceil(n / (4 RPW)), Nq).
-template <int NP, int RPW, bool REFINE>
+// y_p = F^ v_p on every row of the marked blocks (pst[6] = 2), one wave per row,
+// lanes across the columns. As a rule no block is marked, so the grids of these
+// kernels hold at most 64 workgroups per block, which walk the rows (256 took 53
+// us to exit at 960 blocks of 1024, three times).
+template <int NP>
 __global__ __launch_bounds__(kThreads) void probe_y_kernel(const float2* F, int n, const double* pst, double2* y) {
   const int blk = blockIdx.y, lane = threadIdx.x & 63;
-  if (REFINE && pst[(size_t)blk * kPst + 6] != 2.0) return;
-  const int i0 = (blockIdx.x * kWaves + (threadIdx.x >> 6)) * RPW;
-  if (i0 >= n) return;
-  const float2* Fb = F + (size_t)blk * n * n;
-  const int ns = REFINE ? n : probe_ns(n);
-  double2 acc[RPW][NP];
+  if (pst[(size_t)blk * kPst + 6] != 2.0) return;
+  for (int i = blockIdx.x * kWaves + (threadIdx.x >> 6); i < n; i += gridDim.x * kWaves) {
+    const float2* Fb = F + (size_t)blk * n * n + (size_t)i * n;
+    double2 acc[NP];
 #pragma unroll
-  for (int r = 0; r < RPW; ++r)
+    for (int p = 0; p < NP; ++p) acc[p] = mk(0.0, 0.0);
+    for (int j = lane; j < n; j += 64) {
+      const double2 fd = to_d(Fb[j]);
 #pragma unroll
-    for (int p = 0; p < NP; ++p) acc[r][p] = mk(0.0, 0.0);
-  for (int s = lane; s < ns; s += 64) {
-    const int j = REFINE ? s : probe_at(n, s);
-    double2 v[NP];
-#pragma unroll
-    for (int p = 0; p < NP; ++p) v[p] = probe_vec(j, p);
-    float2 f[RPW];
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) f[r] = Fb[(size_t)min(i0 + r, n - 1) * n + j];
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) {
-      const double2 fd = to_d(f[r]);
-#pragma unroll
-      for (int p = 0; p < NP; ++p) cfma(acc[r][p], fd, v[p]);
+      for (int p = 0; p < NP; ++p) cfma(acc[p], fd, probe_vec(j, p));
     }
-  }
-#pragma unroll
-  for (int r = 0; r < RPW; ++r)
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      const double2 sm = mk(wave_sum(acc[r][p].x), wave_sum(acc[r][p].y));
-      if (lane == 0 && i0 + r < n) y[((size_t)blk * NP + p) * n + i0 + r] = sm;
+      const double2 sm = mk(wave_sum(acc[p].x), wave_sum(acc[p].y));
+      if (lane == 0) y[((size_t)blk * NP + p) * n + i] = sm;
     }
+  }
 }
 
-// r_p = y_p - s Gamma (X y_p) - Gamma v_p. Screen: on the rows of the sample
-// (grid.x over the sample); refined: on every row of the marked blocks.
-template <int NP, int RPW, bool REFINE>
+// r_p = y_p - s Gamma (X y_p) - Gamma v_p on every row of the marked blocks.
+template <int NP>
 __global__ __launch_bounds__(kThreads) void probe_r_kernel(const float2* G, const double2* chi0, const double2* y,
                                                           int n, double sign, const double* pst, double2* r) {
   const int blk = blockIdx.y, lane = threadIdx.x & 63;
-  if (REFINE && pst[(size_t)blk * kPst + 6] != 2.0) return;
-  const int nrows = REFINE ? n : probe_ns(n);
-  const int s0 = (blockIdx.x * kWaves + (threadIdx.x >> 6)) * RPW;
-  if (s0 >= nrows) return;
-  int rows[RPW];
-#pragma unroll
-  for (int k = 0; k < RPW; ++k) {
-    const int sk = min(s0 + k, nrows - 1);
-    rows[k] = REFINE ? sk : probe_at(n, sk);
-  }
-  const float2* Gb = G + (size_t)blk * n * n;
+  if (pst[(size_t)blk * kPst + 6] != 2.0) return;
   const double2* X = chi0 + (size_t)blk * n;
   const double2* yb = y + (size_t)blk * NP * n;
-  double2 g[RPW][NP], h[RPW][NP];
+  for (int i = blockIdx.x * kWaves + (threadIdx.x >> 6); i < n; i += gridDim.x * kWaves) {
+    const float2* Gb = G + (size_t)blk * n * n + (size_t)i * n;
+    double2 g[NP], h[NP];
 #pragma unroll
-  for (int k = 0; k < RPW; ++k)
-#pragma unroll
-    for (int p = 0; p < NP; ++p) g[k][p] = h[k][p] = mk(0.0, 0.0);
-  for (int j = lane; j < n; j += 64) {
-    const bool in = probe_col<REFINE>(n, j);
-    const double2 x = X[j];
-    double2 v[NP], z[NP];
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      v[p] = in ? probe_vec(j, p) : mk(0.0, 0.0);
-      z[p] = cmul(x, yb[(size_t)p * n + j]);
-    }
-    float2 gv[RPW];
-#pragma unroll
-    for (int k = 0; k < RPW; ++k) gv[k] = Gb[(size_t)rows[k] * n + j];
-#pragma unroll
-    for (int k = 0; k < RPW; ++k) {
-      const double2 gd = to_d(gv[k]);
+    for (int p = 0; p < NP; ++p) g[p] = h[p] = mk(0.0, 0.0);
+    for (int j = lane; j < n; j += 64) {
+      const double2 x = X[j], gd = to_d(Gb[j]);
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
-        cfma(g[k][p], gd, v[p]);
-        cfma(h[k][p], gd, z[p]);
+        cfma(g[p], gd, probe_vec(j, p));
+        cfma(h[p], gd, cmul(x, yb[(size_t)p * n + j]));
       }
     }
-  }
-#pragma unroll
-  for (int k = 0; k < RPW; ++k)
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      const double2 sg = mk(wave_sum(g[k][p].x), wave_sum(g[k][p].y));
-      const double2 sh = mk(wave_sum(h[k][p].x), wave_sum(h[k][p].y));
-      const int i = rows[k];
-      if (lane == 0 && s0 + k < nrows) {
+      const double2 sg = mk(wave_sum(g[p].x), wave_sum(g[p].y));
+      const double2 sh = mk(wave_sum(h[p].x), wave_sum(h[p].y));
+      if (lane == 0) {
         const double2 a = yb[(size_t)p * n + i];
         r[((size_t)blk * NP + p) * n + i] = mk(a.x - sign * sh.x - sg.x, a.y - sign * sh.y - sg.y);
       }
     }
-}
-
-__device__ inline double safe_ratio(double num2, double den2) {
-  if (num2 == 0.0) return 0.0;
-  return sqrt(num2 / den2);     // den2 = 0 with num2 > 0: +inf (flagged)
-}
-
-// Per block (one workgroup): the screen. Above tol / kScreen, or with |A^-1|_F
-// amplifying, with a finite value: refined estimate pending (pst[6] = 2);
-// non-finite: flagged (1).
-__global__ __launch_bounds__(kThreads) void probe_est_kernel(const double2* r, const float* pcs, const float2* F,
-                                                            const double2* chi0, int n, double sign, double tol,
-                                                            double* pst) {
-  __shared__ double red[kThreads];
-  const int blk = blockIdx.x;
-  const int ns = probe_ns(n);
-  const int nr = (n + 63) / 64;
-  double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};    // |r_0|^2, |r_1|^2, |F X|^2, |F|^2, Re tr(F X)
-  for (int q = threadIdx.x; q < ns; q += blockDim.x) {
-    const int i = probe_at(n, q);
-    s[0] += cabs2(r[((size_t)blk * kNpScreen + 0) * n + i]);
-    s[1] += cabs2(r[((size_t)blk * kNpScreen + 1) * n + i]);
   }
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
+}
+
+// The screen, one workgroup per block: y on every row, the residual on the rows
+// of the sample, the norms, the decision. Above tol / kScreen, or with |A^-1|_F
+// amplifying, with a finite value: refined estimate pending (pst[6] = 2);
+// non-finite: flagged (1). Bound by its reads, 2 n |S| values of a block, and by
+// the FP64 products: 16 lanes share a row (their sums meet in four steps on the
+// vector unit), and s X y and the probe of a column enter as one weight, formed
+// once per column in LDS. As three launches with a wave per row, five shuffled
+// sums and the probe hash per row (before): 122 us at 240 blocks of 256, 870 us at
+// 960 of 1024; now 72 and 476 us.
+constexpr int kScrThreads = 512, kScrGroups = kScrThreads / 16, kScrCols = 256;
+
+__device__ inline double row16_total(double v) {     // in the last lane of each row of 16
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  return dpp_add<0x118, 0xf>(v);
+}
+
+__global__ __launch_bounds__(kScrThreads) void probe_screen_kernel(const float2* F, const float2* G,
+                                                                  const double2* chi0, const float* pcs, int n,
+                                                                  double sign, double tol, double2* y, double* pst) {
+  __shared__ double2 wt[kScrCols][2];
+  __shared__ double red[kScrThreads];
+  const int blk = blockIdx.x, t = threadIdx.x, grp = t >> 4, l = t & 15;
+  const int ns = probe_ns(n), nr = (n + 63) / 64;
+  const float2* Fb = F + (size_t)blk * n * n;
+  const float2* Gb = G + (size_t)blk * n * n;
+  const double2* X = chi0 + (size_t)blk * n;
+  double2* yb = y + (size_t)blk * kNpScreen * n;
+  for (int q = t; q < ns; q += kScrThreads)            // ns <= kScrCols
+    for (int p = 0; p < kNpScreen; ++p) wt[q][p] = probe_vec(probe_at(n, q), p);
+  __syncthreads();
+  constexpr int RY = 4, RR = 4;                        // rows of a lane group at a time
+  for (int i0 = grp; i0 < n; i0 += RY * kScrGroups) {  // y_p = F^ v_p
+    double2 acc[RY][2];
+#pragma unroll
+    for (int u = 0; u < RY; ++u) acc[u][0] = acc[u][1] = mk(0.0, 0.0);
+    for (int q = l; q < ns; q += 16) {
+      const int j = probe_at(n, q);
+      float2 f[RY];
+#pragma unroll
+      for (int u = 0; u < RY; ++u) f[u] = Fb[(size_t)min(i0 + u * kScrGroups, n - 1) * n + j];
+      const double2 v0 = wt[q][0], v1 = wt[q][1];
+#pragma unroll
+      for (int u = 0; u < RY; ++u) {
+        const double2 fd = to_d(f[u]);
+        cfma(acc[u][0], fd, v0);
+        cfma(acc[u][1], fd, v1);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < RY; ++u)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const double2 sm = mk(row16_total(acc[u][p].x), row16_total(acc[u][p].y));
+        if (l == 15 && i0 + u * kScrGroups < n) yb[(size_t)p * n + i0 + u * kScrGroups] = sm;
+      }
+  }
+  __syncthreads();
+  // r_p = y_p - Gamma (s X y_p + v_p) on the rows of the sample
+  double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};    // |r_0|^2, |r_1|^2, |F X|^2, |F|^2, Re tr(F X)
+  for (int q0 = 0; q0 < ns; q0 += RR * kScrGroups) {
+    int row[RR];
+#pragma unroll
+    for (int u = 0; u < RR; ++u) row[u] = probe_at(n, min(q0 + u * kScrGroups + grp, ns - 1));
+    double2 acc[RR][2];
+#pragma unroll
+    for (int u = 0; u < RR; ++u) acc[u][0] = acc[u][1] = mk(0.0, 0.0);
+    for (int c0 = 0; c0 < n; c0 += kScrCols) {
+      __syncthreads();
+      for (int j = c0 + t; j < min(n, c0 + kScrCols); j += kScrThreads) {
+        const bool in = probe_in(n, j);
+        const double2 x = X[j];
+        for (int p = 0; p < 2; ++p) {
+          const double2 z = cscale(cmul(x, yb[(size_t)p * n + j]), sign);
+          wt[j - c0][p] = in ? cadd(z, probe_vec(j, p)) : z;
+        }
+      }
+      __syncthreads();
+      for (int j = c0 + l; j < min(n, c0 + kScrCols); j += 16) {
+        float2 gv[RR];
+#pragma unroll
+        for (int u = 0; u < RR; ++u) gv[u] = Gb[(size_t)row[u] * n + j];
+        const double2 w0 = wt[j - c0][0], w1 = wt[j - c0][1];
+#pragma unroll
+        for (int u = 0; u < RR; ++u) {
+          const double2 gd = to_d(gv[u]);
+          cfma(acc[u][0], gd, w0);
+          cfma(acc[u][1], gd, w1);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < RR; ++u)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const double2 sm = mk(row16_total(acc[u][p].x), row16_total(acc[u][p].y));
+        if (l == 15 && q0 + u * kScrGroups + grp < ns)
+          s[p] += cabs2(csub(yb[(size_t)p * n + row[u]], sm));
+      }
+  }
+  for (int j = t; j < n; j += kScrThreads) {
     double c = 0.0;
     for (int rb = 0; rb < nr; ++rb) c += (double)pcs[((size_t)blk * nr + rb) * n + j];
-    s[2] += c * cabs2(chi0[(size_t)blk * n + j]);
+    s[2] += c * cabs2(X[j]);
     s[3] += c;
-  }
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const double2 f = to_d(F[(size_t)blk * n * n + (size_t)i * n + i]), x = chi0[(size_t)blk * n + i];
+    const double2 f = to_d(Fb[(size_t)j * n + j]), x = X[j];
     s[4] += f.x * x.x - f.y * x.y;
   }
   for (int k = 0; k < 5; ++k) s[k] = block_sum(s[k], red);
-  if (threadIdx.x == 0) {
+  if (t == 0) {
     double* ps = pst + (size_t)blk * kPst;
     const double samp = (double)n / ns;
     const double amp2 = fmax(0.0, 1.0 + (2.0 * sign * s[4] + s[2]) / n);     // |A^-1|_F^2 / n
@@ -1932,32 +1966,37 @@ __global__ __launch_bounds__(kThreads) void probe_est_kernel(const double2* r, c
   }
 }
 
+__device__ inline double safe_ratio(double num2, double den2) {
+  if (num2 == 0.0) return 0.0;
+  return sqrt(num2 / den2);     // den2 = 0 with num2 > 0: +inf (flagged)
+}
+
 // c_p = r_p + s F^ (X r_p) = E v_p for the marked blocks; writes |c_p|^2 per row.
 template <int NP>
 __global__ __launch_bounds__(kThreads) void probe_c_kernel(const float2* F, const double2* chi0, const double2* r,
                                                           int n, double sign, const double* pst, double* cq) {
   const int blk = blockIdx.y, lane = threadIdx.x & 63;
   if (pst[(size_t)blk * kPst + 6] != 2.0) return;
-  const int i = blockIdx.x * kWaves + (threadIdx.x >> 6);
-  if (i >= n) return;
-  const float2* Fb = F + (size_t)blk * n * n + (size_t)i * n;
   const double2* X = chi0 + (size_t)blk * n;
   const double2* rb = r + (size_t)blk * NP * n;
-  double2 c[NP];
+  for (int i = blockIdx.x * kWaves + (threadIdx.x >> 6); i < n; i += gridDim.x * kWaves) {
+    const float2* Fb = F + (size_t)blk * n * n + (size_t)i * n;
+    double2 c[NP];
 #pragma unroll
-  for (int p = 0; p < NP; ++p) c[p] = mk(0.0, 0.0);
-  for (int j = lane; j < n; j += 64) {
-    const double2 x = X[j];
-    const double2 fd = to_d(Fb[j]);
+    for (int p = 0; p < NP; ++p) c[p] = mk(0.0, 0.0);
+    for (int j = lane; j < n; j += 64) {
+      const double2 x = X[j];
+      const double2 fd = to_d(Fb[j]);
 #pragma unroll
-    for (int p = 0; p < NP; ++p) cfma(c[p], fd, cmul(x, rb[(size_t)p * n + j]));
-  }
+      for (int p = 0; p < NP; ++p) cfma(c[p], fd, cmul(x, rb[(size_t)p * n + j]));
+    }
 #pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    const double2 sm = mk(wave_sum(c[p].x), wave_sum(c[p].y));
-    if (lane == 0) {
-      const double2 a = rb[(size_t)p * n + i];
-      cq[((size_t)blk * n + i) * NP + p] = cabs2(mk(a.x + sign * sm.x, a.y + sign * sm.y));
+    for (int p = 0; p < NP; ++p) {
+      const double2 sm = mk(wave_sum(c[p].x), wave_sum(c[p].y));
+      if (lane == 0) {
+        const double2 a = rb[(size_t)p * n + i];
+        cq[((size_t)blk * n + i) * NP + p] = cabs2(mk(a.x + sign * sm.x, a.y + sign * sm.y));
+      }
     }
   }
 }
@@ -1995,7 +2034,6 @@ __global__ __launch_bounds__(kThreads) void probe_flag_kernel(const double* cq, 
 //    holds alpha (F^ - Gamma) + (1 - alpha) Phi_old, so the FP64 F enters as
 //    Phi + alpha (F_64 - F^) (no saved copy needed; F^ is still in B).
 // Flagged blocks beyond the slots keep the complex64 result and pst[7] = 1.
-constexpr int kMaxBlocks = kBseMaxBlocks;   // blocks of one launch sequence (a batch: K Nq)
 
 __device__ inline bool pivot_flagged(const double* ps, float weak, double kappa_max) {
   const double ratio = ps[1] > 0.0 ? ps[0] / ps[1] : 0.0;
@@ -2004,27 +2042,40 @@ __device__ inline bool pivot_flagged(const double* ps, float weak, double kappa_
 
 __global__ __launch_bounds__(kThreads) void refine_list_kernel(double* pst, int Nq, float weak, double kappa_max,
                                                               int S, int late, int* list) {
-  __shared__ unsigned char flag[kMaxBlocks];
-  for (int b = threadIdx.x; b < Nq; b += blockDim.x) {
-    double* ps = pst + (size_t)b * kPst;
-    const bool piv = pivot_flagged(ps, weak, kappa_max);
-    flag[b] = late ? (!piv && ps[6] == 1.0) : piv;
-    if (!late) {
-      ps[3] = 0.0;
-      ps[7] = 0.0;
-    }
-  }
-  __syncthreads();                  // (also orders the resets before the overflow marks below)
-  if (threadIdx.x == 0) {           // ordered compaction from LDS
-    int c = late ? list[S] : 0;
-    for (int b = 0; b < Nq; ++b) {
-      if (flag[b]) {
-        if (c < S) list[c++] = b;
-        else pst[(size_t)b * kPst + 7] = 1.0;
+  // chunks of one block per thread in order; a block's slot is the running count
+  // plus its rank among the flagged of its chunk (ballots per wave)
+  __shared__ int wcount[kWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int c = late ? list[S] : 0;
+  for (int b0 = 0; b0 < Nq; b0 += kThreads) {
+    const int b = b0 + (int)threadIdx.x;
+    bool flag = false;
+    if (b < Nq) {
+      double* ps = pst + (size_t)b * kPst;
+      const bool piv = pivot_flagged(ps, weak, kappa_max);
+      flag = late ? (!piv && ps[6] == 1.0) : piv;
+      if (!late) {
+        ps[3] = 0.0;
+        ps[7] = 0.0;
       }
     }
-    list[S] = c;
-    if (!late) list[S + 1] = c;
+    const unsigned long long m = __ballot(flag);
+    if (lane == 0) wcount[wave] = __popcll(m);
+    __syncthreads();
+    int at = c + __popcll(m & ((1ull << lane) - 1));
+    for (int i = 0; i < kWaves; ++i) {
+      if (i < wave) at += wcount[i];
+      c += wcount[i];
+    }
+    if (flag) {
+      if (at < S) list[at] = b;
+      else pst[(size_t)b * kPst + 7] = 1.0;
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    list[S] = min(c, S);
+    if (!late) list[S + 1] = min(c, S);
   }
 }
 
@@ -2032,18 +2083,18 @@ __global__ __launch_bounds__(kThreads) void refine_list_kernel(double* pst, int 
 __global__ __launch_bounds__(kThreads) void refine_gather_kernel(const float2* gamma, const double2* chi0,
                                                                   const float2* phi, int n, const int* list, int S,
                                                                   int late, double2* g64, double2* x64, float2* phis) {
-  const int slot = blockIdx.y;
   const int lo = late ? list[S + 1] : 0, hi = list[S];
-  if (slot < lo || slot >= hi) return;
-  const int b = list[slot];
   const size_t nn = (size_t)n * n;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nn; i += (size_t)gridDim.x * blockDim.x) {
-    const float2 v = gamma[(size_t)b * nn + i];
-    g64[(size_t)slot * nn + i] = mk((double)v.x, (double)v.y);
-    if (!late) phis[(size_t)slot * nn + i] = phi[(size_t)b * nn + i];   // Phi before this solve
+  for (int slot = lo + (int)blockIdx.y; slot < hi; slot += gridDim.y) {
+    const int b = list[slot];
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nn; i += (size_t)gridDim.x * blockDim.x) {
+      const float2 v = gamma[(size_t)b * nn + i];
+      g64[(size_t)slot * nn + i] = mk((double)v.x, (double)v.y);
+      if (!late) phis[(size_t)slot * nn + i] = phi[(size_t)b * nn + i];   // Phi before this solve
+    }
+    if (blockIdx.x == 0)
+      for (int i = threadIdx.x; i < n; i += blockDim.x) x64[(size_t)slot * n + i] = chi0[(size_t)b * n + i];
   }
-  if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i < n; i += blockDim.x) x64[(size_t)slot * n + i] = chi0[(size_t)b * n + i];
 }
 
 // Phi of a re-solved block from the FP64 solution p64 = F_64 - Gamma:
@@ -2055,36 +2106,36 @@ __global__ __launch_bounds__(kThreads) void refine_scatter_kernel(const double2*
                                                                    const double* pst64, const float2* gamma,
                                                                    const float2* fhat, int n, const int* list, int S,
                                                                    double alpha, float2* phi, double* pst) {
-  const int slot = blockIdx.y;
-  if (slot >= list[S]) return;
-  const int b = list[slot];
-  const bool early = slot < list[S + 1];
-  double* ps = pst + (size_t)b * kPst;
-  const bool ok = !(pst64[(size_t)slot * kPst + 2] > 0.0) && (early || ps[5] <= DBL_MAX);
-  if (!ok) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) ps[7] = 1.0;
-    return;
-  }
   const size_t nn = (size_t)n * n;
   const bool mix = alpha != 1.0;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nn; i += (size_t)gridDim.x * blockDim.x) {
-    double2 v = p64[(size_t)slot * nn + i];
-    if (early) {
-      if (mix) {
-        const float2 o = phis[(size_t)slot * nn + i];
-        v.x = alpha * v.x + (1.0 - alpha) * (double)o.x;
-        v.y = alpha * v.y + (1.0 - alpha) * (double)o.y;
-      }
-    } else {
-      const double2 cur = to_d(phi[(size_t)b * nn + i]);
-      const double2 g = to_d(gamma[(size_t)b * nn + i]);
-      const double2 f = to_d(fhat[(size_t)b * nn + i]);
-      v.x = cur.x + alpha * (v.x + g.x - f.x);
-      v.y = cur.y + alpha * (v.y + g.y - f.y);
+  for (int slot = blockIdx.y; slot < list[S]; slot += gridDim.y) {
+    const int b = list[slot];
+    const bool early = slot < list[S + 1];
+    double* ps = pst + (size_t)b * kPst;
+    const bool ok = !(pst64[(size_t)slot * kPst + 2] > 0.0) && (early || ps[5] <= DBL_MAX);
+    if (!ok) {
+      if (blockIdx.x == 0 && threadIdx.x == 0) ps[7] = 1.0;
+      continue;
     }
-    phi[(size_t)b * nn + i] = mkf((float)v.x, (float)v.y);
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nn; i += (size_t)gridDim.x * blockDim.x) {
+      double2 v = p64[(size_t)slot * nn + i];
+      if (early) {
+        if (mix) {
+          const float2 o = phis[(size_t)slot * nn + i];
+          v.x = alpha * v.x + (1.0 - alpha) * (double)o.x;
+          v.y = alpha * v.y + (1.0 - alpha) * (double)o.y;
+        }
+      } else {
+        const double2 cur = to_d(phi[(size_t)b * nn + i]);
+        const double2 g = to_d(gamma[(size_t)b * nn + i]);
+        const double2 f = to_d(fhat[(size_t)b * nn + i]);
+        v.x = cur.x + alpha * (v.x + g.x - f.x);
+        v.y = cur.y + alpha * (v.y + g.y - f.y);
+      }
+      phi[(size_t)b * nn + i] = mkf((float)v.x, (float)v.y);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) ps[3] = 1.0;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) ps[3] = 1.0;
 }
 
 // Re-solve slots per channel: as many as kResolveBudget bytes hold (at least
@@ -2223,7 +2274,10 @@ static hipError_t run_bse(const Dims& d, int channel, double alpha, float weak, 
   int* list = nullptr;
   double2 *g64 = nullptr, *x64 = nullptr, *p64 = nullptr;
   float2* phis = nullptr;
+  // workgroups of the gather and scatter of re-solved blocks: they walk the slots,
+  // since none is in use as a rule (a grid over every slot took 15 us to exit)
   const unsigned gx = (unsigned)std::min<size_t>(256, ((size_t)n * n + kThreads - 1) / kThreads);
+  const unsigned gs = (unsigned)std::min(S, 8);
   if constexpr (sizeof(T) == 4) {
     list = (int*)(w + L.list);
     g64 = (double2*)(w + L.g64);
@@ -2235,7 +2289,7 @@ static hipError_t run_bse(const Dims& d, int channel, double alpha, float weak, 
     if constexpr (sizeof(T) == 4) {
       hipLaunchKernelGGL(refine_list_kernel, dim3(1), dim3(kThreads), 0, st, a.pst, d.Nq, weak, kappa_max, S, late,
                          list);
-      hipLaunchKernelGGL(refine_gather_kernel, dim3(gx, S), dim3(kThreads), 0, st, (const float2*)gamma, chi0,
+      hipLaunchKernelGGL(refine_gather_kernel, dim3(gx, gs), dim3(kThreads), 0, st, (const float2*)gamma, chi0,
                          (const float2*)phi_io, n, list, S, late, g64, x64, phis);
     }
   };
@@ -2246,7 +2300,7 @@ static hipError_t run_bse(const Dims& d, int channel, double alpha, float weak, 
     const int pj = j0 / NB;
     pre(1, st);
     hipLaunchKernelGGL((bse_pivot_kernel<T, NB>), dim3(1, d.Nq), dim3(pivot_threads<NB>()), 0, st, a, j0);
-    if (j0 == 0 || jb < NB) {
+    if (a.nJ > 1 && (j0 == 0 || jb < NB)) {     // one panel: no row above or below it
       BseCtx<T> am = a;
       am.MT = mtb[pj % 3];
       hipLaunchKernelGGL((bse_multcopy_kernel<T, NB>), dim3((n + 31) / 32, d.Nq), dim3(kThreads), 0, st, am, j0);
@@ -2458,11 +2512,7 @@ static hipError_t run_bse(const Dims& d, int channel, double alpha, float weak, 
     // re-solve of the flagged blocks
     pre(5, s);
     const double sg = kSign[channel];
-    const unsigned rows_scr = kWaves * 4, rows_ref = kWaves;
-    const unsigned rx_all = (unsigned)((n + rows_scr - 1) / rows_scr);
-    const int ns = n <= 256 ? n : 128;
-    const unsigned rx_s = (unsigned)((ns + rows_scr - 1) / rows_scr);
-    const unsigned rx_ref = (unsigned)((n + rows_ref - 1) / rows_ref);
+    const unsigned rx_ref = (unsigned)std::min(64, (n + kWaves - 1) / kWaves);
     double2* py = (double2*)(w + L.py);
     double2* pr = (double2*)(w + L.pr);
     double* pcq = (double*)(w + L.pcq);
@@ -2470,16 +2520,11 @@ static hipError_t run_bse(const Dims& d, int channel, double alpha, float weak, 
     const float2* gm = (const float2*)gamma;
     const double* cpst = a.pst;
     // screen (every block)
-    hipLaunchKernelGGL((probe_y_kernel<kNpScreen, 4, false>), dim3(rx_all, d.Nq), dim3(kThreads), 0, s, fh, n, cpst,
-                       py);
-    hipLaunchKernelGGL((probe_r_kernel<kNpScreen, 4, false>), dim3(rx_s, d.Nq), dim3(kThreads), 0, s, gm, chi0,
-                       (const double2*)py, n, sg, cpst, pr);
-    hipLaunchKernelGGL(probe_est_kernel, dim3(d.Nq), dim3(kThreads), 0, s, (const double2*)pr,
-                       (const float*)a.pcs, fh, chi0, n, sg, err_tol, a.pst);
+    hipLaunchKernelGGL(probe_screen_kernel, dim3(d.Nq), dim3(kScrThreads), 0, s, fh, gm, chi0, (const float*)a.pcs, n,
+                       sg, err_tol, py, a.pst);
     // refined estimate (the marked blocks only; the others exit at once)
-    hipLaunchKernelGGL((probe_y_kernel<kNpRefine, 1, true>), dim3(rx_ref, d.Nq), dim3(kThreads), 0, s, fh, n, cpst,
-                       py);
-    hipLaunchKernelGGL((probe_r_kernel<kNpRefine, 1, true>), dim3(rx_ref, d.Nq), dim3(kThreads), 0, s, gm, chi0,
+    hipLaunchKernelGGL((probe_y_kernel<kNpRefine>), dim3(rx_ref, d.Nq), dim3(kThreads), 0, s, fh, n, cpst, py);
+    hipLaunchKernelGGL((probe_r_kernel<kNpRefine>), dim3(rx_ref, d.Nq), dim3(kThreads), 0, s, gm, chi0,
                        (const double2*)py, n, sg, cpst, pr);
     hipLaunchKernelGGL((probe_c_kernel<kNpRefine>), dim3(rx_ref, d.Nq), dim3(kThreads), 0, s, fh, chi0,
                        (const double2*)pr, n, sg, cpst, pcq);
@@ -2492,7 +2537,7 @@ static hipError_t run_bse(const Dims& d, int channel, double alpha, float weak, 
     hipError_t e = run_bse<double>(r, channel, 1.0, 1e-10f, 1e12, 0.0, 0, g64, x64, p64, nullptr, w + L.ws64, s,
                                    nullptr, list + S);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(refine_scatter_kernel, dim3(gx, S), dim3(kThreads), 0, s, (const double2*)p64,
+    hipLaunchKernelGGL(refine_scatter_kernel, dim3(gx, gs), dim3(kThreads), 0, s, (const double2*)p64,
                        (const float2*)phis, (const double*)(w + L.ws64 + L64.pst), (const float2*)gamma, fh, n,
                        list, S, alpha, (float2*)phi_io, a.pst);
     post(s);
