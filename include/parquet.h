@@ -381,7 +381,8 @@ typedef struct {
    * launches), error estimate and FP64 re-solve): summed device time of its
    * launches and the number of launches. The update includes the back
    * substitution and the mixing fused into it; the last kind runs on the
-   * complex64 paths. */
+   * complex64 paths. Where the four channels of a small box share their
+   * launches, the times and flops are a quarter of theirs. */
   double ms_bse_kernel[6];
   int32_t n_bse_launch[6];
   int32_t resolved_blocks;   /* blocks re-solved in FP64 (stats bit 2), last iteration */
@@ -390,7 +391,10 @@ typedef struct {
   double max_err_est;      /* largest BSE error estimate of the last iteration (complex64) */
 } pq_iter_stats;
 
-/* Device bytes parquet_init needs in its workspace. */
+/* Device bytes for parquet_init's workspace. For small boxes this includes room
+ * for the four channels' Bethe-Salpeter equations in shared launches (at most
+ * 8 GiB); parquet_init also takes a workspace with room for one channel's and then
+ * solves them one by one. */
 pq_status parquet_query_workspace(const pq_params* p, size_t* bytes);
 
 /* Bind a context to caller workspace and stream, and set the bare-vertex start:

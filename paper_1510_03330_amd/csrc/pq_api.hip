@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 
 #include <vector>
@@ -351,6 +352,7 @@ struct pq_ctx {
   double *mu, *dnorm;
   void *phi, *gamma, *bse_ws, *sig_ws;
   size_t bse_bytes, sig_bytes;
+  bool four;               // the BSE takes the four channels in one launch sequence
   pq_bse_block_stats* bstats;
   int iteration;
   double dhist[7];         // the last changes of Sigma (newest first), for the contraction estimate
@@ -371,9 +373,11 @@ namespace {
 struct CtxLayout {
   size_t sigma, sigma_new, g, mu, dnorm, xph, xpp, k1, k2, lam, phi, gamma, bse, sig, bstats, total;
   size_t bse_bytes, sig_bytes;
+  bool four;
 };
 
-CtxLayout ctx_layout(const pq_params& p, const Dims& d) {
+// four: room for the four channels of a small box in one BSE launch sequence
+CtxLayout ctx_layout(const pq_params& p, const Dims& d, bool four) {
   CtxLayout L{};
   size_t off = 0;
   auto take = [&](size_t b) { size_t o = off; off += align256(b); return o; };
@@ -391,7 +395,9 @@ CtxLayout ctx_layout(const pq_params& p, const Dims& d) {
   const size_t vb = elem_bytes(p) * (size_t)d.Nq * d.n * d.n * 4;
   L.phi = take(vb);
   L.gamma = take(vb);
-  L.bse_bytes = bse_ws_bytes(p, d, p.precision);
+  L.bse_bytes = four ? bse_four_ws_bytes(p, d) : 0;
+  L.four = L.bse_bytes > 0;
+  if (!L.four) L.bse_bytes = bse_ws_bytes(p, d, p.precision);
   L.bse = take(L.bse_bytes);
   L.sig_bytes = sigma_ws_bytes(d);
   L.sig = take(L.sig_bytes);
@@ -471,7 +477,12 @@ hipError_t enqueue_iteration(pq_ctx* c, bool record, BseTiming* tm, const char**
     return e;
   }
   rec(4);
-  for (int r = 0; r < 4; ++r) {
+  if (c->four) {
+    e = launch_bse_four(p, d, c->gamma, c->xph, c->xpp, c->phi, p.alpha, c->bstats, c->bse_ws, c->s, tm,
+                        lookahead && c->have_la ? &c->la : nullptr);
+    if (e != hipSuccess) { *where = "bse"; return e; }
+  }
+  for (int r = 0; r < 4 && !c->four; ++r) {
     const double2* x = r < 2 ? c->xph : c->xpp;
     e = launch_bse(p, d, r, p.precision, (char*)c->gamma + r * vstride, x, (char*)c->phi + r * vstride, p.alpha,
                    c->bstats + (size_t)r * d.Nq, c->bse_ws, c->s, r == 0 ? tm : nullptr,
@@ -511,7 +522,7 @@ pq_status parquet_query_workspace(const pq_params* p, size_t* bytes) {
   Dims d;
   if (!make_dims(p, &d)) return PQ_ERR_ARG;
   PQ_CHECK_ARG(bytes, "null output");
-  *bytes = ctx_layout(*p, d).total;
+  *bytes = std::max(ctx_layout(*p, d, true).total, ctx_layout(*p, d, false).total);
   return PQ_OK;
 }
 
@@ -519,7 +530,10 @@ pq_status parquet_init(const pq_params* p, void* ws, size_t ws_bytes, pq_stream 
   Dims d;
   if (!make_dims(p, &d)) return PQ_ERR_ARG;
   PQ_CHECK_ARG(ws && out, "null pointer");
-  CtxLayout L = ctx_layout(*p, d);
+  // a workspace that holds one channel's BSE is enough; the four channels of a
+  // small box share their launches where it holds theirs
+  CtxLayout L = ctx_layout(*p, d, true);
+  if (ws_bytes < L.total) L = ctx_layout(*p, d, false);
   if (ws_bytes < L.total) {
     set_error("parquet workspace %zu < %zu bytes", ws_bytes, L.total);
     return PQ_ERR_NOMEM;
@@ -546,6 +560,7 @@ pq_status parquet_init(const pq_params* p, void* ws, size_t ws_bytes, pq_stream 
   c->phi = w + L.phi;
   c->gamma = w + L.gamma;
   c->bse_ws = w + L.bse;
+  c->four = L.four;
   c->sig_ws = w + L.sig;
   c->bse_bytes = L.bse_bytes;
   c->sig_bytes = L.sig_bytes;
@@ -639,11 +654,12 @@ pq_status parquet_iterate(pq_ctx* c, int32_t n_iter, double tol, pq_iter_stats* 
         stats->ms_stage[6] = elapsed_ms(c->ev[5], c->ev[6]);
       }
       if (timing) {
+        const double share = c->four ? 0.25 : 1.0;        // one channel's part of shared launches
         for (int i = 0; i < tm.used; ++i) {
-          stats->ms_bse_kernel[tm.kind[i]] += elapsed_ms(c->bev[2 * i], c->bev[2 * i + 1]);
+          stats->ms_bse_kernel[tm.kind[i]] += share * elapsed_ms(c->bev[2 * i], c->bev[2 * i + 1]);
           stats->n_bse_launch[tm.kind[i]] += 1;
         }
-        stats->update_flops = tm.update_flops;
+        stats->update_flops = share * tm.update_flops;
       }
     }
     if (!(dn == dn)) {

@@ -293,15 +293,35 @@ __device__ inline C* colptr(C* A, C* B, int n, int j0, int jb, int c) {
   return c < ncolA ? A + (j0 + jb + c) : B + (c - ncolA);
 }
 
+// Where the blocks of a launch sequence lie. One channel: Nq blocks, one bubble
+// and sign. Four channels at once (small boxes): blocks 0 .. nbc - 1 are the
+// density channel's, then magnetic, singlet, triplet, their vertices vcs elements
+// apart; X = X_ph for d, m and X_pp for s, t, s = -1 for the singlet channel.
+struct Chans {
+  int n, nbc, nch;
+  long long vcs;
+  const double2* x[2];     // bubble of the (ph, pp) channels; one channel: x[0]
+  double sign1;            // sign of the one channel
+  __device__ int chan(int blk) const { return nch == 1 ? 0 : blk / nbc; }
+  __device__ size_t voff(int blk) const {
+    const int c = chan(blk);
+    return (size_t)c * vcs + (size_t)(blk - c * nbc) * n * n;
+  }
+  __device__ const double2* xrow(int blk) const {
+    const int c = chan(blk);
+    return x[c >> 1] + (size_t)(blk - c * nbc) * n;
+  }
+  __device__ double sign(int blk) const { return nch == 1 ? sign1 : (chan(blk) == 2 ? -1.0 : 1.0); }
+};
+
 template <typename T>
 struct BseCtx {
   using C = typename cplx_of<T>::type;
   int n, Nq, nJ;
-  T sign;
+  Chans ch;
   double alpha;
   float weak_ratio;
-  const C* gamma;        // [Nq][n][n]
-  const double2* chi0;   // [Nq][n]
+  const C* gamma;        // [Nq][n][n] (per channel; block offsets ch.voff)
   C* phi;                // [Nq][n][n]
   C* A;                  // [Nq][n][n]
   C* B;                  // [Nq][n][n]
@@ -346,10 +366,11 @@ __device__ inline typename cplx_of<T>::type system_elem(const BseCtx<T>& a, int 
   const int n = a.n;
   const bool inA = j < n;
   const int col = inA ? j : j - n;
-  const C g = a.gamma[(size_t)blk * n * n + (size_t)i * n + col];
+  const C g = a.gamma[a.ch.voff(blk) + (size_t)i * n + col];
   if (!inA) return g;
-  const double2 xv = a.chi0[(size_t)blk * n + col];
-  const T sx = a.sign * (T)xv.x, sy = a.sign * (T)xv.y;
+  const double2 xv = a.ch.xrow(blk)[col];
+  const T sign = (T)a.ch.sign(blk);
+  const T sx = sign * (T)xv.x, sy = sign * (T)xv.y;
   C v;
   v.x = (i == j ? (T)1 : (T)0) - (g.x * sx - g.y * sy);
   v.y = -(g.x * sy + g.y * sx);
@@ -737,11 +758,12 @@ __device__ inline ColSrc<T> colsrc(const BseCtx<T>& a, int blk, int j0, int jb, 
   r.sy = (T)0;
   if (FIRST) {
     const int col = c < ncolA ? j0 + jb + c : c - ncolA;
-    r.p = a.gamma + (size_t)blk * n * n + (size_t)j0 * n + col;
+    r.p = a.gamma + a.ch.voff(blk) + (size_t)j0 * n + col;
     if (r.inA) {
-      const double2 xv = a.chi0[(size_t)blk * n + col];
-      r.sx = a.sign * (T)xv.x;
-      r.sy = a.sign * (T)xv.y;
+      const double2 xv = a.ch.xrow(blk)[col];
+      const T sign = (T)a.ch.sign(blk);
+      r.sx = sign * (T)xv.x;
+      r.sy = sign * (T)xv.y;
       r.diag = col;
     }
   } else {
@@ -853,7 +875,7 @@ void bse_panel_kernel(BseCtx<T> a, int j0, int nwb, int mix) {
           if (row < jb && col < ncols) {
             colptr(A, B, n, j0, jb, col)[(size_t)(j0 + row) * n] = v;
             if (mixes) {
-              const size_t e = (size_t)blk * n * n + (size_t)(j0 + row) * n + (col - ncolA);
+              const size_t e = a.ch.voff(blk) + (size_t)(j0 + row) * n + (col - ncolA);
               const bool m = a.alpha != 1.0;
               a.phi[e] = mix_phi<T>(v, a.gamma[e], m ? a.phi[e] : cz<C>(), (T)a.alpha, (T)(1.0 - a.alpha), m);
               if constexpr (sizeof(T) == 4) fs[(rb + rt * 32) / 64 % 2] += (float)v.x * v.x + (float)v.y * v.y;
@@ -1096,8 +1118,8 @@ void bse_update_kernel(BseCtx<T> a, int j0, int ncb, int row_lo, int row_hi, int
   // wave-uniform (mix_lo is a multiple of the workgroup tile height)
   if (i0 >= mix_lo) {
     const int ncolA = n - j0 - jb;                 // B column = combined column - ncolA
-    const C* G = a.gamma + (size_t)blk * n * n;
-    C* P = a.phi + (size_t)blk * n * n;
+    const C* G = a.gamma + a.ch.voff(blk);
+    C* P = a.phi + a.ch.voff(blk);
     const T al = (T)a.alpha, be = (T)(1.0 - a.alpha);
     const bool mix = a.alpha != 1.0;
     // complex64: |F_ij|^2 of the finished rows summed per lane (each lane holds
@@ -1446,8 +1468,8 @@ void bse_update_bf_kernel(BseCtx<float> a, int j0, int ncb, int row_lo, int row_
   };
   if (i0 >= mix_lo) {                            // wave-uniform, as in the FP32 kernel
     const int ncolA = n - j0 - jb;
-    const C* G = a.gamma + (size_t)blk * n * n;
-    C* P = a.phi + (size_t)blk * n * n;
+    const C* G = a.gamma + a.ch.voff(blk);
+    C* P = a.phi + a.ch.voff(blk);
     const float al = (float)a.alpha, be = (float)(1.0 - a.alpha);
     const bool mix = a.alpha != 1.0;
     float cs[WN];
@@ -1639,7 +1661,7 @@ void bse_panel_bf_kernel(BseCtx<float> a, int j0, int mix) {
         cp[(size_t)(j0 + r) * n] = val;
         if (col < ncolA) A[(size_t)(j0 + jb + col) * n + j0 + r] = val;
         if (mixes) {
-          const size_t e = (size_t)blk * n * n + (size_t)(j0 + r) * n + (col - ncolA);
+          const size_t e = a.ch.voff(blk) + (size_t)(j0 + r) * n + (col - ncolA);
           a.phi[e] = mix_phi<float>(val, a.gamma[e], m ? a.phi[e] : cz<C>(), al, be, m);
           cs[y] += val.x * val.x + val.y * val.y;
         }
@@ -1808,14 +1830,15 @@ __global__ __launch_bounds__(kThreads) void probe_y_kernel(const float2* F, int 
 
 // r_p = y_p - s Gamma (X y_p) - Gamma v_p on every row of the marked blocks.
 template <int NP>
-__global__ __launch_bounds__(kThreads) void probe_r_kernel(const float2* G, const double2* chi0, const double2* y,
-                                                          int n, double sign, const double* pst, double2* r) {
+__global__ __launch_bounds__(kThreads) void probe_r_kernel(const float2* G, Chans ch, const double2* y, int n,
+                                                          const double* pst, double2* r) {
   const int blk = blockIdx.y, lane = threadIdx.x & 63;
   if (pst[(size_t)blk * kPst + 6] != 2.0) return;
-  const double2* X = chi0 + (size_t)blk * n;
+  const double2* X = ch.xrow(blk);
+  const double sign = ch.sign(blk);
   const double2* yb = y + (size_t)blk * NP * n;
   for (int i = blockIdx.x * kWaves + (threadIdx.x >> 6); i < n; i += gridDim.x * kWaves) {
-    const float2* Gb = G + (size_t)blk * n * n + (size_t)i * n;
+    const float2* Gb = G + ch.voff(blk) + (size_t)i * n;
     double2 g[NP], h[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) g[p] = h[p] = mk(0.0, 0.0);
@@ -1857,16 +1880,17 @@ __device__ inline double row16_total(double v) {     // in the last lane of each
   return dpp_add<0x118, 0xf>(v);
 }
 
-__global__ __launch_bounds__(kScrThreads) void probe_screen_kernel(const float2* F, const float2* G,
-                                                                  const double2* chi0, const float* pcs, int n,
-                                                                  double sign, double tol, double2* y, double* pst) {
+__global__ __launch_bounds__(kScrThreads) void probe_screen_kernel(const float2* F, const float2* G, Chans ch,
+                                                                  const float* pcs, int n, double tol, double2* y,
+                                                                  double* pst) {
   __shared__ double2 wt[kScrCols][2];
   __shared__ double red[kScrThreads];
   const int blk = blockIdx.x, t = threadIdx.x, grp = t >> 4, l = t & 15;
   const int ns = probe_ns(n), nr = (n + 63) / 64;
   const float2* Fb = F + (size_t)blk * n * n;
-  const float2* Gb = G + (size_t)blk * n * n;
-  const double2* X = chi0 + (size_t)blk * n;
+  const float2* Gb = G + ch.voff(blk);
+  const double2* X = ch.xrow(blk);
+  const double sign = ch.sign(blk);
   double2* yb = y + (size_t)blk * kNpScreen * n;
   for (int q = t; q < ns; q += kScrThreads)            // ns <= kScrCols
     for (int p = 0; p < kNpScreen; ++p) wt[q][p] = probe_vec(probe_at(n, q), p);
@@ -1973,11 +1997,12 @@ __device__ inline double safe_ratio(double num2, double den2) {
 
 // c_p = r_p + s F^ (X r_p) = E v_p for the marked blocks; writes |c_p|^2 per row.
 template <int NP>
-__global__ __launch_bounds__(kThreads) void probe_c_kernel(const float2* F, const double2* chi0, const double2* r,
-                                                          int n, double sign, const double* pst, double* cq) {
+__global__ __launch_bounds__(kThreads) void probe_c_kernel(const float2* F, Chans ch, const double2* r, int n,
+                                                          const double* pst, double* cq) {
   const int blk = blockIdx.y, lane = threadIdx.x & 63;
   if (pst[(size_t)blk * kPst + 6] != 2.0) return;
-  const double2* X = chi0 + (size_t)blk * n;
+  const double2* X = ch.xrow(blk);
+  const double sign = ch.sign(blk);
   const double2* rb = r + (size_t)blk * NP * n;
   for (int i = blockIdx.x * kWaves + (threadIdx.x >> 6); i < n; i += gridDim.x * kWaves) {
     const float2* Fb = F + (size_t)blk * n * n + (size_t)i * n;
@@ -2079,21 +2104,24 @@ __global__ __launch_bounds__(kThreads) void refine_list_kernel(double* pst, int 
   }
 }
 
-// Gamma and X of the slots [lo, hi) into the complex128 slots (early list: also Phi).
-__global__ __launch_bounds__(kThreads) void refine_gather_kernel(const float2* gamma, const double2* chi0,
-                                                                  const float2* phi, int n, const int* list, int S,
-                                                                  int late, double2* g64, double2* x64, float2* phis) {
+// Gamma and s X of the slots [lo, hi) into the complex128 slots (early list: also
+// Phi); the re-solve runs with sign +1.
+__global__ __launch_bounds__(kThreads) void refine_gather_kernel(const float2* gamma, Chans ch, const float2* phi, int n,
+                                                                  const int* list, int S, int late, double2* g64,
+                                                                  double2* x64, float2* phis) {
   const int lo = late ? list[S + 1] : 0, hi = list[S];
   const size_t nn = (size_t)n * n;
   for (int slot = lo + (int)blockIdx.y; slot < hi; slot += gridDim.y) {
     const int b = list[slot];
+    const size_t vo = ch.voff(b);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nn; i += (size_t)gridDim.x * blockDim.x) {
-      const float2 v = gamma[(size_t)b * nn + i];
+      const float2 v = gamma[vo + i];
       g64[(size_t)slot * nn + i] = mk((double)v.x, (double)v.y);
-      if (!late) phis[(size_t)slot * nn + i] = phi[(size_t)b * nn + i];   // Phi before this solve
+      if (!late) phis[(size_t)slot * nn + i] = phi[vo + i];   // Phi before this solve
     }
     if (blockIdx.x == 0)
-      for (int i = threadIdx.x; i < n; i += blockDim.x) x64[(size_t)slot * n + i] = chi0[(size_t)b * n + i];
+      for (int i = threadIdx.x; i < n; i += blockDim.x)
+        x64[(size_t)slot * n + i] = cscale(ch.xrow(b)[i], ch.sign(b));
   }
 }
 
@@ -2104,12 +2132,14 @@ __global__ __launch_bounds__(kThreads) void refine_gather_kernel(const float2* g
 // complex64 F^ is not finite, is left as it is and marked unresolved.
 __global__ __launch_bounds__(kThreads) void refine_scatter_kernel(const double2* p64, const float2* phis,
                                                                    const double* pst64, const float2* gamma,
-                                                                   const float2* fhat, int n, const int* list, int S,
-                                                                   double alpha, float2* phi, double* pst) {
+                                                                   const float2* fhat, Chans ch, int n,
+                                                                   const int* list, int S, double alpha, float2* phi,
+                                                                   double* pst) {
   const size_t nn = (size_t)n * n;
   const bool mix = alpha != 1.0;
   for (int slot = blockIdx.y; slot < list[S]; slot += gridDim.y) {
     const int b = list[slot];
+    const size_t vo = ch.voff(b);
     const bool early = slot < list[S + 1];
     double* ps = pst + (size_t)b * kPst;
     const bool ok = !(pst64[(size_t)slot * kPst + 2] > 0.0) && (early || ps[5] <= DBL_MAX);
@@ -2126,13 +2156,13 @@ __global__ __launch_bounds__(kThreads) void refine_scatter_kernel(const double2*
           v.y = alpha * v.y + (1.0 - alpha) * (double)o.y;
         }
       } else {
-        const double2 cur = to_d(phi[(size_t)b * nn + i]);
-        const double2 g = to_d(gamma[(size_t)b * nn + i]);
+        const double2 cur = to_d(phi[vo + i]);
+        const double2 g = to_d(gamma[vo + i]);
         const double2 f = to_d(fhat[(size_t)b * nn + i]);
         v.x = cur.x + alpha * (v.x + g.x - f.x);
         v.y = cur.y + alpha * (v.y + g.y - f.y);
       }
-      phi[(size_t)b * nn + i] = mkf((float)v.x, (float)v.y);
+      phi[vo + i] = mkf((float)v.x, (float)v.y);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) ps[3] = 1.0;
   }
@@ -2204,26 +2234,28 @@ size_t bse_ws_bytes(const pq_params& p, const Dims& d, int precision) {
   return precision == PQ_PREC_FP64 ? bse_layout<double>(d).total : bse_layout<float>(d, p.resolve_slots).total;
 }
 
+static Chans one_channel(const Dims& d, int channel, const double2* chi0) {
+  return Chans{d.n, d.Nq, 1, 0, {chi0, chi0}, channel == 2 ? -1.0 : 1.0};
+}
+
 template <typename T, bool BF3 = false>
-static hipError_t run_bse(const Dims& d, int channel, double alpha, float weak, double kappa_max, double err_tol,
-                          int slots_req, const void* gamma, const double2* chi0, void* phi_io,
+static hipError_t run_bse(const Dims& d, const Chans& ch, double alpha, float weak, double kappa_max, double err_tol,
+                          int slots_req, const void* gamma, void* phi_io,
                           pq_bse_block_stats* stats, void* ws, hipStream_t s, BseTiming* tm,
                           const int* active = nullptr, int tile = 0, const BseAsync* la = nullptr) {
   using C = typename cplx_of<T>::type;
   constexpr int NB = panel_width<T>();
-  static const double kSign[4] = {1.0, 1.0, -1.0, 1.0};
   const BseLayout L = bse_layout<T>(d, slots_req);
   char* w = (char*)ws;
   BseCtx<T> a;
   a.n = d.n;
   a.Nq = d.Nq;
   a.nJ = (d.n + NB - 1) / NB;
-  a.sign = (T)kSign[channel];
+  a.ch = ch;
   a.alpha = alpha;
   a.weak_ratio = weak;
   a.kappa_max = kappa_max;
   a.gamma = (const C*)gamma;
-  a.chi0 = chi0;
   a.phi = (C*)phi_io;
   a.A = (C*)(w + L.A);
   a.B = (C*)(w + L.B);
@@ -2289,7 +2321,7 @@ static hipError_t run_bse(const Dims& d, int channel, double alpha, float weak, 
     if constexpr (sizeof(T) == 4) {
       hipLaunchKernelGGL(refine_list_kernel, dim3(1), dim3(kThreads), 0, st, a.pst, d.Nq, weak, kappa_max, S, late,
                          list);
-      hipLaunchKernelGGL(refine_gather_kernel, dim3(gx, gs), dim3(kThreads), 0, st, (const float2*)gamma, chi0,
+      hipLaunchKernelGGL(refine_gather_kernel, dim3(gx, gs), dim3(kThreads), 0, st, (const float2*)gamma, ch,
                          (const float2*)phi_io, n, list, S, late, g64, x64, phis);
     }
   };
@@ -2511,7 +2543,6 @@ static hipError_t run_bse(const Dims& d, int channel, double alpha, float weak, 
     // error estimate of every block (B holds the complex64 F), then the FP64
     // re-solve of the flagged blocks
     pre(5, s);
-    const double sg = kSign[channel];
     const unsigned rx_ref = (unsigned)std::min(64, (n + kWaves - 1) / kWaves);
     double2* py = (double2*)(w + L.py);
     double2* pr = (double2*)(w + L.pr);
@@ -2520,25 +2551,25 @@ static hipError_t run_bse(const Dims& d, int channel, double alpha, float weak, 
     const float2* gm = (const float2*)gamma;
     const double* cpst = a.pst;
     // screen (every block)
-    hipLaunchKernelGGL(probe_screen_kernel, dim3(d.Nq), dim3(kScrThreads), 0, s, fh, gm, chi0, (const float*)a.pcs, n,
-                       sg, err_tol, py, a.pst);
+    hipLaunchKernelGGL(probe_screen_kernel, dim3(d.Nq), dim3(kScrThreads), 0, s, fh, gm, ch, (const float*)a.pcs, n,
+                       err_tol, py, a.pst);
     // refined estimate (the marked blocks only; the others exit at once)
     hipLaunchKernelGGL((probe_y_kernel<kNpRefine>), dim3(rx_ref, d.Nq), dim3(kThreads), 0, s, fh, n, cpst, py);
-    hipLaunchKernelGGL((probe_r_kernel<kNpRefine>), dim3(rx_ref, d.Nq), dim3(kThreads), 0, s, gm, chi0,
-                       (const double2*)py, n, sg, cpst, pr);
-    hipLaunchKernelGGL((probe_c_kernel<kNpRefine>), dim3(rx_ref, d.Nq), dim3(kThreads), 0, s, fh, chi0,
-                       (const double2*)pr, n, sg, cpst, pcq);
+    hipLaunchKernelGGL((probe_r_kernel<kNpRefine>), dim3(rx_ref, d.Nq), dim3(kThreads), 0, s, gm, ch,
+                       (const double2*)py, n, cpst, pr);
+    hipLaunchKernelGGL((probe_c_kernel<kNpRefine>), dim3(rx_ref, d.Nq), dim3(kThreads), 0, s, fh, ch,
+                       (const double2*)pr, n, cpst, pcq);
     hipLaunchKernelGGL((probe_flag_kernel<kNpRefine>), dim3(d.Nq), dim3(kThreads), 0, s, (const double*)pcq, n,
                        err_tol, a.pst);
     refine_gather(1, s);
     Dims r = d;
     r.Nq = S;
     const BseLayout L64 = bse_layout<double>(r);
-    hipError_t e = run_bse<double>(r, channel, 1.0, 1e-10f, 1e12, 0.0, 0, g64, x64, p64, nullptr, w + L.ws64, s,
+    hipError_t e = run_bse<double>(r, one_channel(r, 0, x64), 1.0, 1e-10f, 1e12, 0.0, 0, g64, p64, nullptr, w + L.ws64, s,
                                    nullptr, list + S);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(refine_scatter_kernel, dim3(gx, gs), dim3(kThreads), 0, s, (const double2*)p64,
-                       (const float2*)phis, (const double*)(w + L.ws64 + L64.pst), (const float2*)gamma, fh, n,
+                       (const float2*)phis, (const double*)(w + L.ws64 + L64.pst), (const float2*)gamma, fh, ch, n,
                        list, S, alpha, (float2*)phi_io, a.pst);
     post(s);
   }
@@ -2583,13 +2614,12 @@ hipError_t launch_bse_summary(const pq_bse_block_stats* stats, int nb, double* o
   return hipGetLastError();
 }
 
-hipError_t launch_bse(const pq_params& p, const Dims& d, int channel, int precision,
-                      const void* gamma, const double2* chi0, void* phi_io, double alpha,
-                      pq_bse_block_stats* stats, void* ws, hipStream_t s, BseTiming* tm, const BseAsync* la) {
+static hipError_t dispatch_bse(const pq_params& p, const Dims& d, const Chans& ch, int precision, const void* gamma,
+                               void* phi_io, double alpha, pq_bse_block_stats* stats, void* ws, hipStream_t s,
+                               BseTiming* tm, const BseAsync* la, int slots) {
   if (precision == PQ_PREC_FP64) {
     if (p.storage != PQ_STORE_C128) return hipErrorInvalidValue;
-    return run_bse<double>(d, channel, alpha, 1e-10f, 1e12, 0.0, 0, gamma, chi0, phi_io, stats, ws, s, tm, nullptr,
-                           0, la);
+    return run_bse<double>(d, ch, alpha, 1e-10f, 1e12, 0.0, 0, gamma, phi_io, stats, ws, s, tm, nullptr, 0, la);
   }
   if (p.storage != PQ_STORE_C64) return hipErrorInvalidValue;
   // complex64: a block is re-solved in FP64 when its pivot ratio drops below
@@ -2597,10 +2627,47 @@ hipError_t launch_bse(const pq_params& p, const Dims& d, int channel, int precis
   // error estimate exceeds bse_tol (default 2e-5)
   const double tol = p.bse_tol > 0.0 ? p.bse_tol : kDefaultBseTol;
   if (precision == PQ_PREC_BF16X3)
-    return run_bse<float, true>(d, channel, alpha, 1e-3f, 1e3, tol, p.resolve_slots, gamma, chi0, phi_io, stats, ws,
-                                s, tm, nullptr, p.bse_tile, la);
-  return run_bse<float>(d, channel, alpha, 1e-3f, 1e3, tol, p.resolve_slots, gamma, chi0, phi_io, stats, ws, s, tm,
-                        nullptr, p.bse_tile, la);
+    return run_bse<float, true>(d, ch, alpha, 1e-3f, 1e3, tol, slots, gamma, phi_io, stats, ws, s, tm, nullptr,
+                                p.bse_tile, la);
+  return run_bse<float>(d, ch, alpha, 1e-3f, 1e3, tol, slots, gamma, phi_io, stats, ws, s, tm, nullptr, p.bse_tile,
+                        la);
+}
+
+hipError_t launch_bse(const pq_params& p, const Dims& d, int channel, int precision,
+                      const void* gamma, const double2* chi0, void* phi_io, double alpha,
+                      pq_bse_block_stats* stats, void* ws, hipStream_t s, BseTiming* tm, const BseAsync* la) {
+  return dispatch_bse(p, d, one_channel(d, channel, chi0), precision, gamma, phi_io, alpha, stats, ws, s, tm, la,
+                      p.resolve_slots);
+}
+
+// Four channels in one launch sequence: a box of few or small blocks does not fill
+// the chip with one channel's, and a channel's 4 to 60 launches cost more than
+// their work. An iteration, four channels together and one by one: one momentum
+// Nv = 32 complex128 202 and 334 us, 2x2 Nv = 32 complex64 0.54 and 1.04 ms, 4x4
+// Nv = 8 complex128 0.72 and 1.13 ms, 4x4 Nv = 16 complex64 3.18 and 3.87 ms, 6x6
+// Nv = 8 complex64 5.8 and 7.2 ms. The workspace is that of 4 Nq blocks (at most
+// four times one channel's), so what ends it is memory: kFourBytes, 3 % of the card's,
+// beyond which a channel's launches are long enough (8x8 Nv = 16 BF16x3: 52 ms of
+// work a channel). complex64 only where every flagged block has its re-solve slot
+// (a limit on the slots is per channel).
+constexpr size_t kFourBytes = size_t(8) << 30;
+
+size_t bse_four_ws_bytes(const pq_params& p, const Dims& d) {
+  Dims r = d;
+  r.Nq = 4 * d.Nq;
+  if (r.Nq > kBseMaxBlocks) return 0;
+  if (p.precision != PQ_PREC_FP64 && resolve_slots(d, p.resolve_slots) < d.Nq) return 0;
+  const size_t b = p.precision == PQ_PREC_FP64 ? bse_layout<double>(r).total : bse_layout<float>(r, r.Nq).total;
+  return b <= kFourBytes ? b : 0;
+}
+
+hipError_t launch_bse_four(const pq_params& p, const Dims& d, const void* gamma, const double2* xph, const double2* xpp,
+                           void* phi_io, double alpha, pq_bse_block_stats* stats, void* ws, hipStream_t s,
+                           BseTiming* tm, const BseAsync* la) {
+  Dims r = d;
+  r.Nq = 4 * d.Nq;
+  const Chans ch{d.n, d.Nq, 4, d.cs, {xph, xpp}, 1.0};
+  return dispatch_bse(p, r, ch, p.precision, gamma, phi_io, alpha, stats, ws, s, tm, la, r.Nq);
 }
 
 }  // namespace pq

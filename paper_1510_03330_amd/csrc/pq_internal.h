@@ -103,6 +103,13 @@ hipError_t launch_bse(const pq_params& p, const Dims& d, int channel, int precis
                       const void* gamma, const double2* chi0, void* phi_io, double alpha,
                       pq_bse_block_stats* stats, void* ws, hipStream_t s, BseTiming* tm = nullptr,
                       const BseAsync* la = nullptr);
+// All four channels of a small box in one launch sequence (gamma and phi_io:
+// [4][Nq][n][n], stats [4][Nq]); its workspace, or 0 where the box is solved
+// channel by channel.
+size_t bse_four_ws_bytes(const pq_params& p, const Dims& d);
+hipError_t launch_bse_four(const pq_params& p, const Dims& d, const void* gamma, const double2* xph, const double2* xpp,
+                           void* phi_io, double alpha, pq_bse_block_stats* stats, void* ws, hipStream_t s,
+                           BseTiming* tm = nullptr, const BseAsync* la = nullptr);
 // summary of nb block stats into out[0..3]: flagged, re-solved and unresolved
 // block counts, largest error estimate (+inf for a non-finite one); with
 // nchunks > 1, over nchunks runs of nb stats, stride apart

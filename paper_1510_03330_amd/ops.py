@@ -162,28 +162,42 @@ class Solver:
         lib = N.load()
         b = ctypes.c_size_t()
         N.check(lib.parquet_query_workspace(self.stage._pp(), ctypes.byref(b)))
-        self.ws = torch.empty(max(int(b.value), int(ws_bytes)), dtype=torch.uint8, device=self.device)
-        if stream is not None:
-            self.ws.record_stream(stream)      # the context's work runs on its own stream
         self.ctx = None
+        try:
+            self._bind(max(int(b.value), int(ws_bytes)))
+        except torch.OutOfMemoryError:
+            # The channels of a small box share their launches where their room is
+            # there; on a device short of memory one channel's, which is at least a
+            # quarter of the whole, is enough (parquet_init turns down less).
+            for part in range(15, 3, -1):
+                try:
+                    self._bind(max(int(b.value) * part // 16, int(ws_bytes)))
+                    return
+                except torch.OutOfMemoryError:
+                    continue
+                except N.ParquetError:
+                    break
+            raise
+
+    def _bind(self, nbytes: int):
+        self.ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        if self.stream is not None:
+            self.ws.record_stream(self.stream)      # the context's work runs on its own stream
         self.reinit()
 
     def reinit(self, p=None):
         """Start again from the bare-vertex state (a new context on the same
         workspace: parquet_init, nothing allocated), with new model parameters
         p if given (any whose workspace fits the one held)."""
-        if p is not None:
-            st = Stage(p, *self._stage_args)
-            b = ctypes.c_size_t()
-            N.check(N.load().parquet_query_workspace(st._pp(), ctypes.byref(b)))
-            if int(b.value) > self.ws.numel():
-                raise ValueError(f"parameters need a {int(b.value)}-byte workspace, "
-                                 f"this solver holds {self.ws.numel()}")
-            self.stage = st
-        self.close()
+        st = self.stage if p is None else Stage(p, *self._stage_args)
         ctx = ctypes.c_void_p()
-        N.check(N.load().parquet_init(self.stage._pp(), ctypes.c_void_p(self.ws.data_ptr()),
-                                      ctypes.c_size_t(self.ws.numel()), _stream(self.stream), ctypes.byref(ctx)))
+        status = N.load().parquet_init(st._pp(), ctypes.c_void_p(self.ws.data_ptr()),
+                                       ctypes.c_size_t(self.ws.numel()), _stream(self.stream), ctypes.byref(ctx))
+        if status == N.PQ_ERR_NOMEM and p is not None:      # nothing was touched: this solver is as it was
+            raise ValueError(f"parameters need a larger workspace than the {self.ws.numel()} bytes this solver holds")
+        self.close()
+        N.check(status)
+        self.stage = st
         self.ctx = ctx
         self.last_stats = None
 
