@@ -2,10 +2,12 @@
 // and the context API that runs whole parquet iterations on one stream.
 #include <math.h>
 #include <stdarg.h>
+#include <stdint.h>
 #include <stdio.h>
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <new>
 
 #include <vector>
@@ -359,8 +361,11 @@ struct pq_ctx {
   int nhist;
   hipEvent_t ev[8];
   bool have_events;
-  hipEvent_t bev[512];   // BSE launch timing of one channel
+  hipEvent_t bev[512];   // BSE launch timing of one channel (nbev of them)
+  int nbev;
   bool have_bev;
+  double* host;          // pinned results of an iteration (HostSlots), or null
+  bool pending;          // an iteration may still write them
   BseAsync la;           // BSE look-ahead stream and events (uncaptured iterations only)
   bool have_la;
   hipGraphExec_t graph;  // one whole iteration captured on s (parquet_iterate_batch)
@@ -369,6 +374,66 @@ struct pq_ctx {
 };
 
 namespace {
+
+// Results of an iteration (kResults doubles: the norm, the BSE summary
+// (bse_summary), max |Sigma|, mu~), written by its last kernel into pinned host
+// memory, so that the host reads them after its one wait. Copies to pageable
+// memory made it wait twice: one momentum Nv = 32, an iteration 206 us with two,
+// 190 with one, 171 this way. Slots of a page that all contexts of the process
+// share (a page of its own would cost each context its allocation); it is freed
+// with its last slot. Contexts beyond kSlots copy.
+constexpr int kResults = 7;
+
+class HostSlots {
+  static constexpr int kSlots = 64, kDoubles = 8;
+  std::mutex mu_;
+  double* page_ = nullptr;
+  uint64_t used_ = 0;
+
+ public:
+  double* take() {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (!page_) {
+      void* v = nullptr;
+      if (hipHostMalloc(&v, sizeof(double) * kDoubles * kSlots, hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
+      page_ = (double*)v;
+    }
+    for (int i = 0; i < kSlots; ++i)
+      if (!((used_ >> i) & 1)) {
+        used_ |= uint64_t(1) << i;
+        return page_ + kDoubles * i;
+      }
+    return nullptr;
+  }
+  void give(double* p) {
+    if (!p) return;
+    std::lock_guard<std::mutex> lock(mu_);
+    used_ &= ~(uint64_t(1) << ((p - page_) / kDoubles));
+    if (!used_) {
+      (void)hipHostFree(page_);
+      page_ = nullptr;
+    }
+  }
+};
+
+HostSlots& host_slots() {
+  static HostSlots* s = new HostSlots();      // never destroyed: contexts may outlive static objects
+  return *s;
+}
+
+// the results of the iteration that c's stream has finished or is about to
+hipError_t read_results(pq_ctx* c, double (&res)[kResults]) {
+  hipError_t e = hipSuccess;
+  if (!c->host) e = hipMemcpyAsync(res, c->dnorm, sizeof(res), hipMemcpyDeviceToHost, c->s);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->s);
+  if (e != hipSuccess) return e;
+  c->pending = false;
+  if (c->host) memcpy(res, c->host, sizeof(res));
+  return e;
+}
 
 struct CtxLayout {
   size_t sigma, sigma_new, g, mu, dnorm, xph, xpp, k1, k2, lam, phi, gamma, bse, sig, bstats, total;
@@ -385,8 +450,9 @@ CtxLayout ctx_layout(const pq_params& p, const Dims& d, bool four) {
   L.sigma = take(sizeof(double2) * d.Nve * nk);
   L.sigma_new = take(sizeof(double2) * d.Nve * nk);
   L.g = take(sizeof(double2) * d.NG * nk);
-  L.mu = take(sizeof(double));
-  L.dnorm = take(6 * sizeof(double));      // the norm, the BSE summary (bse_summary), max |Sigma|
+  L.dnorm = take(kResults * sizeof(double));
+  L.mu = L.dnorm + (kResults - 1) * sizeof(double);
+  take(sizeof(double));
   L.xph = take(sizeof(double2) * (size_t)d.Nq * d.n);
   L.xpp = take(sizeof(double2) * (size_t)d.Nq * d.n);
   L.k1 = take(sizeof(double2) * 4 * (size_t)d.Nq);
@@ -491,7 +557,7 @@ hipError_t enqueue_iteration(pq_ctx* c, bool record, BseTiming* tm, const char**
   }
   if ((e = launch_bse_summary(c->bstats, 4 * d.Nq, c->dnorm + 1, c->s)) != hipSuccess) { *where = "bse summary"; return e; }
   rec(5);
-  if ((e = launch_mix(d, c->sigma_new, c->sigma, p.alpha, c->dnorm, c->s, c->dnorm + 5)) != hipSuccess) {
+  if ((e = launch_mix(d, c->sigma_new, c->sigma, p.alpha, c->dnorm, c->s, c->dnorm + 5, c->host)) != hipSuccess) {
     *where = "mix";
     return e;
   }
@@ -569,14 +635,19 @@ pq_status parquet_init(const pq_params* p, void* ws, size_t ws_bytes, pq_stream 
   c->nhist = 0;
   c->have_graph = false;
   c->graph_has_lam = false;
+  c->host = host_slots().take();
+  c->pending = false;
   c->have_events = true;
   for (int i = 0; i < 8; ++i)
     if (hipEventCreate(&c->ev[i]) != hipSuccess) c->have_events = false;
+  // as many as its timed launches can need: at most 6 per panel (64 wide or more), 4 beside
+  c->nbev = 2 * std::min(256, 6 * ((d.n + 63) / 64) + 4);
   c->have_bev = true;
-  for (int i = 0; i < 512; ++i)
+  for (int i = 0; i < c->nbev; ++i)
     if (hipEventCreate(&c->bev[i]) != hipSuccess) c->have_bev = false;
-  // look-ahead stream (default priority) and its two events
-  c->have_la = hipStreamCreateWithFlags(&c->la.side, hipStreamNonBlocking) == hipSuccess;
+  // look-ahead stream (default priority) and its two events; blocks of one panel
+  // have nothing to look ahead to
+  c->have_la = d.n > 64 && hipStreamCreateWithFlags(&c->la.side, hipStreamNonBlocking) == hipSuccess;
   if (c->have_la && hipEventCreateWithFlags(&c->la.ready, hipEventDisableTiming) != hipSuccess) {
     (void)hipStreamDestroy(c->la.side);
     c->have_la = false;
@@ -597,9 +668,10 @@ pq_status parquet_init(const pq_params* p, void* ws, size_t ws_bytes, pq_stream 
   *out = c;
   return PQ_OK;
 fail:
+  host_slots().give(c->host);
   for (int i = 0; i < 8; ++i)
     if (c->have_events) (void)hipEventDestroy(c->ev[i]);
-  for (int i = 0; i < 512; ++i)
+  for (int i = 0; i < c->nbev; ++i)
     if (c->have_bev) (void)hipEventDestroy(c->bev[i]);
   if (c->have_la) {
     (void)hipEventDestroy(c->la.ready);
@@ -620,18 +692,20 @@ pq_status parquet_iterate(pq_ctx* c, int32_t n_iter, double tol, pq_iter_stats* 
     hipError_t e = hipSuccess;
     BseTiming tm;
     tm.ev = c->bev;
-    tm.cap = 256;
+    tm.cap = c->nbev / 2;
     tm.used = 0;
     tm.update_flops = 0.0;
-    const bool timing = stats && c->have_bev;
+    // the times are those of the last iteration; without a convergence test that
+    // is known before it runs, and the others go without their events
+    const bool last = tol != 0.0 || it == n_iter - 1;
+    const bool events = c->have_events && stats && last;
+    const bool timing = stats && c->have_bev && last;
     const char* where = nullptr;
-    if ((e = enqueue_iteration(c, c->have_events, timing ? &tm : nullptr, &where, true)) != hipSuccess)
+    c->pending = true;
+    if ((e = enqueue_iteration(c, events, timing ? &tm : nullptr, &where, true)) != hipSuccess)
       return hip_fail(e, where);
-    double res[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, mu = 0.0;  // norm, flagged, re-solved, unresolved,
-                                                                 // max estimate, max |Sigma|
-    if ((e = hipMemcpyAsync(res, c->dnorm, sizeof(res), hipMemcpyDeviceToHost, c->s)) != hipSuccess) return hip_fail(e, "norm copy");
-    if ((e = hipMemcpyAsync(&mu, c->mu, sizeof(double), hipMemcpyDeviceToHost, c->s)) != hipSuccess) return hip_fail(e, "mu copy");
-    if ((e = hipStreamSynchronize(c->s)) != hipSuccess) return hip_fail(e, "iteration");
+    double res[kResults] = {};  // norm, flagged, re-solved, unresolved, max estimate, max |Sigma|, mu~
+    if ((e = read_results(c, res)) != hipSuccess) return hip_fail(e, "iteration");
     const double dn = res[0];
     c->iteration++;
     done++;
@@ -639,12 +713,15 @@ pq_status parquet_iterate(pq_ctx* c, int32_t n_iter, double tol, pq_iter_stats* 
       memset(stats, 0, sizeof(*stats));
       stats->iteration = c->iteration;
       stats->dsigma = dn;
-      stats->mu = mu;
+      stats->mu = res[6];
       stats->flagged_blocks = (int32_t)res[1];
       stats->resolved_blocks = (int32_t)res[2];
       stats->unresolved_blocks = (int32_t)res[3];
       stats->max_err_est = res[4];
-      if (c->have_events) {
+      if (c->have_events && !events) {
+        stats->ms_total = __builtin_nan("");
+        for (double& ms : stats->ms_stage) ms = stats->ms_total;
+      } else if (events) {
         stats->ms_total = elapsed_ms(c->ev[0], c->ev[6]);
         stats->ms_stage[0] = elapsed_ms(c->ev[0], c->ev[1]);
         stats->ms_stage[1] = elapsed_ms(c->ev[1], c->ev[2]);
@@ -724,13 +801,13 @@ pq_status parquet_iterate_batch(pq_ctx* const* ctxs, int32_t count, int32_t n_it
     if (converged) converged[i] = 0;
   }
   std::vector<char> active(count, 1);
-  std::vector<double> res(6 * (size_t)count, 0.0);
   bool nonfinite = false, singular = false;
   for (int it = 0; it < n_iter; ++it) {
     bool any = false;
     for (int i = 0; i < count; ++i) {
       if (!active[i]) continue;
       any = true;
+      ctxs[i]->pending = true;
       hipError_t e = hipGraphLaunch(ctxs[i]->graph, ctxs[i]->s);
       if (e != hipSuccess) return hip_fail(e, "graph launch");
     }
@@ -738,9 +815,8 @@ pq_status parquet_iterate_batch(pq_ctx* const* ctxs, int32_t count, int32_t n_it
     for (int i = 0; i < count; ++i) {
       if (!active[i]) continue;
       pq_ctx* c = ctxs[i];
-      double* r = &res[6 * (size_t)i];
-      hipError_t e = hipMemcpyAsync(r, c->dnorm, 6 * sizeof(double), hipMemcpyDeviceToHost, c->s);
-      if (e == hipSuccess) e = hipStreamSynchronize(c->s);
+      double r[kResults] = {};
+      hipError_t e = read_results(c, r);
       if (e != hipSuccess) return hip_fail(e, "batch iteration");
       c->iteration++;
       if (iters_done) iters_done[i]++;
@@ -868,7 +944,8 @@ pq_status parquet_destroy(pq_ctx* c) {
   if (c->have_events)
     for (int i = 0; i < 8; ++i) (void)hipEventDestroy(c->ev[i]);
   if (c->have_bev)
-    for (int i = 0; i < 512; ++i) (void)hipEventDestroy(c->bev[i]);
+    for (int i = 0; i < c->nbev; ++i) (void)hipEventDestroy(c->bev[i]);
+  if (!c->pending) host_slots().give(c->host);      // kept for good after a failed iteration
   delete c;
   return PQ_OK;
 }

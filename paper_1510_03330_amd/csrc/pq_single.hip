@@ -202,7 +202,7 @@ __global__ __launch_bounds__(kThreads) void bubble_kernel(BubbleArgs a) {
 }
 
 __global__ __launch_bounds__(kThreads) void mix_kernel(int count, const double2* snew, double2* sio,
-                                                       double alpha, double* dnorm, double* smax) {
+                                                       double alpha, double* dnorm, double* smax, double* host) {
   __shared__ double red[kThreads];
   double mx = 0.0, bad = 0.0, sm = 0.0;
   for (int i = threadIdx.x; i < count; i += blockDim.x) {
@@ -221,6 +221,12 @@ __global__ __launch_bounds__(kThreads) void mix_kernel(int count, const double2*
   if (threadIdx.x == 0) {
     *dnorm = bad > 0.0 ? __builtin_nan("") : mx;
     if (smax) *smax = sm;
+    if (host) {                       // dnorm[1 .. 4]: the BSE summary, dnorm[6]: mu~
+      host[0] = *dnorm;
+      for (int i = 1; i < 5; ++i) host[i] = dnorm[i];
+      host[5] = sm;
+      host[6] = dnorm[6];
+    }
   }
 }
 
@@ -314,8 +320,8 @@ hipError_t launch_bubbles(const pq_params& p, const Dims& d, const double2* g, d
 }
 
 hipError_t launch_mix(const Dims& d, const double2* snew, double2* sio, double alpha,
-                      double* dnorm, hipStream_t s, double* smax) {
-  hipLaunchKernelGGL(mix_kernel, dim3(1), dim3(kThreads), 0, s, d.Nve * d.Nk, snew, sio, alpha, dnorm, smax);
+                      double* dnorm, hipStream_t s, double* smax, double* host) {
+  hipLaunchKernelGGL(mix_kernel, dim3(1), dim3(kThreads), 0, s, d.Nve * d.Nk, snew, sio, alpha, dnorm, smax, host);
   return hipGetLastError();
 }
 
