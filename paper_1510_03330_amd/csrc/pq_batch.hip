@@ -30,12 +30,6 @@ using namespace pq;
 
 namespace {
 
-// Branches of a round's graph for the stages of single instances, which one
-// instance leaves waiting on launches of one or a few workgroups (4x4 Nv = 8
-// complex128: 60 of 175 us). Four, as many as a process has hardware queues: four
-// rounds of 8 such instances 19.1 ms on one branch, 17.3 on two, 16.2 on four and
-// on eight; 2x2 3.1 ms on two, 2.6 on four, 2.4 to 2.6 on eight.
-constexpr int kBranches = 4;
 constexpr int kDn = 8;        // doubles per instance: change, BSE summary (4), max |Sigma|, spare
 
 struct BInst {
@@ -140,9 +134,6 @@ struct pq_batch {
   double* dn_host;            // pinned, kDn per instance
   hipGraphExec_t graph;
   bool have_graph;
-  int nbr;                    // branches of a captured round (1: the main stream alone)
-  hipStream_t br[kBranches];  // br[0] = s; the others only take part in captures
-  hipEvent_t fork, join[kBranches];
   int tile;
   float tile_ms[2];
 };
@@ -160,13 +151,10 @@ double2* slot_x(pq_batch* b, size_t base, int slot) {
 double* inst_dn(pq_batch* b, int i) { return (double*)(b->ws + b->L.dn) + (size_t)kDn * i; }
 
 // the stages before the BSE of the instance in a slot
-hipError_t enqueue_pre(pq_batch* b, int slot, int branch, const char** where) {
+hipError_t enqueue_pre(pq_batch* b, int slot, const char** where) {
   BInst& x = b->inst[b->at_slot[slot]];
   const double lam[4] = {x.p.U, -x.p.U, 2.0 * x.p.U, 0.0};
-  hipStream_t s = b->br[branch];
-  // scratch of its own for each branch: the first has its region, the others lie in
-  // the BSE's, which runs after the join
-  void* sig = branch == 0 ? b->ws + b->L.sig : b->ws + b->L.bse + (size_t)(branch - 1) * align256(b->L.sig_bytes);
+  hipStream_t s = b->s;
   void* phi = slot_vertex(b, b->L.phi, slot);
   void* gamma = slot_vertex(b, b->L.gamma, slot);
   double2* xph = slot_x(b, b->L.xph, slot);
@@ -176,7 +164,7 @@ hipError_t enqueue_pre(pq_batch* b, int slot, int branch, const char** where) {
   if ((e = launch_bubbles(x.p, x.d, x.g, xph, xpp, s)) != hipSuccess) { *where = "bubbles"; return e; }
   if ((e = launch_kernel_extract(x.p, x.d, phi, x.k1, x.k2, s)) != hipSuccess) { *where = "kernels"; return e; }
   if ((e = launch_remap(x.p, x.d, lam, nullptr, phi, x.k1, x.k2, gamma, s)) != hipSuccess) { *where = "remap"; return e; }
-  if ((e = launch_sigma(x.p, x.d, phi, x.k1, x.k2, nullptr, x.g, x.mu, x.sigma_new, sig, s)) !=
+  if ((e = launch_sigma(x.p, x.d, phi, x.k1, x.k2, nullptr, x.g, x.mu, x.sigma_new, b->ws + b->L.sig, s)) !=
       hipSuccess) {
     *where = "sigma";
     return e;
@@ -202,10 +190,10 @@ hipError_t enqueue_bse(pq_batch* b, int nactive, const char** where) {
   return hipSuccess;
 }
 
-hipError_t enqueue_post(pq_batch* b, int slot, int branch, const char** where) {
+hipError_t enqueue_post(pq_batch* b, int slot, const char** where) {
   const int i = b->at_slot[slot];
   BInst& x = b->inst[i];
-  hipStream_t s = b->br[branch];
+  hipStream_t s = b->s;
   const Dims& d = b->d0;
   double* dn = inst_dn(b, i);
   hipError_t e = launch_bse_summary((pq_bse_block_stats*)(b->ws + b->L.bstats) + (size_t)slot * d.Nq, d.Nq, dn + 1,
@@ -213,34 +201,6 @@ hipError_t enqueue_post(pq_batch* b, int slot, int branch, const char** where) {
   if (e != hipSuccess) { *where = "bse summary"; return e; }
   if ((e = launch_mix(x.d, x.sigma_new, x.sigma, x.p.alpha, dn, s, dn + 5)) != hipSuccess) { *where = "mix"; return e; }
   return hipSuccess;
-}
-
-void close_branches(pq_batch* b) {
-  for (int i = 1; i < b->nbr; ++i) {
-    (void)hipEventDestroy(b->join[i]);
-    (void)hipStreamDestroy(b->br[i]);
-  }
-  if (b->nbr > 1) (void)hipEventDestroy(b->fork);
-  b->nbr = 1;
-}
-
-// the branches that the batch has work and scratch for (fewer where the runtime
-// gives no more streams or events)
-void open_branches(pq_batch* b) {
-  b->br[0] = b->s;
-  b->nbr = 1;
-  const size_t more = b->L.bse_bytes / align256(b->L.sig_bytes);
-  const int want = (int)std::min<size_t>(std::min(kBranches, b->K), 1 + more);
-  if (want < 2 || hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) != hipSuccess) return;
-  for (int i = 1; i < want; ++i) {
-    if (hipStreamCreateWithFlags(&b->br[i], hipStreamNonBlocking) != hipSuccess) break;
-    if (hipEventCreateWithFlags(&b->join[i], hipEventDisableTiming) != hipSuccess) {
-      (void)hipStreamDestroy(b->br[i]);
-      break;
-    }
-    b->nbr = i + 1;
-  }
-  if (b->nbr == 1) (void)hipEventDestroy(b->fork);
 }
 
 // one round of the active instances, captured into b->graph
@@ -253,21 +213,9 @@ hipError_t capture_round(pq_batch* b, const char** where) {
   hipError_t e = hipStreamBeginCapture(b->s, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) { *where = "capture begin"; return e; }
   hipError_t err = hipSuccess;
-  const int nbr = std::min(b->nbr, A);
-  // every slot's launches on the branch that is its turn, the branches joined after them
-  auto over_slots = [&](hipError_t (*enqueue)(pq_batch*, int, int, const char**)) {
-    if (nbr > 1 && (err = hipEventRecord(b->fork, b->s)) != hipSuccess) *where = "fork";
-    for (int i = 1; i < nbr && err == hipSuccess; ++i)
-      if ((err = hipStreamWaitEvent(b->br[i], b->fork, 0)) != hipSuccess) *where = "fork";
-    for (int slot = 0; slot < A && err == hipSuccess; ++slot) err = enqueue(b, slot, slot % nbr, where);
-    for (int i = 1; i < nbr && err == hipSuccess; ++i) {
-      if ((err = hipEventRecord(b->join[i], b->br[i])) == hipSuccess) err = hipStreamWaitEvent(b->s, b->join[i], 0);
-      if (err != hipSuccess) *where = "join";
-    }
-  };
-  over_slots(enqueue_pre);
+  for (int slot = 0; slot < A && err == hipSuccess; ++slot) err = enqueue_pre(b, slot, where);
   if (err == hipSuccess) err = enqueue_bse(b, A, where);
-  if (err == hipSuccess) over_slots(enqueue_post);
+  for (int slot = 0; slot < A && err == hipSuccess; ++slot) err = enqueue_post(b, slot, where);
   hipGraph_t g = nullptr;
   e = hipStreamEndCapture(b->s, &g);
   if (err != hipSuccess) {
@@ -425,10 +373,8 @@ pq_status parquet_batch_init(const pq_params* ps, int32_t count, void* ws, size_
     for (double& h : x.dhist) h = 0.0;
     b->at_slot[i] = i;
   }
-  open_branches(b);
   e = batch_setup(b, autotune != 0);
   if (e != hipSuccess) {
-    close_branches(b);
     (void)hipHostFree(b->dn_host);
     delete b;
     return hip_fail(e, "parquet_batch_init");
@@ -538,7 +484,6 @@ pq_status parquet_batch_destroy(pq_batch* b) {
   if (!b) return PQ_OK;
   (void)hipStreamSynchronize(b->s);
   if (b->have_graph) (void)hipGraphExecDestroy(b->graph);
-  close_branches(b);
   if (b->dn_host) (void)hipHostFree(b->dn_host);
   delete b;
   return PQ_OK;
