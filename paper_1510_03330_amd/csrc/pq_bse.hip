@@ -359,23 +359,36 @@ __device__ inline bool inactive(const BseCtx<T>& a, int blk) { return a.active &
 // first panel read Gamma and form A = 1 - s Gamma diag(X) on the fly (B starts
 // as Gamma), and their writes create the A and B arrays the later panels use
 // (pivot rows from the pivot-row step, every other row from the update).
-// Element (i, j) of [A | B] in the combined column index j (< n: A, else B).
+// A column of A, or (first panel) of Gamma with the factors that make it one of A.
+// Block offsets, X and the sign are looked up once per column: the loads of a
+// kernel's elements are then independent and unbranched.
 template <typename T>
-__device__ inline typename cplx_of<T>::type system_elem(const BseCtx<T>& a, int blk, int i, int j) {
+struct SysCol {
   using C = typename cplx_of<T>::type;
-  const int n = a.n;
-  const bool inA = j < n;
-  const int col = inA ? j : j - n;
-  const C g = a.gamma[a.ch.voff(blk) + (size_t)i * n + col];
-  if (!inA) return g;
-  const double2 xv = a.ch.xrow(blk)[col];
-  const T sign = (T)a.ch.sign(blk);
-  const T sx = sign * (T)xv.x, sy = sign * (T)xv.y;
-  C v;
-  v.x = (i == j ? (T)1 : (T)0) - (g.x * sx - g.y * sy);
-  v.y = -(g.x * sy + g.y * sx);
-  return v;
-}
+  const C* p;
+  T sx, sy;
+  bool first;
+  int n, j;
+  __device__ SysCol(const BseCtx<T>& a, int blk, int j0, int col) : first(j0 == 0), n(a.n), j(col) {
+    p = (first ? a.gamma + a.ch.voff(blk) : a.A + (size_t)blk * n * n) + col;
+    sx = sy = (T)0;
+    if (first) {
+      const double2 xv = a.ch.xrow(blk)[col];
+      const T sign = (T)a.ch.sign(blk);
+      sx = sign * (T)xv.x;
+      sy = sign * (T)xv.y;
+    }
+  }
+  __device__ C raw(int i) const { return p[(size_t)i * n]; }
+  __device__ C form(C g, int i) const {
+    C v;
+    v.x = (i == j ? (T)1 : (T)0) - (g.x * sx - g.y * sy);
+    v.y = -(g.x * sy + g.y * sx);
+    v.x = first ? v.x : g.x;                      // by parts: a select of structs can go through memory
+    v.y = first ? v.y : g.y;
+    return v;
+  }
+};
 
 // Multipliers of panel J: A[i][J0 .. J0 + NB) for 32 rows i0 .. i0 + 31,
 // through an LDS transpose into MT[k][i]; rows k >= jb of MT (ragged last
@@ -392,19 +405,26 @@ template <typename T, int NB>
 __device__ void copy_multipliers(const BseCtx<T>& a, int blk, int j0, int i0,
                                  typename cplx_of<T>::type (*X)[NB + 1]) {
   using C = typename cplx_of<T>::type;
-  const int t = threadIdx.x, nt = blockDim.x, n = a.n;
+  const int t = threadIdx.x, n = a.n;
   const int jb = min(NB, n - j0);
   C* A = a.A + (size_t)blk * n * n;
   C* MT = a.MT + (size_t)blk * NB * n;
   C* UT = j0 != (a.nJ - 1) * NB ? A + (size_t)j0 * n : MT;
-  for (int idx = t; idx < 32 * NB; idx += nt) {
-    const int r = idx / NB, k = idx - (idx / NB) * NB;
-    const int i = min(i0 + r, n - 1), j = j0 + min(k, jb - 1);
-    const C v = j0 == 0 ? system_elem(a, blk, i, j) : A[(size_t)i * n + j];
-    X[r][k] = k < jb ? v : cz<C>();
+  static_assert(kThreads % NB == 0, "one column per thread");
+  constexpr int RS = kThreads / NB, NR = 32 / RS;          // rows per pass, passes
+  const int k = t % NB, r0 = t / NB;
+  const SysCol<T> src(a, blk, j0, j0 + min(k, jb - 1));
+  C g[NR];
+#pragma unroll
+  for (int q = 0; q < NR; ++q) g[q] = src.raw(min(i0 + r0 + q * RS, n - 1));
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    const int r = r0 + q * RS;
+    X[r][k] = k < jb ? src.form(g[q], min(i0 + r, n - 1)) : cz<C>();
   }
   __syncthreads();
-  for (int idx = t; idx < 32 * NB; idx += nt) {
+#pragma unroll
+  for (int idx = t; idx < 32 * NB; idx += kThreads) {
     const int k = idx >> 5, r = idx & 31;
     if (i0 + r < n) (i0 + r < j0 ? UT : MT)[(size_t)k * n + i0 + r] = X[r][k];
   }
@@ -427,8 +447,9 @@ __device__ void copy_multipliers(const BseCtx<T>& a, int blk, int j0, int i0,
 // Four real products per complex product; bound by the matrix cores (128 x 128
 // complex64: 65k cycles per block and CU) and, with one block per CU, by the chain
 // of 16 x 16 inversions. One pivot at a time on the vector unit with a barrier
-// each (before): 226 us for 240 complex64 blocks, 588 for 960; complex128 64 x 64:
-// 52 us for 31 blocks, 211 for 896. Now 82 and 237, 27 and 120 us.
+// each (before): 226 us for 240 complex64 blocks, 588 for 960; complex128 52 us for 31
+// blocks of 32 x 32, 211 for 896 of 64 x 64. Now 79 and 232, 20 and 95 us (27 and
+// 120 while the pivots of a step were kept through scratch memory).
 template <int NB> constexpr int pivot_threads() { return 4 * NB; }
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -517,18 +538,27 @@ __device__ __forceinline__ void invert_step(T (&xr)[4], T (&xi)[4], typename cpl
   C p;
   p.x = row_bcast<c>(pcr);
   p.y = row_bcast<c>(pci);
-  pv = r == c ? p : pv;                                             // lane c: pivot c
+  pv.x = r == c ? p.x : pv.x;                                       // lane c: pivot c (by parts: a select of
+  pv.y = r == c ? p.y : pv.y;                                       // structs goes through scratch memory)
+  // every row r takes x - m E[c], m = E[r][c] / pivot; row c itself is E[c] / pivot
+  // (x = 0, m = -1 / pivot), and column c enters as the identity's
   const C ip = pivot_recip(p);
+  const bool prow = r == c;
+  const T mr = prow ? -ip.x : pcr * ip.x - pci * ip.y;
+  const T mi = prow ? -ip.y : pcr * ip.y + pci * ip.x;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const T rr = row_bcast<c>(xr[q]), ri = row_bcast<c>(xi[q]);       // E[c][own column]
-    const bool pcol = q == V && g == G;
-    const T ur = pcol ? ip.x : rr * ip.x - ri * ip.y;
-    const T ui = pcol ? ip.y : rr * ip.y + ri * ip.x;
-    const T x0 = pcol ? (T)0 : xr[q], x1 = pcol ? (T)0 : xi[q];
-    const T nr = fma(-pcr, ur, fma(pci, ui, x0)), ni = fma(-pcr, ui, fma(-pci, ur, x1));
-    xr[q] = r == c ? ur : nr;
-    xi[q] = r == c ? ui : ni;
+    T rr = row_bcast<c>(xr[q]), ri = row_bcast<c>(xi[q]);             // E[c][own column]
+    T x0 = prow ? (T)0 : xr[q], x1 = prow ? (T)0 : xi[q];
+    if (q == V) {
+      const bool pcol = g == G;
+      rr = pcol ? (T)1 : rr;
+      ri = pcol ? (T)0 : ri;
+      x0 = pcol ? (T)0 : x0;
+      x1 = pcol ? (T)0 : x1;
+    }
+    xr[q] = fma(-mr, rr, fma(mi, ri, x0));
+    xi[q] = fma(-mr, ri, fma(-mi, rr, x1));
   }
   if constexpr (c + 1 < 16) invert_step<T, c + 1>(xr, xi, pv);
 }
@@ -548,19 +578,32 @@ void bse_pivot_kernel(BseCtx<T> a, int j0) {
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int col = t & 15, g = (t >> 4) & 3;
   const int jb = min(NB, n - j0), steps = (jb + 15) / 16;
-  const C* A = a.A + (size_t)blk * n * n;
   acc_t re[TN], im[TN];                              // tile p: rows 16 ((s + p) % TN) ..
+  {
+    const int j = 16 * w + col;
+    const SysCol<T> src(a, blk, j0, j0 + min(j, jb - 1));
 #pragma unroll
-  for (int p = 0; p < TN; ++p)
+    for (int p = 0; p < TN; ++p)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = 16 * p + M::crow(g, v), j = 16 * w + col;
-      const int ri = j0 + min(r, jb - 1), ci = j0 + min(j, jb - 1);
-      const C x = j0 == 0 ? system_elem(a, blk, ri, ci) : A[(size_t)ri * n + ci];
-      const bool in = r < jb && j < jb;
-      re[p][v] = in ? x.x : (r == j ? (T)1 : (T)0);
-      im[p][v] = in ? x.y : (T)0;
-    }
+      for (int v = 0; v < 4; ++v) {
+        const C x = src.raw(j0 + min(16 * p + M::crow(g, v), jb - 1));
+        re[p][v] = x.x;
+        im[p][v] = x.y;
+      }
+#pragma unroll
+    for (int p = 0; p < TN; ++p)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = 16 * p + M::crow(g, v);
+        C x;
+        x.x = re[p][v];
+        x.y = im[p][v];
+        const C y = src.form(x, j0 + min(r, jb - 1));
+        const bool in = r < jb && j < jb;
+        re[p][v] = in ? y.x : (r == j ? (T)1 : (T)0);
+        im[p][v] = in ? y.y : (T)0;
+      }
+  }
   // D^-1 of a diagonal tile to LDS, by the wave that owns it
   auto publish_inverse = [&](const acc_t& dr, const acc_t& di, int s, int b) __attribute__((always_inline)) {
     T xr[4], xi[4];
@@ -582,7 +625,7 @@ void bse_pivot_kernel(BseCtx<T> a, int j0) {
       dinv[b][M::crow(g, v)][col] = x;
     }
   };
-  auto publish_column = [&](int s, int b) {          // tile p holds the rows of tile row s + p
+  auto publish_column = [&](int s, int b) __attribute__((always_inline)) {   // tile p: the rows of tile row s + p
 #pragma unroll
     for (int p = 0; p < TN; ++p)
 #pragma unroll
@@ -594,7 +637,8 @@ void bse_pivot_kernel(BseCtx<T> a, int j0) {
       }
   };
   // c -= (sub) or = m b, m a 16 x 16 LDS tile in the first operand's layout
-  auto product = [&](const C (*m)[M::LD], const acc_t& br, const acc_t& bi, acc_t& cr, acc_t& ci, bool sub) {
+  auto product = [&](const C (*m)[M::LD], const acc_t& br, const acc_t& bi, acc_t& cr, acc_t& ci,
+                     bool sub) __attribute__((always_inline)) {
     C x[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) x[q] = m[col][M::crow(g, q)];
@@ -697,8 +741,9 @@ void bse_pivot_kernel(BseCtx<T> a, int j0) {
   }
 }
 
-// Multiplier copy of panel J (independent of the diagonal-block inverse; its
-// own launch, since sharing the inversion launch halves both kernels' slots):
+// Multiplier copy of panel J, a stream of it (960 blocks, n = 256, complex64: 503
+// MB in 84 us, 139 us with one load in flight; independent of the diagonal-block
+// inverse; its own launch, since sharing the inversion launch halves both kernels' slots):
 // 32 rows of A_IJ per workgroup into MT.
 template <typename T, int NB>
 __global__ __launch_bounds__(kThreads) void bse_multcopy_kernel(BseCtx<T> a, int j0) {
