@@ -20,6 +20,7 @@
 // gathers), and the kernel part only needs contiguous rows of K2.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "pq_internal.h"
@@ -270,16 +271,18 @@ __global__ __launch_bounds__(kRowThreads) void s1_row_kernel(S1Args a) {
 // The momentum sums are therefore done first, once per (p, n_b):
 //   U1 = sum_B G(b+p) G(b),  U3 = sum_B G(p-b) G(b),
 //   V1d, V1m = sum_B G(b+p) G(b) K2_{d,m}(b;p),  V3st = sum_B G(p-b) G(b) (K2_s + K2_t)(b;p)
-// (the V's for b in the box), and the k sum runs over n_b only:
-//   s16 = G(k+p) sum e16 U1,  s25 = G(k+p) sum e25 U1,  s34 = G(p-k) sum e34 U3,
-//   sk  = G(k+p) sum [e16 V1d - (e16 + 2 e25) V1m] + G(p-k) sum e34 V3st.
+// (the V's for b in the box), then the sums over n_b once per (n_k, p),
+//   A16 = sum e16 U1,  A25 = sum e25 U1,  A34 = sum e34 U3,
+//   B1 = sum [e16 V1d - (e16 + 2 e25) V1m],  B3 = sum e34 V3st,
+// and for every k
+//   s16 = G(k+p) A16,  s25 = G(k+p) A25,  s34 = G(p-k) A34,  sk = G(k+p) B1 + G(p-k) B3.
 struct S2Args {
   Dims d;
   int level;
   const double2* g;
   const double2* k1;     // [4][Nq]
   const double2* k2;     // [4][Nq][n]
-  double2* tab;          // [NG][5][Nq]  U1, U3, V1d, V1m, V3st per (n_b, p)
+  double2* tab;          // [Nve][5][Nq]  A16, A25, A34, B1, B3 per (n_k, p) (room for NG >= Nve)
 };
 
 __device__ inline double ind(bool b) { return b ? 1.0 : 0.0; }
@@ -289,39 +292,107 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
-// sw lanes (the power of two >= Nk) per (n_b, p), over the momentum B: a lattice
-// of few momenta fills its waves with several entries
-__global__ __launch_bounds__(kThreads) void s2_tables_kernel(S2Args a, int sw) {
+constexpr int kS2Chunk = 256;    // frequencies n_b whose U, V lie in LDS at a time (20 KB)
+constexpr int kS2Sl = 8;         // lanes that share a sum over n_b
+
+// One workgroup per transfer p (of few transfers: per p and 32 n_k, up to 1024
+// workgroups): U and V of a chunk of frequencies into LDS (sw
+// lanes, the power of two >= Nk, per n_b, over the momentum B), then the sums over
+// n_b, kS2Sl lanes for each of 32 n_k at a time. A box of more than kS2Chunk
+// frequencies forms its chunks again for every 32 n_k. Bound by its integer and
+// weight arithmetic (about 150 instructions per (n_k, n_b, p)), which a kernel with
+// one workgroup per k did for every momentum K of k before. With the sums over p
+// (sigma2_kernel), before -> now: 4x4, Nv = 16: 40 -> 24 us, 8x8, Nv = 8: 66 -> 57,
+// one momentum, Nv = 32: 16 -> 15; 16 lanes a sum 25, 60, 13 us, 32 lanes 36, 83, 13.
+__global__ __launch_bounds__(kThreads) void s2_sums_kernel(S2Args a, int sw) {
+  __shared__ double2 tab[5][kS2Chunk];
   const Dims& d = a.d;
-  const int wid = (blockIdx.x * kThreads + threadIdx.x) / sw, lane = threadIdx.x & (sw - 1);
-  if (wid >= d.NG * d.Nq) return;                 // uniform over the sw lanes
-  const int nbi = wid / d.Nq, qi = wid - (wid / d.Nq) * d.Nq;
-  const int hG = d.NG / 2, nb = nbi - hG;
+  const int qi = blockIdx.x, t = threadIdx.x;
   const int jm = qi / d.Nk, P = qi - jm * d.Nk, mp = jm - (d.Nv / 2 - 1);
-  const bool r1 = nb + mp >= -hG && nb + mp < hG, r3 = mp - nb - 1 >= -hG && mp - nb - 1 < hG;
-  const bool kb2 = in_fbox(nb, d.Nv) && a.level >= 2;
+  const int hF = d.Nve / 2, hBe = d.Nve / 2 - 1, hG = d.NG / 2;
   const size_t n = d.n;
-  double v[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  if (lane < d.Nk) {
-    const int B = lane;
-    const double2 gb = a.g[(size_t)(nb + hG) * d.Nk + B];
-    const double2 g1 = r1 ? a.g[(size_t)(nb + mp + hG) * d.Nk + kadd(B, P, d.Lx, d.Ly)] : mk(0, 0);
-    const double2 g3 = r3 ? a.g[(size_t)(mp - nb - 1 + hG) * d.Nk + ksub(P, B, d.Lx, d.Ly)] : mk(0, 0);
-    const double2 u1 = cmul(g1, gb), u3 = cmul(g3, gb);
-    double2 w1d = mk(0, 0), w1m = mk(0, 0), w3 = mk(0, 0);
-    if (kb2) {
-      const size_t bidx = (size_t)(nb + d.Nv / 2) * d.Nk + B;
-      w1d = cmul(u1, a.k2[((size_t)0 * d.Nq + qi) * n + bidx]);
-      w1m = cmul(u1, a.k2[((size_t)1 * d.Nq + qi) * n + bidx]);
-      w3 = cmul(u3, cadd(a.k2[((size_t)2 * d.Nq + qi) * n + bidx], a.k2[((size_t)3 * d.Nq + qi) * n + bidx]));
+  const int sl = t % kS2Sl;
+  constexpr int EK = kThreads / kS2Sl;
+  bool formed = false;
+  for (int ek0 = blockIdx.y * EK; ek0 < d.Nve; ek0 += gridDim.y * EK) {
+    const int ek = ek0 + t / kS2Sl, nk = ek - hF;
+    const bool kbox = in_fbox(nk, d.Nv);
+    const int nkp = nk + mp;
+    const bool Ye = nkp >= -hF && nkp <= hF - 1;
+    const bool Yb = in_fbox(nkp, d.Nv);
+    int lo = min(-hF, min(nk - hBe, -mp - nk - 1 - hBe));
+    int hi = max(hF - 1, max(nk + hBe, -mp - nk - 1 + hBe));
+    lo = max(lo, -hG);
+    hi = ek < d.Nve ? min(hi, hG - 1) : lo - 1;
+    double2 a16 = mk(0, 0), a25 = mk(0, 0), a34 = mk(0, 0), b1 = mk(0, 0), b3 = mk(0, 0);
+    for (int c0 = 0; c0 < d.NG; c0 += kS2Chunk) {
+      if (!formed || d.NG > kS2Chunk) {
+        formed = true;
+        __syncthreads();
+        const int lane = t & (sw - 1), cn = min(kS2Chunk, d.NG - c0);
+        for (int x = t / sw; x < cn; x += kThreads / sw) {        // uniform over the sw lanes
+          const int nb = c0 + x - hG;
+          const bool r1 = nb + mp >= -hG && nb + mp < hG, r3 = mp - nb - 1 >= -hG && mp - nb - 1 < hG;
+          const bool kb2 = in_fbox(nb, d.Nv) && a.level >= 2;
+          double v[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+          if (lane < d.Nk) {
+            const int B = lane;
+            const double2 gb = a.g[(size_t)(nb + hG) * d.Nk + B];
+            const double2 g1 = r1 ? a.g[(size_t)(nb + mp + hG) * d.Nk + kadd(B, P, d.Lx, d.Ly)] : mk(0, 0);
+            const double2 g3 = r3 ? a.g[(size_t)(mp - nb - 1 + hG) * d.Nk + ksub(P, B, d.Lx, d.Ly)] : mk(0, 0);
+            const double2 u1 = cmul(g1, gb), u3 = cmul(g3, gb);
+            double2 w1d = mk(0, 0), w1m = mk(0, 0), w3 = mk(0, 0);
+            if (kb2) {
+              const size_t bidx = (size_t)(nb + d.Nv / 2) * d.Nk + B;
+              w1d = cmul(u1, a.k2[((size_t)0 * d.Nq + qi) * n + bidx]);
+              w1m = cmul(u1, a.k2[((size_t)1 * d.Nq + qi) * n + bidx]);
+              w3 = cmul(u3, cadd(a.k2[((size_t)2 * d.Nq + qi) * n + bidx], a.k2[((size_t)3 * d.Nq + qi) * n + bidx]));
+            }
+            v[0] = u1.x; v[1] = u1.y; v[2] = u3.x; v[3] = u3.y;
+            v[4] = w1d.x; v[5] = w1d.y; v[6] = w1m.x; v[7] = w1m.y; v[8] = w3.x; v[9] = w3.y;
+          }
+          for (int o = sw >> 1; o > 0; o >>= 1) {
+#pragma unroll
+            for (int i = 0; i < 10; ++i) v[i] += __shfl_xor(v[i], o, 64);
+          }
+          if (lane == 0)
+            for (int i = 0; i < 5; ++i) tab[i][x] = mk(v[2 * i], v[2 * i + 1]);
+        }
+        __syncthreads();
+      }
+      const int last = min(hi, c0 + kS2Chunk - 1 - hG);
+      for (int nb = max(lo, c0 - hG) + sl; nb <= last; nb += kS2Sl) {
+        const bool bFe = nb >= -hF && nb <= hF - 1;
+        const bool bFb = in_fbox(nb, d.Nv);
+        const int x1 = mp + nk + nb + 1, x2 = nb - nk, x3 = mp - nk - nb - 1;
+        double e16 = bFe ? 1.0 + ind(x1 >= -hBe && x1 <= hBe) : 0.0;
+        double e25 = Ye ? ind(x2 >= -hBe && x2 <= hBe) + ind(x1 >= -hBe && x1 <= hBe) : 0.0;
+        double e34 = bFe ? 1.0 + ind(x3 >= -hBe && x3 <= hBe) : 0.0;
+        if (kbox && bFb) {
+          e16 -= 1.0 + ind(in_bbox(x1, d.Nv));
+          e25 -= Yb ? ind(in_bbox(x2, d.Nv)) + ind(in_bbox(x1, d.Nv)) : 0.0;
+          e34 -= 1.0 + ind(in_bbox(x3, d.Nv));
+        }
+        if (e16 == 0.0 && e25 == 0.0 && e34 == 0.0) continue;
+        const int x = nb + hG - c0;
+        const double2 u1 = tab[0][x], u3 = tab[1][x];
+        a16 = cadd(a16, cscale(u1, e16));
+        a25 = cadd(a25, cscale(u1, e25));
+        a34 = cadd(a34, cscale(u3, e34));
+        if (bFb && a.level >= 2) {
+          b1 = cadd(b1, csub(cscale(tab[2][x], e16), cscale(tab[3][x], e16 + 2.0 * e25)));
+          b3 = cadd(b3, cscale(tab[4][x], e34));
+        }
+      }
     }
-    v[0] = u1.x; v[1] = u1.y; v[2] = u3.x; v[3] = u3.y;
-    v[4] = w1d.x; v[5] = w1d.y; v[6] = w1m.x; v[7] = w1m.y; v[8] = w3.x; v[9] = w3.y;
+    double v[10] = {a16.x, a16.y, a25.x, a25.y, a34.x, a34.y, b1.x, b1.y, b3.x, b3.y};
+#pragma unroll
+    for (int o = kS2Sl / 2; o > 0; o >>= 1)
+#pragma unroll
+      for (int i = 0; i < 10; ++i) v[i] += __shfl_xor(v[i], o, 64);
+    if (sl == 0 && ek < d.Nve)
+      for (int i = 0; i < 5; ++i) a.tab[((size_t)ek * 5 + i) * d.Nq + qi] = mk(v[2 * i], v[2 * i + 1]);
   }
-  for (int i = 0; i < 10; ++i)
-    for (int o = sw >> 1; o > 0; o >>= 1) v[i] += __shfl_xor(v[i], o, 64);
-  if (lane == 0)
-    for (int i = 0; i < 5; ++i) a.tab[((size_t)nbi * 5 + i) * d.Nq + qi] = mk(v[2 * i], v[2 * i + 1]);
 }
 
 struct CombineArgs {
@@ -336,10 +407,8 @@ struct CombineArgs {
 
 // The sum of the pieces, one workgroup per k point of the extended box:
 // Sigma~_1 plus the Schwinger-Dyson constant times the kernel part (threads over
-// the transfers p, and over slices of the frequencies n_b where the transfers
-// alone leave threads idle: nqp is the power of two >= Nq, at most the
-// workgroup), the box part's sums over the bosonic index, and the box Lambda.
-__global__ __launch_bounds__(kThreads) void sigma2_kernel(S2Args a, CombineArgs c_, int nqp) {
+// the transfers p), the box part's sums over the bosonic index, and the box Lambda.
+__global__ __launch_bounds__(kThreads) void sigma2_kernel(S2Args a, CombineArgs c_) {
   __shared__ double red[kThreads];
   const Dims& d = a.d;
   const int kid = blockIdx.x;
@@ -347,11 +416,10 @@ __global__ __launch_bounds__(kThreads) void sigma2_kernel(S2Args a, CombineArgs 
   const int nk = ek - d.Nve / 2;
   const bool kbox = in_fbox(nk, d.Nv);
   const int kbi = kbox ? (nk + d.Nv / 2) * d.Nk + K : 0;
-  const int hF = d.Nve / 2, hBe = d.Nve / 2 - 1, hBb = d.Nv / 2 - 1, hG = d.NG / 2;
+  const int hBb = d.Nv / 2 - 1, hG = d.NG / 2;
   const size_t n = d.n, nq = d.Nq;
-  const int nsl = kThreads / nqp, sl = threadIdx.x / nqp;
   double tr = 0.0, ti = 0.0;
-  for (int qi = threadIdx.x % nqp; c_.has_s2 && qi < d.Nq; qi += nqp) {
+  for (int qi = threadIdx.x; c_.has_s2 && qi < d.Nq; qi += kThreads) {
     const int jm = qi / d.Nk, P = qi - jm * d.Nk;
     const int mp = jm - hBb;
     double2 c[4];
@@ -360,41 +428,11 @@ __global__ __launch_bounds__(kThreads) void sigma2_kernel(S2Args a, CombineArgs 
       if (kbox && a.level >= 2) c[r] = cadd(c[r], a.k2[((size_t)r * d.Nq + qi) * n + kbi]);
     }
     const int nkp = nk + mp;
-    const bool Ye = nkp >= -hF && nkp <= hF - 1;
-    const bool Yb = in_fbox(nkp, d.Nv);
     const double2 g_kp = a.g[(size_t)(nkp + hG) * d.Nk + kadd(K, P, d.Lx, d.Ly)];
     const double2 g_pk = a.g[(size_t)(mp - nk - 1 + hG) * d.Nk + ksub(P, K, d.Lx, d.Ly)];
-    int lo = min(-hF, min(nk - hBe, -mp - nk - 1 - hBe));
-    int hi = max(hF - 1, max(nk + hBe, -mp - nk - 1 + hBe));
-    lo = max(lo, -hG);
-    hi = min(hi, hG - 1);
-    double2 a16 = mk(0, 0), a25 = mk(0, 0), a34 = mk(0, 0), kd = mk(0, 0), km = mk(0, 0), kst = mk(0, 0);
-    for (int nb = lo + sl; nb <= hi; nb += nsl) {
-      const bool bFe = nb >= -hF && nb <= hF - 1;
-      const bool bFb = in_fbox(nb, d.Nv);
-      const int x1 = mp + nk + nb + 1, x2 = nb - nk, x3 = mp - nk - nb - 1;
-      double e16 = bFe ? 1.0 + ind(x1 >= -hBe && x1 <= hBe) : 0.0;
-      double e25 = Ye ? ind(x2 >= -hBe && x2 <= hBe) + ind(x1 >= -hBe && x1 <= hBe) : 0.0;
-      double e34 = bFe ? 1.0 + ind(x3 >= -hBe && x3 <= hBe) : 0.0;
-      if (kbox && bFb) {
-        e16 -= 1.0 + ind(in_bbox(x1, d.Nv));
-        e25 -= Yb ? ind(in_bbox(x2, d.Nv)) + ind(in_bbox(x1, d.Nv)) : 0.0;
-        e34 -= 1.0 + ind(in_bbox(x3, d.Nv));
-      }
-      if (e16 == 0.0 && e25 == 0.0 && e34 == 0.0) continue;
-      const double2* t = a.tab + (size_t)(nb + hG) * 5 * nq + qi;
-      const double2 u1 = t[0], u3 = t[nq];
-      a16 = cadd(a16, cscale(u1, e16));
-      a25 = cadd(a25, cscale(u1, e25));
-      a34 = cadd(a34, cscale(u3, e34));
-      if (bFb && a.level >= 2) {
-        kd = cadd(kd, cscale(t[2 * nq], e16));
-        km = cadd(km, cscale(t[3 * nq], e16 + 2.0 * e25));
-        kst = cadd(kst, cscale(t[4 * nq], e34));
-      }
-    }
-    const double2 s16 = cmul(g_kp, a16), s25 = cmul(g_kp, a25), s34 = cmul(g_pk, a34);
-    const double2 sk = cadd(cmul(g_kp, csub(kd, km)), cmul(g_pk, kst));
+    const double2* t = a.tab + (size_t)ek * 5 * nq + qi;
+    const double2 s16 = cmul(g_kp, t[0]), s25 = cmul(g_kp, t[nq]), s34 = cmul(g_pk, t[2 * nq]);
+    const double2 sk = cadd(cmul(g_kp, t[3 * nq]), cmul(g_pk, t[4 * nq]));
     double2 contrib = cmul(c[0], s16);
     contrib = csub(contrib, cmul(c[1], cadd(s16, cscale(s25, 2.0))));
     contrib = cadd(contrib, cmul(cadd(c[2], c[3]), s34));
@@ -787,7 +825,8 @@ hipError_t launch_sigma(const pq_params& p, const Dims& d, const void* phi, cons
   S2Args a2{d, p.kernel_level, g, k1, k2, (double2*)(ws + L.tab)};
   if (has_s2) {
     const int sw = pow2_ge(d.Nk);
-    hipLaunchKernelGGL(s2_tables_kernel, dim3(nblk((size_t)d.NG * d.Nq * sw)), dim3(kThreads), 0, s, a2, sw);
+    const int parts = std::max(1, std::min(1024 / d.Nq, (d.Nve * kS2Sl + kThreads - 1) / kThreads));
+    hipLaunchKernelGGL(s2_sums_kernel, dim3(d.Nq, parts), dim3(kThreads), 0, s, a2, sw);
   }
   if (p.storage == PQ_STORE_C64)
     launch_sigmab(SBArgs<float2>{d, (const float2*)phi, g, part}, s);
@@ -802,8 +841,7 @@ hipError_t launch_sigma(const pq_params& p, const Dims& d, const void* phi, cons
   }
   const double T = 1.0 / p.beta;
   CombineArgs ac{d, -p.U * T * T / (4.0 * d.Nk * (double)d.Nk), has_s2, s1, part, lpart, sigma_out};
-  const int nqp = pow2_ge(d.Nq) < kThreads ? pow2_ge(d.Nq) : kThreads;
-  hipLaunchKernelGGL(sigma2_kernel, dim3(d.Nve * d.Nk), dim3(kThreads), 0, s, a2, ac, nqp);
+  hipLaunchKernelGGL(sigma2_kernel, dim3(d.Nve * d.Nk), dim3(kThreads), 0, s, a2, ac);
   return hipGetLastError();
 }
 

@@ -46,3 +46,10 @@ def test_sigma_sde_sizes(prec, lx, ly, nv, f, level, beta):
     torch.cuda.synchronize()
     err = np.max(np.abs(out.cpu().numpy() - ref)) / np.max(np.abs(ref))
     assert err < 1e-11, err
+
+
+@pytest.mark.parametrize("lx,ly,nv,f,level", [(1, 1, 8, 16, 2), (2, 1, 10, 16, 2), (3, 1, 10, 14, 1)])
+def test_kernel_part_chunks(lx, ly, nv, f, level):
+    """One and two chunks of 256 frequencies of the kernel part's inner sum."""
+    print("CASE sigma chunks", lx, ly, nv, f, level, flush=True)
+    test_sigma_sde_sizes("fp64", lx, ly, nv, f, level, 2.0)
