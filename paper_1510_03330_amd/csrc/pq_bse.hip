@@ -2627,8 +2627,11 @@ static hipError_t run_bse(const Dims& d, const Chans& ch, double alpha, float we
 namespace {
 // Counts over the block stats of one iteration (one workgroup, fixed-order sums).
 // nchunks runs of nb stats, stride apart
-__global__ __launch_bounds__(kThreads) void bse_summary_kernel(const pq_bse_block_stats* st, int nb, int nchunks,
-                                                               size_t stride, double* out) {
+template <int N>
+__global__ __launch_bounds__(kThreads) void bse_summary_kernel(Many<SummaryIn, N> ms, int nb, int nchunks,
+                                                               size_t stride) {
+  const pq_bse_block_stats* st = ms.a[N == 1 ? 0 : blockIdx.z].stats;
+  double* out = ms.a[N == 1 ? 0 : blockIdx.z].out;
   __shared__ double red[kThreads];
   double f = 0.0, r = 0.0, u = 0.0, m = 0.0;
   for (int t = threadIdx.x; t < nb * nchunks; t += blockDim.x) {
@@ -2653,10 +2656,18 @@ __global__ __launch_bounds__(kThreads) void bse_summary_kernel(const pq_bse_bloc
 }
 }  // namespace
 
+hipError_t launch_bse_summary_many(const SummaryIn* x, int count, int nb, int nchunks, size_t stride, hipStream_t s) {
+  launch_groups<SummaryIn>(count, [&](int i) { return x[i]; }, [&](const auto& m, int, int n) {
+    hipLaunchKernelGGL((bse_summary_kernel<sizeof(m.a) / sizeof(m.a[0])>), dim3(1, 1, n), dim3(kThreads), 0, s, m, nb,
+                       nchunks, stride);
+  });
+  return hipGetLastError();
+}
+
 hipError_t launch_bse_summary(const pq_bse_block_stats* stats, int nb, double* out, hipStream_t s, int nchunks,
                               size_t stride) {
-  hipLaunchKernelGGL(bse_summary_kernel, dim3(1), dim3(kThreads), 0, s, stats, nb, nchunks, stride, out);
-  return hipGetLastError();
+  const SummaryIn x{stats, out};
+  return launch_bse_summary_many(&x, 1, nb, nchunks, stride, s);
 }
 
 static hipError_t dispatch_bse(const pq_params& p, const Dims& d, const Chans& ch, int precision, const void* gamma,

@@ -31,6 +31,53 @@ inline size_t elem_bytes(const pq_params& p) {
   return p.storage == PQ_STORE_C64 ? sizeof(float2) : sizeof(double2);
 }
 
+// One launch over several instances of a box: their arguments side by side in the
+// kernel's own (kMany at a time, 4 KB at most), the instance in blockIdx.z.
+constexpr int kMany = 8;
+template <typename A, int N> struct Many { A a[N]; };
+template <typename A, typename G, typename F>
+inline void launch_groups(int count, G&& args, F&& launch) {   // args(i): instance i's; launch(Many, first, instances)
+  for (int i = 0; i < count; i += kMany) {
+    const int n = count - i < kMany ? count - i : kMany;
+    if (n == 1) {
+      launch(Many<A, 1>{{args(i)}}, i, 1);
+      continue;
+    }
+    Many<A, kMany> m;
+    for (int k = 0; k < kMany; ++k) m.a[k] = args(i + (k < n ? k : 0));
+    launch(m, i, n);
+  }
+}
+
+// An instance's part of the launches over several (one box: sizes alike, parameters
+// of each)
+struct StageIn {
+  const pq_params* p;
+  const Dims* d;
+  const double2* sigma;
+  double2* g;
+  double* mu;
+  double2 *xph, *xpp;
+  const void* phi;
+  const double2 *k1, *k2;
+  double2* sigma_new;
+  void* sig_ws;          // scratch of its own (sigma_ws_bytes)
+};
+struct MixIn {
+  const double2* snew;
+  double2* sio;
+  double *dnorm, *smax, *host;
+};
+struct SummaryIn {
+  const pq_bse_block_stats* stats;
+  double* out;
+};
+hipError_t launch_dyson_many(const StageIn* x, int count, hipStream_t s);
+hipError_t launch_bubbles_many(const StageIn* x, int count, hipStream_t s);
+hipError_t launch_sigma_many(const StageIn* x, int count, hipStream_t s);
+hipError_t launch_bse_summary_many(const SummaryIn* x, int count, int nb, int nchunks, size_t stride, hipStream_t s);
+hipError_t launch_mix_many(const Dims& d, const MixIn* x, int count, double alpha, hipStream_t s);
+
 // ---- launchers (enqueue only) ----
 hipError_t launch_dyson(const pq_params& p, const Dims& d, const double2* sigma, double2* g,
                         double* mu_out, hipStream_t s);

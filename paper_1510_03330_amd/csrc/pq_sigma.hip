@@ -106,7 +106,10 @@ struct S1Args {
 // their own did before with one thread per output and a sincos per term (4x4,
 // Nv = 16: 19 + 9 us; one momentum, Nv = 32: 67 + 84 us for the pole sums).
 // Latency-bound: a few hundred operations per thread, N / 2 workgroups.
-__global__ __launch_bounds__(kThreads) void s1_tau_kernel(S1Args a) {
+template <int N>
+__global__ __launch_bounds__(kThreads) void s1_tau_kernel(Many<S1Args, N> m) {
+  const S1Args& a = m.a[N == 1 ? 0 : blockIdx.z];
+  if ((int)blockIdx.x >= (a.d.ntau + 1) / 2) return;     // an instance of fewer nodes than the launch's most
   __shared__ double2 ph[kThreads];
   __shared__ double2 red[2][kThreads];
   __shared__ double2 gk[2][kMaxNk];
@@ -220,7 +223,9 @@ __global__ __launch_bounds__(kThreads) void s1_tau_kernel(S1Args a) {
 // workgroup per frequency e, a slice of the nodes per thread (the sums over the
 // nodes ran serially in one thread per output before: 103-200 us).
 constexpr int kRowThreads = 1024;
-__global__ __launch_bounds__(kRowThreads) void s1_row_kernel(S1Args a) {
+template <int N>
+__global__ __launch_bounds__(kRowThreads) void s1_row_kernel(Many<S1Args, N> m) {
+  const S1Args& a = m.a[N == 1 ? 0 : blockIdx.z];
   __shared__ double2 ph[kRowThreads];
   __shared__ double2 red[kRowThreads];
   __shared__ double2 tx[kMaxNk], ty[kMaxNk];
@@ -304,7 +309,9 @@ constexpr int kS2Sl = 8;         // lanes that share a sum over n_b
 // one workgroup per k did for every momentum K of k before. With the sums over p
 // (sigma2_kernel), before -> now: 4x4, Nv = 16: 40 -> 24 us, 8x8, Nv = 8: 66 -> 57,
 // one momentum, Nv = 32: 16 -> 15; 16 lanes a sum 25, 60, 13 us, 32 lanes 36, 83, 13.
-__global__ __launch_bounds__(kThreads) void s2_sums_kernel(S2Args a, int sw) {
+template <int N>
+__global__ __launch_bounds__(kThreads) void s2_sums_kernel(Many<S2Args, N> m, int sw) {
+  const S2Args& a = m.a[N == 1 ? 0 : blockIdx.z];
   __shared__ double2 tab[5][kS2Chunk];
   const Dims& d = a.d;
   const int qi = blockIdx.x, t = threadIdx.x;
@@ -408,7 +415,10 @@ struct CombineArgs {
 // The sum of the pieces, one workgroup per k point of the extended box:
 // Sigma~_1 plus the Schwinger-Dyson constant times the kernel part (threads over
 // the transfers p), the box part's sums over the bosonic index, and the box Lambda.
-__global__ __launch_bounds__(kThreads) void sigma2_kernel(S2Args a, CombineArgs c_) {
+template <int N>
+__global__ __launch_bounds__(kThreads) void sigma2_kernel(Many<S2Args, N> m2, Many<CombineArgs, N> mc) {
+  const S2Args& a = m2.a[N == 1 ? 0 : blockIdx.z];
+  const CombineArgs& c_ = mc.a[N == 1 ? 0 : blockIdx.z];
   __shared__ double red[kThreads];
   const Dims& d = a.d;
   const int kid = blockIdx.x;
@@ -750,12 +760,19 @@ WsLayout ws_layout(const Dims& d) {
 
 inline unsigned nblk(size_t total) { return (unsigned)((total + kThreads - 1) / kThreads); }
 
-hipError_t run_sigma1(const pq_params& p, const Dims& d, const double2* g, const double* mu,
-                      double2* out, char* ws, hipStream_t s) {
-  WsLayout L = ws_layout(d);
-  S1Args a{d, p.beta, p.U, p.t, p.tp, p.D, d.Nk == 1 ? 1 : 0, g, mu, (double2*)(ws + L.srt), out};
-  hipLaunchKernelGGL(s1_tau_kernel, dim3((d.ntau + 1) / 2), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(s1_row_kernel, dim3(d.Nve), dim3(kRowThreads), 0, s, a);
+S1Args s1_args(const pq_params& p, const Dims& d, const double2* g, const double* mu, double2* out, char* ws) {
+  return S1Args{d, p.beta, p.U, p.t, p.tp, p.D, d.Nk == 1 ? 1 : 0, g, mu, (double2*)(ws + ws_layout(d).srt), out};
+}
+
+template <typename G>
+hipError_t run_sigma1(G&& args, int count, hipStream_t s) {
+  launch_groups<S1Args>(count, args, [&](const auto& m, int, int n) {
+    constexpr int N = sizeof(m.a) / sizeof(m.a[0]);
+    int nt = 0;
+    for (int i = 0; i < n; ++i) nt = std::max(nt, m.a[i].d.ntau);
+    hipLaunchKernelGGL(s1_tau_kernel<N>, dim3((nt + 1) / 2, 1, n), dim3(kThreads), 0, s, m);
+    hipLaunchKernelGGL(s1_row_kernel<N>, dim3(m.a[0].d.Nve, 1, n), dim3(kRowThreads), 0, s, m);
+  });
   return hipGetLastError();
 }
 
@@ -797,7 +814,9 @@ hipError_t static_scratch(void** out) {
 // without the regulation, truncated to the box.
 static hipError_t run_second_order(const pq_params& p, const Dims& d, const double2* g, const double* mu,
                                    double2* out, char* ws, hipStream_t s) {
-  if (p.regulation != 0) return run_sigma1(p, d, g, mu, out, ws, s);
+  if (p.regulation != 0) {
+    return run_sigma1([&](int) { return s1_args(p, d, g, mu, out, ws); }, 1, s);
+  }
   const WsLayout L = ws_layout(d);
   const double T = 1.0 / p.beta;
   S2BoxArgs a{d, -p.U * p.U * T * T / (2.0 * d.Nk * (double)d.Nk), g, (double2*)(ws + L.sq), out};
@@ -812,6 +831,80 @@ hipError_t launch_sigma1(const pq_params& p, const Dims& d, const double2* g, co
   return run_second_order(p, d, g, mu, sigma_out, (char*)ws, s);
 }
 
+namespace {
+
+CombineArgs combine_args(const pq_params& p, const Dims& d, const double2* s1, const double2* part,
+                         const double2* lpart, double2* sigma_out) {
+  const double T = 1.0 / p.beta;
+  return CombineArgs{d, -p.U * T * T / (4.0 * d.Nk * (double)d.Nk), p.kernel_level > 0 ? 1 : 0, s1, part, lpart,
+                     sigma_out};
+}
+
+template <typename G>
+void run_s2_sums(const Dims& d, G&& args, int count, hipStream_t s) {
+  const int parts = std::max(1, std::min(1024 / (d.Nq * count), (d.Nve * kS2Sl + kThreads - 1) / kThreads));
+  launch_groups<S2Args>(count, args, [&](const auto& m, int, int n) {
+    hipLaunchKernelGGL((s2_sums_kernel<sizeof(m.a) / sizeof(m.a[0])>), dim3(d.Nq, parts, n), dim3(kThreads), 0, s, m,
+                       pow2_ge(d.Nk));
+  });
+}
+
+template <typename G2, typename GC>
+void run_sigma2(const Dims& d, G2&& args, GC&& combine, int count, hipStream_t s) {
+  launch_groups<S2Args>(count, args, [&](const auto& m, int first, int n) {
+    constexpr int N = sizeof(m.a) / sizeof(m.a[0]);
+    static_assert(sizeof(Many<S2Args, N>) + sizeof(Many<CombineArgs, N>) <= 4096, "arguments of a launch");
+    Many<CombineArgs, N> mc;
+    for (int i = 0; i < N; ++i) mc.a[i] = combine(first + (i < n ? i : 0));
+    hipLaunchKernelGGL(sigma2_kernel<N>, dim3(d.Nve * d.Nk, 1, n), dim3(kThreads), 0, s, m, mc);
+  });
+}
+
+}  // namespace
+
+// The stage of several instances of a box: a launch of each kernel over them, but
+// for the box part, whose one instance fills the chip. Without the regulation (the
+// second-order term in the box) one after another.
+hipError_t launch_sigma_many(const StageIn* x, int count, hipStream_t s) {
+  bool each = count == 1;
+  for (int i = 0; i < count; ++i) each = each || x[i].p->regulation == 0;
+  if (each) {
+    for (int i = 0; i < count; ++i) {
+      const hipError_t e = launch_sigma(*x[i].p, *x[i].d, x[i].phi, x[i].k1, x[i].k2, nullptr, x[i].g, x[i].mu,
+                                        x[i].sigma_new, x[i].sig_ws, s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  const Dims& d = *x[0].d;
+  auto ws = [&](int i, size_t WsLayout::*part) {
+    return (double2*)((char*)x[i].sig_ws + ws_layout(*x[i].d).*part);
+  };
+  auto a2 = [&](int i) {
+    return S2Args{*x[i].d, x[i].p->kernel_level, x[i].g, x[i].k1, x[i].k2, ws(i, &WsLayout::tab)};
+  };
+  const hipError_t e = run_sigma1(
+      [&](int i) { return s1_args(*x[i].p, *x[i].d, x[i].g, x[i].mu, ws(i, &WsLayout::s1), (char*)x[i].sig_ws); }, count,
+      s);
+  if (e != hipSuccess) return e;
+  bool has_s2 = false;
+  for (int i = 0; i < count; ++i) has_s2 = has_s2 || x[i].p->kernel_level > 0;
+  if (has_s2) run_s2_sums(d, a2, count, s);          // an instance without kernels does not read its own
+  for (int i = 0; i < count; ++i) {
+    if (x[i].p->storage == PQ_STORE_C64)
+      launch_sigmab(SBArgs<float2>{*x[i].d, (const float2*)x[i].phi, x[i].g, ws(i, &WsLayout::part)}, s);
+    else
+      launch_sigmab(SBArgs<double2>{*x[i].d, (const double2*)x[i].phi, x[i].g, ws(i, &WsLayout::part)}, s);
+  }
+  run_sigma2(
+      d, a2,
+      [&](int i) {
+        return combine_args(*x[i].p, *x[i].d, ws(i, &WsLayout::s1), ws(i, &WsLayout::part), nullptr, x[i].sigma_new);
+      },
+      count, s);
+  return hipGetLastError();
+}
+
 hipError_t launch_sigma(const pq_params& p, const Dims& d, const void* phi, const double2* k1,
                         const double2* k2, const double2* lam_box, const double2* g, const double* mu,
                         double2* sigma_out, void* wsv, hipStream_t s) {
@@ -821,13 +914,8 @@ hipError_t launch_sigma(const pq_params& p, const Dims& d, const void* phi, cons
   double2* part = (double2*)(ws + L.part);
   hipError_t e = run_second_order(p, d, g, mu, s1, ws, s);
   if (e != hipSuccess) return e;
-  const int has_s2 = p.kernel_level > 0 ? 1 : 0;
-  S2Args a2{d, p.kernel_level, g, k1, k2, (double2*)(ws + L.tab)};
-  if (has_s2) {
-    const int sw = pow2_ge(d.Nk);
-    const int parts = std::max(1, std::min(1024 / d.Nq, (d.Nve * kS2Sl + kThreads - 1) / kThreads));
-    hipLaunchKernelGGL(s2_sums_kernel, dim3(d.Nq, parts), dim3(kThreads), 0, s, a2, sw);
-  }
+  auto a2 = [&](int) { return S2Args{d, p.kernel_level, g, k1, k2, (double2*)(ws + L.tab)}; };
+  if (p.kernel_level > 0) run_s2_sums(d, a2, 1, s);
   if (p.storage == PQ_STORE_C64)
     launch_sigmab(SBArgs<float2>{d, (const float2*)phi, g, part}, s);
   else
@@ -839,9 +927,7 @@ hipError_t launch_sigma(const pq_params& p, const Dims& d, const void* phi, cons
     hipLaunchKernelGGL(lam_tables_kernel, dim3(nblk((size_t)d.Nv * d.NW * d.Nk)), dim3(kThreads), 0, s, al);
     hipLaunchKernelGGL(lam_sigma_kernel, dim3(d.n), dim3(kThreads), 0, s, al);
   }
-  const double T = 1.0 / p.beta;
-  CombineArgs ac{d, -p.U * T * T / (4.0 * d.Nk * (double)d.Nk), has_s2, s1, part, lpart, sigma_out};
-  hipLaunchKernelGGL(sigma2_kernel, dim3(d.Nve * d.Nk), dim3(kThreads), 0, s, a2, ac);
+  run_sigma2(d, a2, [&](int) { return combine_args(p, d, s1, part, lpart, sigma_out); }, 1, s);
   return hipGetLastError();
 }
 

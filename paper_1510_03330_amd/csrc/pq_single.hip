@@ -97,8 +97,9 @@ __device__ inline double density_term(const DElem& v, double mu) {
 // step): 213 us at 4x4, Nv = 8, 490 us at 8x8, Nv = 16; now 26 and 45 us.
 constexpr int dyson_threads(int lv, int lp) { return (((1 << lv) - 1) * lp + 63) / 64 * 64; }
 
-template <int LV, int LP, int RE>
-__global__ __launch_bounds__(dyson_threads(LV, LP)) void dyson_kernel(DysonArgs a) {
+template <int LV, int LP, int RE, int N>
+__global__ __launch_bounds__(dyson_threads(LV, LP)) void dyson_kernel(Many<DysonArgs, N> m) {
+  const DysonArgs& a = m.a[N == 1 ? 0 : blockIdx.z];
   constexpr int NC = (1 << LV) - 1;                  // points per pass
   constexpr int LG = LP < 64 ? LP : 64;              // lanes of one partial sum
   constexpr int W = LP / LG;                         // partial sums per point
@@ -184,7 +185,9 @@ struct BubbleArgs {
   double2* xpp;
 };
 
-__global__ __launch_bounds__(kThreads) void bubble_kernel(BubbleArgs a) {
+template <int N>
+__global__ __launch_bounds__(kThreads) void bubble_kernel(Many<BubbleArgs, N> ms) {
+  const BubbleArgs& a = ms.a[N == 1 ? 0 : blockIdx.z];
   const Dims& d = a.d;
   size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (size_t)d.Nq * d.n) return;
@@ -201,8 +204,12 @@ __global__ __launch_bounds__(kThreads) void bubble_kernel(BubbleArgs a) {
   a.xpp[idx] = cscale(cmul(gk, gqk), a.T / (2.0 * d.Nk));
 }
 
-__global__ __launch_bounds__(kThreads) void mix_kernel(int count, const double2* snew, double2* sio,
-                                                       double alpha, double* dnorm, double* smax, double* host) {
+template <int N>
+__global__ __launch_bounds__(kThreads) void mix_kernel(int count, Many<MixIn, N> m, double alpha) {
+  const MixIn& x = m.a[N == 1 ? 0 : blockIdx.z];
+  const double2* snew = x.snew;
+  double2* sio = x.sio;
+  double *dnorm = x.dnorm, *smax = x.smax, *host = x.host;
   __shared__ double red[kThreads];
   double mx = 0.0, bad = 0.0, sm = 0.0;
   for (int i = threadIdx.x; i < count; i += blockDim.x) {
@@ -287,18 +294,26 @@ hipError_t launch_convert(const void* src, int src_storage, void* dst, int dst_s
   return hipGetLastError();
 }
 
-hipError_t launch_dyson(const pq_params& p, const Dims& d, const double2* sigma, double2* g,
-                        double* mu_out, hipStream_t s) {
+static_assert(sizeof(Many<DysonArgs, kMany>) <= 4096, "arguments of a launch");
+
+hipError_t launch_dyson_many(const StageIn* x, int count, hipStream_t s) {
+  const Dims& d = *x[0].d;
   if (d.Nk > kMaxNk) return hipErrorInvalidValue;
-  DysonArgs a{d, p.beta, p.t, p.tp, p.D, p.filling, p.mu_fixed, p.U, p.mu_mode, d.Nk == 1 ? 1 : 0,
-              sigma, g, mu_out};
+  auto args = [&](int i) {
+    const pq_params& p = *x[i].p;
+    return DysonArgs{*x[i].d, p.beta, p.t, p.tp, p.D, p.filling, p.mu_fixed, p.U, p.mu_mode, d.Nk == 1 ? 1 : 0,
+                     x[i].sigma, x[i].g, x[i].mu};
+  };
   // points per pass and lanes per point by the number of self-energy values, the
   // shape whose pass costs least per bisection step (256 values: 16 lanes
   // per point 26 us, a wave per point 33; 1024: 3 steps on 128 lanes per point 48,
   // 2 on 256 lanes 35; 2048: 2 on 256 lanes 58, 1 on 1024 lanes 50, on 512 45)
   const int values = d.Nve * d.Nk;
-#define PQ_DYSON(LV, LP, RE) \
-  hipLaunchKernelGGL((dyson_kernel<LV, LP, RE>), dim3(1), dim3(dyson_threads(LV, LP)), 0, s, a)
+#define PQ_DYSON(LV, LP, RE)                                                                                      \
+  launch_groups<DysonArgs>(count, args, [&](const auto& m, int, int n) {                                          \
+    hipLaunchKernelGGL((dyson_kernel<LV, LP, RE, sizeof(m.a) / sizeof(m.a[0])>), dim3(1, 1, n),                   \
+                       dim3(dyson_threads(LV, LP)), 0, s, m);                                                     \
+  })
   if (values <= 16 * 8) PQ_DYSON(4, 16, 8);
   else if (values <= 16 * 16) PQ_DYSON(4, 16, 16);
   else if (values <= 128 * 4) PQ_DYSON(2, 128, 4);
@@ -310,19 +325,50 @@ hipError_t launch_dyson(const pq_params& p, const Dims& d, const double2* sigma,
   return hipGetLastError();
 }
 
+hipError_t launch_dyson(const pq_params& p, const Dims& d, const double2* sigma, double2* g,
+                        double* mu_out, hipStream_t s) {
+  StageIn x{};
+  x.p = &p;
+  x.d = &d;
+  x.sigma = sigma;
+  x.g = g;
+  x.mu = mu_out;
+  return launch_dyson_many(&x, 1, s);
+}
+
+hipError_t launch_bubbles_many(const StageIn* x, int count, hipStream_t s) {
+  auto args = [&](int i) { return BubbleArgs{*x[i].d, 1.0 / x[i].p->beta, x[i].g, x[i].xph, x[i].xpp}; };
+  const size_t total = (size_t)x[0].d->Nq * x[0].d->n;
+  const unsigned blocks = (unsigned)((total + kThreads - 1) / kThreads);
+  launch_groups<BubbleArgs>(count, args, [&](const auto& m, int, int n) {
+    hipLaunchKernelGGL((bubble_kernel<sizeof(m.a) / sizeof(m.a[0])>), dim3(blocks, 1, n), dim3(kThreads), 0, s, m);
+  });
+  return hipGetLastError();
+}
+
 hipError_t launch_bubbles(const pq_params& p, const Dims& d, const double2* g, double2* xph,
                           double2* xpp, hipStream_t s) {
-  BubbleArgs a{d, 1.0 / p.beta, g, xph, xpp};
-  size_t total = (size_t)d.Nq * d.n;
-  unsigned blocks = (unsigned)((total + kThreads - 1) / kThreads);
-  hipLaunchKernelGGL(bubble_kernel, dim3(blocks), dim3(kThreads), 0, s, a);
+  StageIn x{};
+  x.p = &p;
+  x.d = &d;
+  x.g = const_cast<double2*>(g);
+  x.xph = xph;
+  x.xpp = xpp;
+  return launch_bubbles_many(&x, 1, s);
+}
+
+hipError_t launch_mix_many(const Dims& d, const MixIn* x, int count, double alpha, hipStream_t s) {
+  launch_groups<MixIn>(count, [&](int i) { return x[i]; }, [&](const auto& m, int, int n) {
+    hipLaunchKernelGGL((mix_kernel<sizeof(m.a) / sizeof(m.a[0])>), dim3(1, 1, n), dim3(kThreads), 0, s, d.Nve * d.Nk, m,
+                       alpha);
+  });
   return hipGetLastError();
 }
 
 hipError_t launch_mix(const Dims& d, const double2* snew, double2* sio, double alpha,
                       double* dnorm, hipStream_t s, double* smax, double* host) {
-  hipLaunchKernelGGL(mix_kernel, dim3(1), dim3(kThreads), 0, s, d.Nve * d.Nk, snew, sio, alpha, dnorm, smax, host);
-  return hipGetLastError();
+  const MixIn x{snew, sio, dnorm, smax, host};
+  return launch_mix_many(d, &x, 1, alpha, s);
 }
 
 }  // namespace pq
