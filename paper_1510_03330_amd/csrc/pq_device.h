@@ -109,30 +109,38 @@ __device__ inline double group_total(double v) {
   return v;
 }
 
-// Deterministic block reduction of doubles (fixed tree). blockDim.x must be a
-// power of two <= 1024; `red` is LDS of blockDim.x doubles.
+template <int CTRL, int ROWS>
+__device__ inline double dpp_max(double v) {         // lanes without a source keep their own
+  const int l = __double2loint(v), h = __double2hiint(v);
+  return fmax(v, __hiloint2double(__builtin_amdgcn_update_dpp(h, h, CTRL, ROWS, 0xf, false),
+                                  __builtin_amdgcn_update_dpp(l, l, CTRL, ROWS, 0xf, false)));
+}
+
+// Deterministic block reductions of doubles: in the wave's registers, then one
+// exchange (a tree in LDS, with a barrier per level, took about 1 us a call in
+// kernels of 5 to 15 us that make two to five of them). blockDim.x must be a
+// multiple of 64, at most 1024; `red` is LDS of blockDim.x / 64 doubles or more.
 __device__ inline double block_sum(double v, double* red) {
-  const int t = threadIdx.x;
-  red[t] = v;
+  v = group_total<64>(v);
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int s = blockDim.x >> 1; s > 0; s >>= 1) {
-    if (t < s) red[t] += red[t + s];
-    __syncthreads();
-  }
   double r = red[0];
+  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) r += red[w];
   __syncthreads();
   return r;
 }
 
 __device__ inline double block_max(double v, double* red) {
-  const int t = threadIdx.x;
-  red[t] = v;
+  v = dpp_max<0x111, 0xf>(v);
+  v = dpp_max<0x112, 0xf>(v);
+  v = dpp_max<0x114, 0xf>(v);
+  v = dpp_max<0x118, 0xf>(v);
+  v = dpp_max<0x142, 0xa>(v);
+  v = dpp_max<0x143, 0xc>(v);
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int s = blockDim.x >> 1; s > 0; s >>= 1) {
-    if (t < s) red[t] = fmax(red[t], red[t + s]);
-    __syncthreads();
-  }
   double r = red[0];
+  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) r = fmax(r, red[w]);
   __syncthreads();
   return r;
 }
