@@ -6,9 +6,10 @@
 // [4][K][Nq][n][n] (Dims::cs = K Nq n^2 between channels), with the bubbles
 // [K][Nq][n], so the Bethe-Salpeter blocks of every active instance in one
 // channel are contiguous and one BSE launch sequence (Eq. PA_F_Phi) covers all
-// (instance, q) blocks. The per-instance stages (Dyson, bubbles, kernel
-// functions, channel remap, Schwinger-Dyson; then the mixing) are launched
-// instance after instance around it. One round (one iteration of every active
+// (instance, q) blocks. Of the stages around it, those too small for the chip
+// (Dyson, bubbles, Schwinger-Dyson sums, mixing) are launched over the instances,
+// the others (kernel functions, remap, the box part) instance after instance.
+// One round (one iteration of every active
 // instance) is captured on one stream into a single HIP graph, replayed until
 // the set of active instances changes. An instance that converges, diverges or fails
 // is retired: the last active instance's vertex moves into its arena slot, so
