@@ -45,6 +45,7 @@ struct BInst {
 struct BatchLayout {
   size_t phi, gamma, xph, xpp, bstats, bse, sig, dn, inst, inst_stride, total;
   size_t bse_bytes, sig_bytes;
+  bool four;                                  // room for the BSE of the four channels in one launch sequence
   size_t sigma, sigma_new, g, k1, k2, mu;     // offsets inside one instance's region
 };
 
@@ -72,7 +73,9 @@ bool batch_dims(const pq_params* ps, int K, std::vector<Dims>* dims) {
   return true;
 }
 
-BatchLayout batch_layout(const pq_params* ps, const std::vector<Dims>& dims) {
+// four: room for the four channels in one BSE launch sequence (small boxes; a batch
+// of one keeps one channel's, the size by which callers choose their batches)
+BatchLayout batch_layout(const pq_params* ps, const std::vector<Dims>& dims, bool four) {
   const int K = (int)dims.size();
   const Dims& d = dims[0];
   const pq_params& p = ps[0];
@@ -87,7 +90,9 @@ BatchLayout batch_layout(const pq_params* ps, const std::vector<Dims>& dims) {
   L.bstats = take(sizeof(pq_bse_block_stats) * 4 * (size_t)K * d.Nq);
   Dims dk = d;
   dk.Nq = K * d.Nq;
-  L.bse_bytes = bse_ws_bytes(p, dk, p.precision);
+  L.bse_bytes = four && K > 1 ? bse_four_ws_bytes(p, dk) : 0;
+  L.four = L.bse_bytes > 0;
+  if (!L.four) L.bse_bytes = bse_ws_bytes(p, dk, p.precision);
   L.bse = take(L.bse_bytes);
   size_t sb = 0;
   for (int i = 0; i < K; ++i) sb = std::max(sb, sigma_ws_bytes(dims[i]));
@@ -192,7 +197,10 @@ hipError_t enqueue_pre(pq_batch* b, int nactive, const char** where) {
   return hipSuccess;
 }
 
-// the BSE of every active block of the four channels, on the main stream
+// The BSE of every active block, on the main stream: the four channels in one
+// launch sequence where the workspace holds them (four rounds of eight instances,
+// complex128, against a sequence each: 4x4, Nv = 8: 15.0 and 16.2 ms, 2x2 1.48 and
+// 1.79).
 hipError_t enqueue_bse(pq_batch* b, int nactive, const char** where) {
   const Dims& d = b->d0;
   Dims r = d;
@@ -200,6 +208,13 @@ hipError_t enqueue_bse(pq_batch* b, int nactive, const char** where) {
   const size_t chan = elem_bytes(b->p0) * (size_t)d.cs;
   pq_params p = b->p0;
   p.bse_tile = b->tile;
+  if (b->L.four) {
+    hipError_t e = launch_bse_four(p, r, b->ws + b->L.gamma, (const double2*)(b->ws + b->L.xph),
+                                   (const double2*)(b->ws + b->L.xpp), b->ws + b->L.phi, p.alpha,
+                                   (pq_bse_block_stats*)(b->ws + b->L.bstats), b->ws + b->L.bse, b->s);
+    if (e != hipSuccess) *where = "bse";
+    return e;
+  }
   for (int c = 0; c < 4; ++c) {
     const double2* x = (const double2*)(b->ws + (c < 2 ? b->L.xph : b->L.xpp));
     hipError_t e = launch_bse(p, r, c, p.precision, b->ws + b->L.gamma + c * chan, x, b->ws + b->L.phi + c * chan,
@@ -221,7 +236,8 @@ hipError_t enqueue_post(pq_batch* b, int nactive, const char** where) {
     sum[slot] = SummaryIn{(pq_bse_block_stats*)(b->ws + b->L.bstats) + (size_t)slot * d.Nq, dn + 1};
     mix[slot] = MixIn{x.sigma_new, x.sigma, dn, dn + 5, nullptr};
   }
-  hipError_t e = launch_bse_summary_many(sum.data(), nactive, d.Nq, 4, (size_t)b->K * d.Nq, b->s);
+  const size_t chan = (size_t)(b->L.four ? nactive : b->K) * d.Nq;      // between the channels' block stats
+  hipError_t e = launch_bse_summary_many(sum.data(), nactive, d.Nq, 4, chan, b->s);
   if (e != hipSuccess) { *where = "bse summary"; return e; }
   if ((e = launch_mix_many(d, mix.data(), nactive, b->p0.alpha, b->s)) != hipSuccess) { *where = "mix"; return e; }
   return hipSuccess;
@@ -342,7 +358,7 @@ pq_status parquet_batch_query_workspace(const pq_params* ps, int32_t count, size
   std::vector<Dims> dims;
   if (!batch_dims(ps, count, &dims)) return PQ_ERR_ARG;
   PQB_CHECK_ARG(bytes, "null output");
-  *bytes = batch_layout(ps, dims).total;
+  *bytes = std::max(batch_layout(ps, dims, true).total, batch_layout(ps, dims, false).total);
   return PQ_OK;
 }
 
@@ -352,7 +368,8 @@ pq_status parquet_batch_init(const pq_params* ps, int32_t count, void* ws, size_
   if (!batch_dims(ps, count, &dims)) return PQ_ERR_ARG;
   PQB_CHECK_ARG(ws && out, "null pointer");
   PQB_CHECK_ARG(stream != nullptr, "the batch needs a created stream (its rounds are captured into graphs)");
-  const BatchLayout L = batch_layout(ps, dims);
+  BatchLayout L = batch_layout(ps, dims, true);
+  if (ws_bytes < L.total) L = batch_layout(ps, dims, false);
   if (ws_bytes < L.total) {
     set_error("batch workspace %zu < %zu bytes", ws_bytes, L.total);
     return PQ_ERR_NOMEM;

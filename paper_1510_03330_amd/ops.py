@@ -328,7 +328,10 @@ class Batch:
     block, one HIP graph per round; autotune times the two complex64 update tiles
     on the batch's own block count at set-up."""
 
-    def __init__(self, params, precision: str = "fp32", device: str = "cuda:0", autotune: bool = True):
+    def __init__(self, params, precision: str = "fp32", device: str = "cuda:0", autotune: bool = True,
+                 max_bytes: int = 0):
+        """max_bytes: a bound on the workspace of several instances (0: none), where
+        one channel's part of the Bethe-Salpeter scratch fits it."""
         self.params = list(params)
         self.precision = precision
         self.device = torch.device(device)
@@ -338,16 +341,39 @@ class Batch:
         lib = N.load()
         b = ctypes.c_size_t()
         N.check(lib.parquet_batch_query_workspace(self._pp, K, ctypes.byref(b)))
-        self.ws = torch.empty(int(b.value), dtype=torch.uint8, device=self.device)
+        need = int(b.value)
+        sizes = [need * part // 16 for part in range(16, 3, -1)]      # on a device short of memory, as Solver does
+        if K > 1 and 0 < max_bytes < need:
+            sizes.insert(0, int(max_bytes))
+        oom = None
+        for size in sizes:
+            try:
+                self._bind(size, autotune)
+                break
+            except torch.OutOfMemoryError as err:
+                oom = err
+            except N.ParquetError as err:
+                if err.status != N.PQ_ERR_NOMEM or size == need:
+                    raise
+                if oom is not None:
+                    raise oom
+        else:
+            raise oom
+        self.stage = Stage(self.params[0], precision)
+
+    def _bind(self, nbytes: int, autotune: bool):
+        self.ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         torch.cuda.synchronize(self.device)
         self.stream = new_stream(str(self.device))           # pooled: created once, reused
         self.ws.record_stream(self.stream)
         h = ctypes.c_void_p()
-        N.check(lib.parquet_batch_init(self._pp, K, ctypes.c_void_p(self.ws.data_ptr()), ctypes.c_size_t(b.value),
-                                       ctypes.c_void_p(self.stream.cuda_stream), int(bool(autotune)),
-                                       ctypes.byref(h)))
+        status = N.load().parquet_batch_init(self._pp, self.K, ctypes.c_void_p(self.ws.data_ptr()),
+                                             ctypes.c_size_t(nbytes), ctypes.c_void_p(self.stream.cuda_stream),
+                                             int(bool(autotune)), ctypes.byref(h))
+        if status != N.PQ_OK:
+            release_stream(self.stream)
+        N.check(status)
         self.h = h
-        self.stage = Stage(self.params[0], precision)
 
     @staticmethod
     def workspace_bytes(params, precision: str = "fp32") -> int:
@@ -422,7 +448,7 @@ def run_batched(params, precision: str = "fp32", device: str = "cuda:0", tol: fl
             chunk = idx[c0:c0 + cap]
             torch.cuda.synchronize()
             t0 = time.perf_counter()
-            b = Batch([params[i] for i in chunk], precision, device, autotune)
+            b = Batch([params[i] for i in chunk], precision, device, autotune, max_bytes=int(mem_budget))
             t1 = time.perf_counter()
             rounds = 0
             while rounds < max_iter:

@@ -43,6 +43,26 @@ def test_rounds(prec, K, box):
     b.close()
 
 
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("K,box", [(2, (2, 2, 6)), (5, (3, 1, 4)), (3, (2, 1, 34))])
+def test_four_channels(prec, K, box):
+    """The four channels in one launch sequence against one by one (a workspace one
+    byte short), before and after an instance retires."""
+    print("CASE batch four channels", prec, K, box, flush=True)
+    from paper_1510_03330_amd.ops import Batch
+    ps = [instance(i, *box) for i in range(K)]
+    a = Batch(ps, prec, autotune=False)
+    b = Batch(ps, prec, autotune=False, max_bytes=a.ws.numel() - 1)
+    for diverge in (0.0, 0.0, 1e-3, 0.0):                    # the third round retires what still moves
+        left = a.iterate(1, tol=0.0, diverge=diverge)
+        assert b.iterate(1, tol=0.0, diverge=diverge) == left
+    for i in range(K):
+        assert a.status()[i][:2] == b.status()[i][:2]
+        assert rel(a.get(i, "sigma"), b.get(i, "sigma")) < {**TOL, "bf16x3": 2e-3}[prec]
+    a.close()
+    b.close()
+
+
 @pytest.mark.parametrize("threads", [1, pytest.param(2, marks=pytest.mark.skip(
     reason="two batches at once from two threads ended in a host segmentation fault when a round's graph had "
            "several branches (its cause was not found, the branches are gone); not run again since"))])
@@ -73,3 +93,25 @@ def test_retire(threads):
             s = Solver(p, "fp64")
             s.iterate(it)
             assert rel(sg, s.get("sigma").cpu()) < 1e-10
+
+
+@pytest.mark.parametrize("share,ok", [(0.8, True), (0.2, False)])
+def test_device_short_of_memory(monkeypatch, share, ok):
+    print("CASE batch short of memory", share, flush=True)
+    from paper_1510_03330_amd.ops import Batch
+    ps = [instance(i, 2, 2, 16) for i in range(3)]
+    real, room = torch.empty, int(share * Batch.workspace_bytes(ps, "fp64"))
+
+    def empty(size, *args, **kw):
+        if kw.get("dtype") is torch.uint8 and size > room:
+            raise torch.OutOfMemoryError("no room")
+        return real(size, *args, **kw)
+
+    monkeypatch.setattr(torch, "empty", empty)
+    if not ok:
+        with pytest.raises(torch.OutOfMemoryError):
+            Batch(ps, "fp64")
+        return
+    b = Batch(ps, "fp64")
+    assert b.ws.numel() <= room and b.iterate(1, tol=0.0) == 3
+    b.close()
