@@ -288,13 +288,15 @@ def new_stream(device: str = "cuda:0"):
     allocator record an event on that stream when the tensor is freed, which
     may happen after the context is gone. release_stream returns one for reuse."""
     global _hip
-    pool = _stream_pool.setdefault(str(device), [])
-    if pool:
-        return pool.pop()
+    try:
+        return _stream_pool.setdefault(str(device), []).pop()    # one step: another thread may take the last one
+    except IndexError:
+        pass
     if _hip is None:
-        _hip = ctypes.CDLL("libamdhip64.so")
-        _hip.hipStreamCreate.argtypes = [ctypes.POINTER(ctypes.c_void_p)]
-        _hip.hipStreamCreate.restype = ctypes.c_int
+        hip = ctypes.CDLL("libamdhip64.so")
+        hip.hipStreamCreate.argtypes = [ctypes.POINTER(ctypes.c_void_p)]
+        hip.hipStreamCreate.restype = ctypes.c_int
+        _hip = hip
     with torch.cuda.device(device):
         h = ctypes.c_void_p()
         if _hip.hipStreamCreate(ctypes.byref(h)) != 0:
