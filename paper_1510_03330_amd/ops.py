@@ -373,9 +373,16 @@ class Batch:
                                              ctypes.c_size_t(nbytes), ctypes.c_void_p(self.stream.cuda_stream),
                                              int(bool(autotune)), ctypes.byref(h))
         if status != N.PQ_OK:
-            release_stream(self.stream)
+            self._give_back()
         N.check(status)
         self.h = h
+
+    def _give_back(self):
+        """The workspace, then its stream: freeing a tensor recorded on a stream
+        records an event there, which must not meet the next user's capture."""
+        self.ws = None
+        stream, self.stream = self.stream, None
+        release_stream(stream)
 
     @staticmethod
     def workspace_bytes(params, precision: str = "fp32") -> int:
@@ -419,7 +426,7 @@ class Batch:
         if getattr(self, "h", None) is not None:
             N.load().parquet_batch_destroy(self.h)
             self.h = None
-            release_stream(self.stream)
+            self._give_back()
 
     def __del__(self):
         try:
@@ -551,6 +558,7 @@ class BatchRunner:
                 st = new_stream(self.device)
                 s = Solver(self.params[i], self.precision, self.device, stream=st)
                 active.append([i, s, time.perf_counter(), 0, nb, st])
+                del s                                       # (its workspace goes with its entry, before its stream)
                 used += nb
             done, conv = iterate_batch([a[1] for a in active], chunk, tol)
             keep = []
