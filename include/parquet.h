@@ -508,7 +508,11 @@ pq_status parquet_destroy(pq_ctx* ctx);
  * (pq_batch_state) and the last change of Sigma (arrays of count; each
  * pointer may be null). parquet_batch_get copies one instance's field
  * (PQ_FIELD_SIGMA, G, MU, K1, K2; PHI only while the instance is active) to
- * device memory; bytes must equal the field size. */
+ * device memory; bytes must equal the field size.
+ * Several threads may each drive batches (and contexts) of their own; one batch is
+ * not for two threads at the same time. The capture and launch of rounds, here and
+ * in parquet_iterate_batch, is one thread's at a time in a process; waiting for
+ * them and their work on the device are not held up. */
 typedef struct pq_batch pq_batch;
 typedef enum {
   PQ_BATCH_RUNNING = 0,

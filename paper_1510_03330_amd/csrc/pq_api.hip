@@ -30,6 +30,11 @@ pq_status hip_fail(hipError_t e, const char* what) {
   return PQ_ERR_HIP;
 }
 
+std::mutex& graph_mutex() {
+  static std::mutex* m = new std::mutex();    // never destroyed: contexts may outlive static objects
+  return *m;
+}
+
 double max_abs_eps(const pq_params& p, const Dims& d) {
   if (d.Nk == 1) return 0.0;
   double mx = 0.0;
@@ -775,6 +780,7 @@ pq_status parquet_iterate_batch(pq_ctx* const* ctxs, int32_t count, int32_t n_it
   }
   for (int i = 0; i < count; ++i) {
     pq_ctx* c = ctxs[i];
+    std::lock_guard<std::mutex> lock(graph_mutex());
     if (c->have_graph && c->graph_has_lam != c->has_lam) {
       (void)hipGraphExecDestroy(c->graph);
       c->have_graph = false;
@@ -808,6 +814,7 @@ pq_status parquet_iterate_batch(pq_ctx* const* ctxs, int32_t count, int32_t n_it
       if (!active[i]) continue;
       any = true;
       ctxs[i]->pending = true;
+      std::lock_guard<std::mutex> lock(graph_mutex());
       hipError_t e = hipGraphLaunch(ctxs[i]->graph, ctxs[i]->s);
       if (e != hipSuccess) return hip_fail(e, "graph launch");
     }
@@ -940,7 +947,10 @@ pq_status parquet_destroy(pq_ctx* c) {
     (void)hipEventDestroy(c->la.done);
     (void)hipStreamDestroy(c->la.side);
   }
-  if (c->have_graph) (void)hipGraphExecDestroy(c->graph);
+  if (c->have_graph) {
+    std::lock_guard<std::mutex> lock(graph_mutex());
+    (void)hipGraphExecDestroy(c->graph);
+  }
   if (c->have_events)
     for (int i = 0; i < 8; ++i) (void)hipEventDestroy(c->ev[i]);
   if (c->have_bev)

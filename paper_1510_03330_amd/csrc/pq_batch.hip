@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -245,10 +246,6 @@ hipError_t enqueue_post(pq_batch* b, int nactive, const char** where) {
 
 // one round of the active instances, captured into b->graph
 hipError_t capture_round(pq_batch* b, const char** where) {
-  if (b->have_graph) {
-    (void)hipGraphExecDestroy(b->graph);
-    b->have_graph = false;
-  }
   const int A = b->active;
   hipError_t e = hipStreamBeginCapture(b->s, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) { *where = "capture begin"; return e; }
@@ -267,6 +264,24 @@ hipError_t capture_round(pq_batch* b, const char** where) {
   if (e != hipSuccess) { *where = "graph instantiate"; return e; }
   b->have_graph = true;
   return hipSuccess;
+}
+
+void drop_graph(pq_batch* b) {
+  if (!b->have_graph) return;
+  std::lock_guard<std::mutex> lock(graph_mutex());
+  (void)hipGraphExecDestroy(b->graph);
+  b->have_graph = false;
+}
+
+// a replay of the round, captured first if the active instances changed
+hipError_t launch_round(pq_batch* b, const char** where) {
+  std::lock_guard<std::mutex> lock(graph_mutex());
+  if (!b->have_graph) {
+    const hipError_t e = capture_round(b, where);
+    if (e != hipSuccess) return e;
+  }
+  *where = "batch round";
+  return hipGraphLaunch(b->graph, b->s);
 }
 
 // retire the instances of the given slots (any order): the last active
@@ -428,8 +443,7 @@ pq_status parquet_batch_iterate(pq_batch* b, int32_t n_iter, double tol, double 
   for (int it = 0; it < n_iter && b->active > 0; ++it) {
     const char* where = nullptr;
     hipError_t e = hipSuccess;
-    if (!b->have_graph && (e = capture_round(b, &where)) != hipSuccess) return hip_fail(e, where);
-    if ((e = hipGraphLaunch(b->graph, b->s)) != hipSuccess) return hip_fail(e, "batch round");
+    if ((e = launch_round(b, &where)) != hipSuccess) return hip_fail(e, where);
     if ((e = hipMemcpyAsync(b->dn_host, b->ws + b->L.dn, sizeof(double) * kDn * b->K, hipMemcpyDeviceToHost,
                             b->s)) != hipSuccess)
       return hip_fail(e, "batch norms");
@@ -453,10 +467,7 @@ pq_status parquet_batch_iterate(pq_batch* b, int32_t n_iter, double tol, double 
     }
     if (!done.empty()) {
       if ((e = retire(b, done)) != hipSuccess) return hip_fail(e, "batch retire");
-      if (b->have_graph) {
-        (void)hipGraphExecDestroy(b->graph);
-        b->have_graph = false;
-      }
+      drop_graph(b);
     }
   }
   if (active_left) *active_left = b->active;
@@ -523,7 +534,7 @@ pq_status parquet_batch_tile(pq_batch* b, int32_t* tile, float* ms) {
 pq_status parquet_batch_destroy(pq_batch* b) {
   if (!b) return PQ_OK;
   (void)hipStreamSynchronize(b->s);
-  if (b->have_graph) (void)hipGraphExecDestroy(b->graph);
+  drop_graph(b);
   if (b->dn_host) (void)hipHostFree(b->dn_host);
   delete b;
   return PQ_OK;

@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <mutex>
+
 #include "parquet.h"
 #include "pq_device.h"
 
@@ -10,6 +12,12 @@ namespace pq {
 // thread-local error message
 void set_error(const char* fmt, ...);
 pq_status hip_fail(hipError_t e, const char* what);
+
+// Held while a graph is captured, instantiated, launched or destroyed (never while
+// the device is waited for), so that one thread at a time is in the runtime's graph
+// calls: two threads there at once, each with a batch of its own, ended in a host
+// segmentation fault whose cause was not found (the graphs had four branches then).
+std::mutex& graph_mutex();
 
 // Validates params and fills the device size struct (sets the error on failure).
 bool make_dims(const pq_params* p, Dims* d);

@@ -1,0 +1,87 @@
+"""The library's host code without a device, over the calls of fake_hip.c: what
+it launches and when, from a process of its own."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+HEAD = """
+import ctypes, sys, threading
+sys.path.insert(0, sys.argv[2])
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+from ctypes import byref, c_int32, c_size_t, c_void_p
+from paper_1510_03330_amd import native as N
+from workloads import ModelParams
+lib = N.load()
+
+def setting(name):
+    return ctypes.c_int.in_dll(fake, name)
+
+def room(nbytes):                           # host memory in place of a workspace
+    return ctypes.create_string_buffer(int(nbytes) + 256)
+"""
+
+
+@pytest.fixture(scope="module")
+def fake_hip(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-pthread", os.path.join(HERE, "fake_hip.c"), "-o", so], check=True)
+    return so
+
+
+def run(so, body):
+    res = subprocess.run([sys.executable, "-c", HEAD + textwrap.dedent(body), so, ROOT], capture_output=True, text=True,
+                         timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_one_thread_at_a_time_in_graph_calls(fake_hip):
+    """Two batches and two sets of contexts, each with a thread of its own: no graph
+    call of one meets one of another, and every round is launched."""
+    run(fake_hip, """
+        setting("fake_graph_us").value = 3000
+        p = ModelParams(Lx=2, Ly=1, Nv=4, U=1.0, beta=2.0, mu_mode=0, alpha=0.6)
+        start = threading.Barrier(4)
+        bad = []
+
+        def batch(t):
+            pp = (N.PqParams * 2)(*[N.make_params(p, "fp64")] * 2)
+            need, h, left = c_size_t(), c_void_p(), c_int32()
+            N.check(lib.parquet_batch_query_workspace(pp, 2, byref(need)))
+            ws = room(need.value)
+            N.check(lib.parquet_batch_init(pp, 2, ws, need, c_void_p(16 + t), 0, byref(h)))
+            start.wait()
+            for _ in range(5):
+                bad.append(lib.parquet_batch_iterate(h, 2, 0.0, 0.0, byref(left)) or left.value != 2)
+            N.check(lib.parquet_batch_destroy(h))
+
+        def contexts(t):
+            pp = N.make_params(p, "fp64")
+            need, done = c_size_t(), (c_int32 * 2)()
+            N.check(lib.parquet_query_workspace(byref(pp), byref(need)))
+            ws, cs = [room(need.value) for _ in range(2)], (c_void_p * 2)()
+            for i in range(2):
+                c = c_void_p()
+                N.check(lib.parquet_init(byref(pp), ws[i], need, c_void_p(32 + 2 * t + i), byref(c)))
+                cs[i] = c.value
+            start.wait()
+            for _ in range(5):
+                bad.append(lib.parquet_iterate_batch(cs, 2, 2, 0.0, done, None) or list(done) != [2, 2])
+            for c in cs:
+                N.check(lib.parquet_destroy(c))
+
+        th = [threading.Thread(target=f, args=(t,)) for t in range(2) for f in (batch, contexts)]
+        for t in th:
+            t.start()
+        for t in th:
+            t.join()
+        assert len(bad) == 20 and not any(bad), bad
+        # a capture, an instantiation and two destructions per graph, and the rounds
+        assert setting("fake_graph_calls").value == 4 * (2 + 4) + 2 * 10 + 4 * 10
+        assert setting("fake_overlaps").value == 0, setting("fake_overlaps").value
+    """)
