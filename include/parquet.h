@@ -395,9 +395,10 @@ typedef struct {
 
 /* Device bytes for parquet_init's workspace. For small boxes this includes room
  * for the four channels' Bethe-Salpeter equations in shared launches (at most
- * 8 GiB); parquet_init also takes a workspace with room for one channel's and then
- * solves them one by one. */
+ * 8 GiB). parquet_query_workspace_min: the least that parquet_init takes, with room
+ * for one channel's; the channels are then solved one by one. */
 pq_status parquet_query_workspace(const pq_params* p, size_t* bytes);
+pq_status parquet_query_workspace_min(const pq_params* p, size_t* bytes);
 
 /* Bind a context to caller workspace and stream, and set the bare-vertex start:
  * Phi_r = 0, Sigma_0 = Sigma~_1[G_0] (second-order diagram of the Sigma = 0 G;

@@ -597,6 +597,14 @@ pq_status parquet_query_workspace(const pq_params* p, size_t* bytes) {
   return PQ_OK;
 }
 
+pq_status parquet_query_workspace_min(const pq_params* p, size_t* bytes) {
+  Dims d;
+  if (!make_dims(p, &d)) return PQ_ERR_ARG;
+  PQ_CHECK_ARG(bytes, "null output");
+  *bytes = ctx_layout(*p, d, false).total;
+  return PQ_OK;
+}
+
 pq_status parquet_init(const pq_params* p, void* ws, size_t ws_bytes, pq_stream stream, pq_ctx** out) {
   Dims d;
   if (!make_dims(p, &d)) return PQ_ERR_ARG;

@@ -37,7 +37,7 @@ EXPORTS = [
     "mlp_basis_workspace", "mlp_basis", "mlp_expand", "parquet_warm_start",
     "parquet_batch_query_workspace", "parquet_batch_init", "parquet_batch_iterate", "parquet_batch_status",
     "parquet_batch_get", "parquet_batch_tile", "parquet_batch_destroy", "hbm_stream",
-    "sigma_sde_no_alloc",
+    "sigma_sde_no_alloc", "parquet_query_workspace_min",
 ]
 
 
@@ -113,6 +113,7 @@ def load() -> ctypes.CDLL:
                       c_void_p, c_size_t, c_void_p],
         "sigma_mix": [P, c_void_p, c_void_p, c_double, c_void_p, c_void_p],
         "parquet_query_workspace": [P, POINTER(c_size_t)],
+        "parquet_query_workspace_min": [P, POINTER(c_size_t)],
         "parquet_init": [P, c_void_p, c_size_t, c_void_p, POINTER(c_void_p)],
         "parquet_iterate": [c_void_p, c_int32, c_double, POINTER(PqIterStats), POINTER(c_int32),
                             POINTER(c_int32)],

@@ -141,30 +141,35 @@ class Stage:
                                    _ptr(dnorm, torch.float64, (1,), "dnorm"), _stream(stream)))
 
 
+def _workspace(query: str, pp) -> int:
+    b = ctypes.c_size_t()
+    N.check(getattr(N.load(), query)(ctypes.byref(pp), ctypes.byref(b)))
+    return int(b.value)
+
+
 def workspace_bytes(p, precision: str = "fp64", resolve_slots: int = 0, bse_tol: float = 0.0) -> int:
     """Device workspace a context of these parameters needs (parquet_query_workspace)."""
-    st = Stage(p, precision, resolve_slots, bse_tol)
-    b = ctypes.c_size_t()
-    N.check(N.load().parquet_query_workspace(st._pp(), ctypes.byref(b)))
-    return int(b.value)
+    return _workspace("parquet_query_workspace", Stage(p, precision, resolve_slots, bse_tol).pp)
 
 
 class Solver:
     """A parquet context on one device: workspace owned by a torch uint8 tensor
-    (at least ws_bytes, so that reinit can take parameters of a larger need)."""
+    (at least ws_bytes, so that reinit can take parameters of a larger need).
+    compact: the least workspace, in which the channels of a small box are solved
+    one by one instead of in shared launches."""
 
     def __init__(self, p, precision: str = "fp64", device: str = "cuda:0", stream=None, resolve_slots: int = 0,
-                 bse_tol: float = 0.0, ws_bytes: int = 0, bse_tile: int = 0):
+                 bse_tol: float = 0.0, ws_bytes: int = 0, bse_tile: int = 0, compact: bool = False):
         self.stage = Stage(p, precision, resolve_slots, bse_tol, bse_tile)
         self._stage_args = (precision, resolve_slots, bse_tol, bse_tile)
         self.device = torch.device(device)
         self.stream = stream
-        lib = N.load()
         b = ctypes.c_size_t()
-        N.check(lib.parquet_query_workspace(self.stage._pp(), ctypes.byref(b)))
+        N.check(N.load().parquet_query_workspace(self.stage._pp(), ctypes.byref(b)))
+        need = _workspace("parquet_query_workspace_min", self.stage.pp) if compact else int(b.value)
         self.ctx = None
         try:
-            self._bind(max(int(b.value), int(ws_bytes)))
+            self._bind(max(need, int(ws_bytes)))
         except torch.OutOfMemoryError:
             # The channels of a small box share their launches where their room is
             # there; on a device short of memory one channel's, which is at least a
@@ -490,7 +495,9 @@ class BatchRunner:
     Instances run concurrently, each in its own context and stream with its
     iteration captured in a graph (parquet_iterate_batch); at most `width` at a
     time and within `mem_budget` bytes of workspace, new instances starting as
-    others finish. `autotune` picks the width from `widths` by timing a few
+    others finish. Contexts are compact (Solver) where the full workspaces of any
+    `width` of the instances would not fit the budget together, so that the budget
+    admits as many as their least workspaces allow. `autotune` picks the width from `widths` by timing a few
     batched iterations of copies of the median instance (instance-iterations
     per second) before the run."""
 
@@ -504,10 +511,13 @@ class BatchRunner:
         self.width = None
         self.tuning = {}
 
-    def _bytes(self, p):
-        b = ctypes.c_size_t()
-        N.check(N.load().parquet_query_workspace(ctypes.byref(N.make_params(p, self.precision)), ctypes.byref(b)))
-        return int(b.value)
+    def _bytes(self, p, compact=True):
+        query = "parquet_query_workspace_min" if compact else "parquet_query_workspace"
+        return _workspace(query, N.make_params(p, self.precision))
+
+    def _compact(self, width):
+        full = sorted((self._bytes(p, False) for p in self.params), reverse=True)
+        return sum(full[:width]) > self.mem_budget
 
     def autotune(self, probe_iters: int = 3):
         import time
@@ -519,7 +529,8 @@ class BatchRunner:
             if w > len(self.params) or w * nb > self.mem_budget:
                 break
             streams = [new_stream(self.device) for _ in range(w)]
-            solvers = [Solver(p_med, self.precision, self.device, stream=st) for st in streams]
+            compact = self._compact(w)
+            solvers = [Solver(p_med, self.precision, self.device, stream=st, compact=compact) for st in streams]
             iterate_batch(solvers, 1)                       # graph capture + first replay
             torch.cuda.synchronize()
             t0 = time.perf_counter()
@@ -543,6 +554,7 @@ class BatchRunner:
         its start to its end (wall, shared with the instances beside it)."""
         import time
         width = self.width or self.autotune()
+        compact = self._compact(width)
         pending = list(range(len(self.params)))
         active = []                 # (index, solver, start time, iterations)
         out = [None] * len(self.params)
@@ -551,12 +563,12 @@ class BatchRunner:
         while pending or active:
             while pending and len(active) < width:
                 i = pending[0]
-                nb = self._bytes(self.params[i])
+                nb = self._bytes(self.params[i], compact)
                 if active and used + nb > self.mem_budget:
                     break
                 pending.pop(0)
                 st = new_stream(self.device)
-                s = Solver(self.params[i], self.precision, self.device, stream=st)
+                s = Solver(self.params[i], self.precision, self.device, stream=st, compact=compact)
                 active.append([i, s, time.perf_counter(), 0, nb, st])
                 del s                                       # (its workspace goes with its entry, before its stream)
                 used += nb

@@ -1,0 +1,69 @@
+"""Workspace sizes and what the callers make of them, on the CPU (the queries are
+host code; allocations and contexts are stand-ins)."""
+import types
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1510_03330_amd import native as N
+from paper_1510_03330_amd import ops
+from workloads import ModelParams
+
+
+def box(lx=2, ly=2, nv=16, **kw):
+    return ModelParams(Lx=lx, Ly=ly, Nv=nv, U=1.3, beta=2.5, mu_mode=0, alpha=0.6, **kw)
+
+
+def full(p, prec):
+    return ops._workspace("parquet_query_workspace", N.make_params(p, prec))
+
+
+def least(p, prec):
+    return ops._workspace("parquet_query_workspace_min", N.make_params(p, prec))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+def test_least_workspace(prec):
+    """Below the preferred one for a small box, the same where the channels go one by one."""
+    assert least(box(), prec) < 0.7 * full(box(), prec)
+    assert least(box(8, 8, 16), prec) == full(box(8, 8, 16), prec)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("budget,width", [(4.5, 4), (2.2, 2), (1e6, 4)])
+def test_runner_admits_what_least_workspaces_allow(monkeypatch, prec, budget, width):
+    """budget: in least workspaces of the largest instance; at most four run at a time."""
+    ps = [box(nv=16 if i % 2 else 14) for i in range(8)]
+    budget = budget * least(ps[1], prec)
+    live, most, compacts = [], [], set()
+
+    class Context:
+        def __init__(self, p, precision, device, stream=None, compact=False):
+            self.bytes = least(p, precision) if compact else full(p, precision)
+            compacts.add(compact)
+            live.append(self.bytes)
+            assert sum(live) <= budget
+
+        def get(self, name):
+            return torch.zeros(1, dtype=torch.complex128)
+
+        def close(self):
+            live.remove(self.bytes)
+
+    def iterate(solvers, n, tol=0.0):
+        most.append(len(solvers))
+        return [n] * len(solvers), [True] * len(solvers)
+
+    monkeypatch.setattr(ops, "Solver", Context)
+    monkeypatch.setattr(ops, "iterate_batch", iterate)
+    monkeypatch.setattr(ops, "new_stream", lambda d: types.SimpleNamespace())
+    monkeypatch.setattr(ops, "release_stream", lambda s: None)
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda d=None: None)
+    r = ops.BatchRunner(ps, prec, mem_budget=budget, widths=(1, 2, 4))
+    r.autotune()
+    assert sorted(r.tuning) == [w for w in (1, 2, 4) if w <= width]
+    r.width, most[:] = 4, []
+    out, _ = r.run()
+    assert max(most) >= width and all(o["converged"] for o in out)
+    assert (True in compacts) == (4 * full(ps[1], prec) > budget)
