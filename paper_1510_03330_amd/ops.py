@@ -164,25 +164,16 @@ class Solver:
         self._stage_args = (precision, resolve_slots, bse_tol, bse_tile)
         self.device = torch.device(device)
         self.stream = stream
-        b = ctypes.c_size_t()
-        N.check(N.load().parquet_query_workspace(self.stage._pp(), ctypes.byref(b)))
-        need = _workspace("parquet_query_workspace_min", self.stage.pp) if compact else int(b.value)
+        full = _workspace("parquet_query_workspace", self.stage.pp)
+        least = _workspace("parquet_query_workspace_min", self.stage.pp)
+        sizes = [max(size, int(ws_bytes)) for size in ([least] if compact else [full, least])]
         self.ctx = None
         try:
-            self._bind(max(need, int(ws_bytes)))
-        except torch.OutOfMemoryError:
-            # The channels of a small box share their launches where their room is
-            # there; on a device short of memory one channel's, which is at least a
-            # quarter of the whole, is enough (parquet_init turns down less).
-            for part in range(15, 3, -1):
-                try:
-                    self._bind(max(int(b.value) * part // 16, int(ws_bytes)))
-                    return
-                except torch.OutOfMemoryError:
-                    continue
-                except N.ParquetError:
-                    break
-            raise
+            self._bind(sizes[0])
+        except torch.OutOfMemoryError:                 # a device short of memory may hold one channel's part
+            if sizes[-1] == sizes[0]:
+                raise
+            self._bind(sizes[-1])
 
     def _bind(self, nbytes: int):
         self.ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)

@@ -67,3 +67,38 @@ def test_runner_admits_what_least_workspaces_allow(monkeypatch, prec, budget, wi
     out, _ = r.run()
     assert max(most) >= width and all(o["converged"] for o in out)
     assert (True in compacts) == (4 * full(ps[1], prec) > budget)
+
+
+class Device:
+    """torch.empty over `room` bytes."""
+
+    def __init__(self, room):
+        self.room, self.sizes = room, []
+
+    def empty(self, size, dtype, device):
+        if size > self.room:
+            raise torch.OutOfMemoryError("no room")
+        self.sizes.append(size)
+        return types.SimpleNamespace(numel=lambda: size, record_stream=lambda s: None)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("p", [box(), box(3, 2, 4), box(8, 8, 16)])
+def test_context_on_a_device_short_of_memory(monkeypatch, prec, p):
+    """Accepted down to the least workspace, to the byte; the full one where it fits."""
+    hi, lo = full(p, prec), least(p, prec)
+    monkeypatch.setattr(ops.Solver, "reinit", lambda self, p=None: None)
+    for room, size in ((hi, hi), (hi - 1, lo), (lo, lo), (lo - 1, None)):
+        dev = Device(room)
+        monkeypatch.setattr(torch, "empty", dev.empty)
+        if size is None or size > room:
+            with pytest.raises(torch.OutOfMemoryError):
+                ops.Solver(p, prec)
+        else:
+            ops.Solver(p, prec)
+            assert dev.sizes == [size]
+    dev = Device(2 * hi)
+    monkeypatch.setattr(torch, "empty", dev.empty)
+    ops.Solver(p, prec, ws_bytes=2 * hi)
+    ops.Solver(p, prec, compact=True)
+    assert dev.sizes == [2 * hi, lo]
