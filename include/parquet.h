@@ -500,7 +500,9 @@ pq_status parquet_destroy(pq_ctx* ctx);
  * (pq_params.bse_tile) of the batch's BSE on its own block count and keeps the
  * faster (parquet_batch_tile reports the choice and the times, ms per launch
  * sequence of one channel). ws: parquet_batch_query_workspace bytes, owned by
- * the caller. stream: a created stream (not the null stream; the rounds are
+ * the caller; for small boxes they include room for the four channels' BSE in
+ * shared launches, and parquet_batch_query_workspace_min tells the least that is
+ * taken, with room for one channel's. stream: a created stream (not the null stream; the rounds are
  * captured into graphs on it) that the batch uses until it is destroyed;
  * every call is synchronous.
  * parquet_batch_iterate runs up to n_iter rounds, stopping early when no
@@ -523,6 +525,7 @@ typedef enum {
   PQ_BATCH_SINGULAR = 4    /* a BSE block unresolved                         */
 } pq_batch_state;
 pq_status parquet_batch_query_workspace(const pq_params* ps, int32_t count, size_t* bytes);
+pq_status parquet_batch_query_workspace_min(const pq_params* ps, int32_t count, size_t* bytes);
 pq_status parquet_batch_init(const pq_params* ps, int32_t count, void* ws, size_t ws_bytes, pq_stream stream,
                              int32_t autotune, pq_batch** out);
 pq_status parquet_batch_iterate(pq_batch* b, int32_t n_iter, double tol, double diverge, int32_t* active_left);

@@ -377,6 +377,14 @@ pq_status parquet_batch_query_workspace(const pq_params* ps, int32_t count, size
   return PQ_OK;
 }
 
+pq_status parquet_batch_query_workspace_min(const pq_params* ps, int32_t count, size_t* bytes) {
+  std::vector<Dims> dims;
+  if (!batch_dims(ps, count, &dims)) return PQ_ERR_ARG;
+  PQB_CHECK_ARG(bytes, "null output");
+  *bytes = batch_layout(ps, dims, false).total;
+  return PQ_OK;
+}
+
 pq_status parquet_batch_init(const pq_params* ps, int32_t count, void* ws, size_t ws_bytes, pq_stream stream,
                              int32_t autotune, pq_batch** out) {
   std::vector<Dims> dims;

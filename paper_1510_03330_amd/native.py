@@ -38,6 +38,7 @@ EXPORTS = [
     "parquet_batch_query_workspace", "parquet_batch_init", "parquet_batch_iterate", "parquet_batch_status",
     "parquet_batch_get", "parquet_batch_tile", "parquet_batch_destroy", "hbm_stream",
     "sigma_sde_no_alloc", "parquet_query_workspace_min",
+    "parquet_batch_query_workspace_min",
 ]
 
 
@@ -137,6 +138,7 @@ def load() -> ctypes.CDLL:
         "mlp_expand": [c_void_p, c_int32, c_size_t, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p],
         "parquet_destroy": [c_void_p],
         "parquet_batch_query_workspace": [P, c_int32, POINTER(c_size_t)],
+        "parquet_batch_query_workspace_min": [P, c_int32, POINTER(c_size_t)],
         "parquet_batch_init": [P, c_int32, c_void_p, c_size_t, c_void_p, c_int32, POINTER(c_void_p)],
         "parquet_batch_iterate": [c_void_p, c_int32, c_double, c_double, POINTER(c_int32)],
         "parquet_batch_status": [c_void_p, c_void_p, c_void_p, c_void_p],

@@ -328,35 +328,24 @@ class Batch:
 
     def __init__(self, params, precision: str = "fp32", device: str = "cuda:0", autotune: bool = True,
                  max_bytes: int = 0):
-        """max_bytes: a bound on the workspace of several instances (0: none), where
-        one channel's part of the Bethe-Salpeter scratch fits it."""
+        """max_bytes: a bound on the workspace (0: none), above which it is the least
+        one, where the channels of small boxes do not share their launches."""
         self.params = list(params)
         self.precision = precision
         self.device = torch.device(device)
         K = len(self.params)
         self.K = K
         self._pp = (N.PqParams * K)(*[N.make_params(p, precision) for p in self.params])
-        lib = N.load()
-        b = ctypes.c_size_t()
-        N.check(lib.parquet_batch_query_workspace(self._pp, K, ctypes.byref(b)))
-        need = int(b.value)
-        sizes = [need * part // 16 for part in range(16, 3, -1)]      # on a device short of memory, as Solver does
-        if K > 1 and 0 < max_bytes < need:
-            sizes.insert(0, int(max_bytes))
-        oom = None
-        for size in sizes:
-            try:
-                self._bind(size, autotune)
-                break
-            except torch.OutOfMemoryError as err:
-                oom = err
-            except N.ParquetError as err:
-                if err.status != N.PQ_ERR_NOMEM or size == need:
-                    raise
-                if oom is not None:
-                    raise oom
-        else:
-            raise oom
+        b, least = ctypes.c_size_t(), ctypes.c_size_t()
+        N.check(N.load().parquet_batch_query_workspace(self._pp, K, ctypes.byref(b)))
+        N.check(N.load().parquet_batch_query_workspace_min(self._pp, K, ctypes.byref(least)))
+        size = least.value if 0 < max_bytes < b.value else b.value
+        try:
+            self._bind(size, autotune)
+        except torch.OutOfMemoryError:                 # as Solver does
+            if size == least.value:
+                raise
+            self._bind(least.value, autotune)
         self.stage = Stage(self.params[0], precision)
 
     def _bind(self, nbytes: int, autotune: bool):

@@ -1,5 +1,6 @@
 """Workspace sizes and what the callers make of them, on the CPU (the queries are
 host code; allocations and contexts are stand-ins)."""
+import ctypes
 import types
 
 import pytest
@@ -102,3 +103,28 @@ def test_context_on_a_device_short_of_memory(monkeypatch, prec, p):
     ops.Solver(p, prec, ws_bytes=2 * hi)
     ops.Solver(p, prec, compact=True)
     assert dev.sizes == [2 * hi, lo]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("p,count", [(box(), 3), (box(3, 2, 4), 2), (box(), 1)])
+def test_batch_on_a_device_short_of_memory(monkeypatch, prec, p, count):
+    """As a context; a bound below the full size takes the least one at once, and
+    holds nothing besides."""
+    pp = (N.PqParams * count)(*[N.make_params(p, prec)] * count)
+    hi, lo = ctypes.c_size_t(), ctypes.c_size_t()
+    N.check(N.load().parquet_batch_query_workspace(pp, count, ctypes.byref(hi)))
+    N.check(N.load().parquet_batch_query_workspace_min(pp, count, ctypes.byref(lo)))
+    hi, lo = hi.value, lo.value
+    assert (lo < hi) == (count > 1)
+    made = []
+    monkeypatch.setattr(ops.Batch, "_bind", lambda self, n, tune: made.append(torch.empty(n, torch.uint8, None)))
+    for room, bound, size in ((hi, 0, hi), (hi - 1, 0, lo), (lo, 0, lo), (lo - 1, 0, None), (2 * hi, hi, hi),
+                              (2 * hi, hi - 1, lo), (2 * hi, lo - 1, lo), (lo, 1, lo)):
+        dev = Device(room)
+        monkeypatch.setattr(torch, "empty", dev.empty)
+        if size is None or size > room:
+            with pytest.raises(torch.OutOfMemoryError):
+                ops.Batch([p] * count, prec, max_bytes=bound)
+        else:
+            ops.Batch([p] * count, prec, max_bytes=bound)
+            assert dev.sizes == [size]

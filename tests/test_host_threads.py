@@ -45,21 +45,20 @@ def test_stream_pool_last_stream_taken_by_another_thread(monkeypatch):
 
 
 class Lib:
-    """The batch's entry points without a device: a workspace below `least` bytes is refused."""
+    """The batch's entry points without a device."""
 
-    def __init__(self, full, least):
-        self.full, self.least, self.sizes = full, least, []
+    def __init__(self, status=ops.N.PQ_OK):
+        self.status = status
 
     def parquet_batch_query_workspace(self, pp, count, out):
-        out._obj.value = self.full
+        out._obj.value = 1000
         return ops.N.PQ_OK
 
+    parquet_batch_query_workspace_min = parquet_batch_query_workspace
+
     def parquet_batch_init(self, pp, count, ws, size, stream, autotune, out):
-        self.sizes.append(size.value)
-        if size.value < self.least:
-            return ops.N.PQ_ERR_NOMEM
         out._obj.value = 1
-        return ops.N.PQ_OK
+        return self.status
 
     def parquet_batch_destroy(self, h):
         return ops.N.PQ_OK
@@ -69,15 +68,12 @@ class Lib:
 
 
 class Device:
-    """torch's allocations as byte counts, `room` bytes of them."""
+    """torch's allocations, those still held."""
 
-    def __init__(self, room=None):
-        self.room, self.live = room, []
+    def __init__(self):
+        self.live = []
 
     def empty(self, size, dtype, device):
-        self.live = [r for r in self.live if r() is not None]
-        if self.room is not None and size + sum(r().size for r in self.live) > self.room:
-            raise torch.OutOfMemoryError("no room")
         t = Buffer(size)
         self.live.append(weakref.ref(t))
         return t
@@ -100,30 +96,24 @@ class Buffer:
         pass
 
 
-@pytest.fixture
-def batch_of(monkeypatch):
-    """Batch of three instances over Lib and Device; the buffers held whenever its stream goes back."""
-    from workloads import ModelParams
-    ps = [ModelParams(Lx=2, Ly=1, Nv=4, U=1.0, beta=2.0, mu_mode=0, alpha=0.6)] * 3
-
-    def make(lib, dev, **kw):
-        held = []
-        monkeypatch.setattr(ops.N, "load", lambda: lib)
-        monkeypatch.setattr(ops, "Stage", lambda *a: None)
-        monkeypatch.setattr(torch, "empty", dev.empty)
-        monkeypatch.setattr(torch.cuda, "synchronize", lambda d=None: None)
-        monkeypatch.setattr(ops, "new_stream", lambda d: types.SimpleNamespace(cuda_stream=0x20))
-        monkeypatch.setattr(ops, "release_stream", lambda s: held.append(dev.held()))
-        return ops.Batch(ps, "fp64", **kw), held
-
-    return make
-
-
-def test_batch_frees_its_workspace_before_its_stream(batch_of):
+@pytest.mark.parametrize("status", [ops.N.PQ_OK, ops.N.PQ_ERR_HIP])
+def test_batch_frees_its_workspace_before_its_stream(monkeypatch, status):
     """A stream that goes back to the pool may be captured by its next user at once;
     freeing a tensor recorded on it puts an event there. Closed and refused batches."""
-    dev = Device()
-    b, held = batch_of(Lib(1000, 900), dev, max_bytes=800)       # 800 is refused
-    assert dev.held() == 1
-    b.close()
-    assert held and not any(held)
+    from workloads import ModelParams
+    ps = [ModelParams(Lx=2, Ly=1, Nv=4, U=1.0, beta=2.0, mu_mode=0, alpha=0.6)] * 3
+    dev, lib, held = Device(), Lib(status), []
+    monkeypatch.setattr(ops.N, "load", lambda: lib)
+    monkeypatch.setattr(ops, "Stage", lambda *a: None)
+    monkeypatch.setattr(torch, "empty", dev.empty)
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda d=None: None)
+    monkeypatch.setattr(ops, "new_stream", lambda d: types.SimpleNamespace(cuda_stream=0x20))
+    monkeypatch.setattr(ops, "release_stream", lambda s: held.append(dev.held()))
+    if status == ops.N.PQ_OK:
+        b = ops.Batch(ps, "fp64")
+        assert dev.held() == 1
+        b.close()
+    else:
+        with pytest.raises(ops.N.ParquetError):
+            ops.Batch(ps, "fp64")
+    assert held == [0]
