@@ -260,8 +260,8 @@ pq_status sigma_mix(const pq_params* p, const void* sigma_new, void* sigma_io, d
 }
 
 // ------------------------------------------------------ learned warm start
-// widths and batch up to 65535 GEMM tiles of 64 (the products put the output
-// width and the batch on the grid's second dimension)
+// widths and batch up to 65535 times 64, a limit of the interface alone: the
+// products put their 32 x 32 tiles on both dimensions of the grid
 constexpr int32_t kMlpMaxWidth = 65535 * 64;
 constexpr int32_t kMlpMaxBasisRows = 4096;
 

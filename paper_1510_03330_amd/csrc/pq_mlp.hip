@@ -187,6 +187,17 @@ struct WCols {
   __device__ void put(Stage& st, int e, bf16x8 v) const { st.b[e % 32][e / 32] = v; }
 };
 
+// The tiles of a launch over the grid's two dimensions: a dimension takes fewer
+// than 2^32 work items, which 2^23 workgroups of 512 reach (8192 outputs of a batch
+// of 2^20). Workgroups past the last tile exit.
+constexpr size_t kGridX = size_t(1) << 22;
+constexpr size_t kMaxTiles = size_t(1) << 30;        // (4 TB of outputs)
+inline dim3 tile_grid(size_t tiles) {
+  const size_t x = std::min(tiles, kGridX);
+  return dim3((unsigned)x, (unsigned)((tiles + x - 1) / x));
+}
+__device__ inline unsigned tile_index() { return blockIdx.y * gridDim.x + blockIdx.x; }
+
 // y[b][o] = act(sum_i h[b][i] W[o][i] + bias[o])
 template <bool VEC>
 __global__ __launch_bounds__(kSThreads) void mlp_forward_kernel(int B, int out, int in, const float* h,
@@ -194,8 +205,9 @@ __global__ __launch_bounds__(kSThreads) void mlp_forward_kernel(int B, int out, 
                                                                 int tanh_act) {
   __shared__ Stage st;
   __shared__ float res[16][64];
-  const unsigned nt = (out + 31) / 32;
-  const int m0 = (int)(blockIdx.x / nt) * 32, n0 = (int)(blockIdx.x % nt) * 32;
+  const unsigned nt = (out + 31) / 32, id = tile_index();
+  const int m0 = (int)(id / nt) * 32, n0 = (int)(id % nt) * 32;
+  if (m0 >= B) return;
   tile_product(
       st, res, in,
       [&](int r, int k, float (&v)[8]) {
@@ -224,7 +236,8 @@ __global__ __launch_bounds__(kSThreads) void mlp_backward_kernel(int B, int out,
   __shared__ Stage st;
   __shared__ float res[16][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int id = blockIdx.x;
+  int id = (int)tile_index();
+  if (id >= ndn + ngw + ngb + (d.t ? 1 : 0)) return;
   if (id < ndn) {
     const int nt = (in + 31) / 32, m0 = (id / nt) * 32, n0 = (id - (id / nt) * nt) * 32;
     tile_product(
@@ -514,9 +527,10 @@ hipError_t launch_mlp_forward(const int32_t* w, int nl, const void* pb, const fl
     const int in = w[l], out = w[l + 1];
     float* y = acts + aoff;
     const __bf16* W = (const __bf16*)pb + off;
-    const unsigned tiles = (unsigned)((out + 31) / 32) * (unsigned)((B + 31) / 32);
+    const size_t tiles = (size_t)((out + 31) / 32) * ((B + 31) / 32);
+    if (tiles > kMaxTiles) return hipErrorInvalidConfiguration;
     auto kernel = vec8(h, in) && vec8(W, in) ? mlp_forward_kernel<true> : mlp_forward_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kSThreads), 0, s, B, out, in, h, W, p + off + (size_t)out * in, y,
+    hipLaunchKernelGGL(kernel, tile_grid(tiles), dim3(kSThreads), 0, s, B, out, in, h, W, p + off + (size_t)out * in, y,
                        l < nl - 1 ? 1 : 0);
     off += (size_t)out * in + out;
     aoff += (size_t)B * out;
@@ -549,14 +563,16 @@ hipError_t launch_mlp_backward(const int32_t* w, int nl, const void* pb, const f
   }
   for (int l = nl - 1; l >= 0; --l) {
     const int in = w[l], out = w[l + 1];
-    const int ndn = l > 0 ? (B + 31) / 32 * ((in + 31) / 32) : 0;
-    const int ngw = (out + 31) / 32 * ((in + 32 * kSW - 1) / (32 * kSW));
+    const size_t tdn = l > 0 ? (size_t)((B + 31) / 32) * ((in + 31) / 32) : 0;
+    const size_t tgw = (size_t)((out + 31) / 32) * ((in + 32 * kSW - 1) / (32 * kSW));
+    if (tdn + tgw > kMaxTiles) return hipErrorInvalidConfiguration;
+    const int ndn = (int)tdn, ngw = (int)tgw;
     float* gW = grad + poff[l];
     const float* hin = l == 0 ? x : acts + aoff[l - 1];
     const bool vec = vec8(g.p, out) && (!g.t || vec8(g.t, out));
     auto kernel = vec ? mlp_backward_kernel<true> : mlp_backward_kernel<false>;
     const int ngb = (out + kSThreads - 1) / kSThreads;
-    hipLaunchKernelGGL(kernel, dim3(ndn + ngw + ngb + (g.t ? 1 : 0)), dim3(kSThreads), 0, s, B, out, in, g, hin,
+    hipLaunchKernelGGL(kernel, tile_grid((size_t)ndn + ngw + ngb + (g.t ? 1 : 0)), dim3(kSThreads), 0, s, B, out, in, g, hin,
                        (const __bf16*)pb + poff[l], gW, gW + (size_t)out * in, dn, loss, ndn, ngw, ngb);
     g = GradSrc{dn, nullptr, 0.f};
     std::swap(d, dn);

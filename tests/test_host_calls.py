@@ -85,3 +85,33 @@ def test_one_thread_at_a_time_in_graph_calls(fake_hip):
         assert setting("fake_graph_calls").value == 4 * (2 + 4) + 2 * 10 + 4 * 10
         assert setting("fake_overlaps").value == 0, setting("fake_overlaps").value
     """)
+
+
+@pytest.mark.parametrize("batch,widths", [(33, (3, 65, 7)), (2 ** 20 + 33, (3, 8192, 5)), (4194240, (2, 2100, 2050)),
+                                          (40, (2, 4194240, 3))])
+def test_perceptron_grids(fake_hip, batch, widths):
+    """Every launch of the forward and backward pass within the limits of a grid (a
+    dimension below 2^32 work items, the second and third at most 65535 workgroups),
+    with a workgroup for every 32 x 32 tile."""
+    run(fake_hip, f"""
+        batch, widths = {batch}, {widths}
+        w, nl, a = (c_int32 * len(widths))(*widths), {len(widths) - 1}, c_void_p(0x100000)
+        N.check(lib.mlp_forward(w, nl, a, a, a, a, batch, None))
+        N.check(lib.mlp_backward(w, nl, a, a, a, a, a, a, a, batch, None))
+        n = setting("fake_launches").value
+        dims = [list(d) for d in ((ctypes.c_uint * 6) * 4096).in_dll(fake, "fake_dims")[:n]]
+        for d in dims:
+            assert all(0 < d[i] * d[3 + i] < 2 ** 32 for i in range(3)), d
+            assert max(d[1:3]) <= 65535, d
+
+        def up(x, k):
+            return -(-x // k)
+
+        fwd = [up(o, 32) * up(batch, 32) for o in widths[1:]]
+        bwd = [up(o, 32) * up(i, 256) + up(o, 512) + (up(i, 32) * up(batch, 32) if l else 0)
+               for l, (i, o) in enumerate(zip(widths, widths[1:]))][::-1]
+        got = [d for d in dims if d[3] == 512]
+        assert len(got) == 2 * nl
+        for d, need in zip(got, fwd + bwd):
+            assert need <= d[0] * d[1] <= need + d[0], (d, need)       # one more: the loss
+    """)
