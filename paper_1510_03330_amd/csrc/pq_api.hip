@@ -548,6 +548,10 @@ hipError_t enqueue_iteration(pq_ctx* c, bool record, BseTiming* tm, const char**
     return e;
   }
   rec(4);
+  if (tm) {
+    tm->mark = record && er == hipSuccess ? c->ev[4] : nullptr;
+    tm->mark_stream = c->s;
+  }
   if (c->four) {
     e = launch_bse_four(p, d, c->gamma, c->xph, c->xpp, c->phi, p.alpha, c->bstats, c->bse_ws, c->s, tm,
                         lookahead && c->have_la ? &c->la : nullptr);
@@ -650,14 +654,16 @@ pq_status parquet_init(const pq_params* p, void* ws, size_t ws_bytes, pq_stream 
   c->graph_has_lam = false;
   c->host = host_slots().take();
   c->pending = false;
+  // events for times alone (the results are read after a wait for the stream): without
+  // the fence of one that others wait for, 1 us less each
   c->have_events = true;
   for (int i = 0; i < 8; ++i)
-    if (hipEventCreate(&c->ev[i]) != hipSuccess) c->have_events = false;
+    if (hipEventCreateWithFlags(&c->ev[i], hipEventDisableSystemFence) != hipSuccess) c->have_events = false;
   // as many as its timed launches can need: at most 6 per panel (64 wide or more), 4 beside
   c->nbev = 2 * std::min(256, 6 * ((d.n + 63) / 64) + 4);
   c->have_bev = true;
   for (int i = 0; i < c->nbev; ++i)
-    if (hipEventCreate(&c->bev[i]) != hipSuccess) c->have_bev = false;
+    if (hipEventCreateWithFlags(&c->bev[i], hipEventDisableSystemFence) != hipSuccess) c->have_bev = false;
   // look-ahead stream (default priority) and its two events; blocks of one panel
   // have nothing to look ahead to
   c->have_la = d.n > 64 && hipStreamCreateWithFlags(&c->la.side, hipStreamNonBlocking) == hipSuccess;
@@ -701,18 +707,17 @@ pq_status parquet_iterate(pq_ctx* c, int32_t n_iter, double tol, pq_iter_stats* 
   PQ_CHECK_ARG(n_iter >= 0, "n_iter must be >= 0");
   int done = 0, conv = 0;
   pq_status st = PQ_OK;
+  // Any iteration may be the last one, whose times are reported (an error ends the
+  // call also without a convergence test), so each records its events; only the
+  // last one's are read (one momentum Nv = 32: 143 us an iteration, 128 without).
+  const bool events = c->have_events && stats, timing = c->have_bev && stats;
+  BseTiming tm;
   for (int it = 0; it < n_iter; ++it) {
     hipError_t e = hipSuccess;
-    BseTiming tm;
     tm.ev = c->bev;
     tm.cap = c->nbev / 2;
     tm.used = 0;
     tm.update_flops = 0.0;
-    // the times are those of the last iteration; without a convergence test that
-    // is known before it runs, and the others go without their events
-    const bool last = tol != 0.0 || it == n_iter - 1;
-    const bool events = c->have_events && stats && last;
-    const bool timing = stats && c->have_bev && last;
     const char* where = nullptr;
     c->pending = true;
     if ((e = enqueue_iteration(c, events, timing ? &tm : nullptr, &where, true)) != hipSuccess)
@@ -731,25 +736,9 @@ pq_status parquet_iterate(pq_ctx* c, int32_t n_iter, double tol, pq_iter_stats* 
       stats->resolved_blocks = (int32_t)res[2];
       stats->unresolved_blocks = (int32_t)res[3];
       stats->max_err_est = res[4];
-      if (c->have_events && !events) {
+      if (events) {             // until they are read
         stats->ms_total = __builtin_nan("");
-        for (double& ms : stats->ms_stage) ms = stats->ms_total;
-      } else if (events) {
-        stats->ms_total = elapsed_ms(c->ev[0], c->ev[6]);
-        stats->ms_stage[0] = elapsed_ms(c->ev[0], c->ev[1]);
-        stats->ms_stage[1] = elapsed_ms(c->ev[1], c->ev[2]);
-        stats->ms_stage[3] = elapsed_ms(c->ev[2], c->ev[3]);
-        stats->ms_stage[4] = elapsed_ms(c->ev[3], c->ev[4]);
-        stats->ms_stage[5] = elapsed_ms(c->ev[4], c->ev[5]);
-        stats->ms_stage[6] = elapsed_ms(c->ev[5], c->ev[6]);
-      }
-      if (timing) {
-        const double share = c->four ? 0.25 : 1.0;        // one channel's part of shared launches
-        for (int i = 0; i < tm.used; ++i) {
-          stats->ms_bse_kernel[tm.kind[i]] += share * elapsed_ms(c->bev[2 * i], c->bev[2 * i + 1]);
-          stats->n_bse_launch[tm.kind[i]] += 1;
-        }
-        stats->update_flops = share * tm.update_flops;
+        for (int i : {0, 1, 3, 4, 5, 6}) stats->ms_stage[i] = stats->ms_total;
       }
     }
     if (!(dn == dn)) {
@@ -767,6 +756,23 @@ pq_status parquet_iterate(pq_ctx* c, int32_t n_iter, double tol, pq_iter_stats* 
       conv = 1;
       break;
     }
+  }
+  if (events && done > 0) {
+    stats->ms_total = elapsed_ms(c->ev[0], c->ev[6]);
+    stats->ms_stage[0] = elapsed_ms(c->ev[0], c->ev[1]);
+    stats->ms_stage[1] = elapsed_ms(c->ev[1], c->ev[2]);
+    stats->ms_stage[3] = elapsed_ms(c->ev[2], c->ev[3]);
+    stats->ms_stage[4] = elapsed_ms(c->ev[3], c->ev[4]);
+    stats->ms_stage[5] = elapsed_ms(c->ev[4], c->ev[5]);
+    stats->ms_stage[6] = elapsed_ms(c->ev[5], c->ev[6]);
+  }
+  if (timing && done > 0) {
+    const double share = c->four ? 0.25 : 1.0;        // one channel's part of shared launches
+    for (int i = 0; i < tm.used; ++i) {
+      stats->ms_bse_kernel[tm.kind[i]] += share * elapsed_ms(tm.from[i], tm.to[i]);
+      stats->n_bse_launch[tm.kind[i]] += 1;
+    }
+    stats->update_flops = share * tm.update_flops;
   }
   if (st == PQ_OK && tol != 0.0 && !conv && n_iter > 0) {
     set_error("not converged to %g in %d iterations", tol, done);

@@ -2323,13 +2323,15 @@ static hipError_t run_bse(const Dims& d, const Chans& ch, double alpha, float we
   auto pre = [&](int kind, hipStream_t st) {
     if (tm && tm->used < tm->cap) {
       tm->kind[tm->used] = kind;
-      note(hipEventRecord(tm->ev[2 * tm->used], st));
+      if (!tm->mark || tm->mark_stream != st) note(hipEventRecord(tm->mark = tm->ev[2 * tm->used], st));
+      tm->from[tm->used] = tm->mark;
     }
   };
   auto post = [&](hipStream_t st) {
     if (tm && tm->used < tm->cap) {
-      note(hipEventRecord(tm->ev[2 * tm->used + 1], st));
-      tm->used++;
+      note(hipEventRecord(tm->mark = tm->ev[2 * tm->used + 1], st));
+      tm->mark_stream = st;
+      tm->to[tm->used++] = tm->mark;
     }
   };
   if (tm) tm->update_flops = 0.0;
@@ -2364,6 +2366,7 @@ static hipError_t run_bse(const Dims& d, const Chans& ch, double alpha, float we
   }
   auto refine_gather = [&](int late, hipStream_t st) {
     if constexpr (sizeof(T) == 4) {
+      if (tm) tm->mark = nullptr;
       hipLaunchKernelGGL(refine_list_kernel, dim3(1), dim3(kThreads), 0, st, a.pst, d.Nq, weak, kappa_max, S, late,
                          list);
       hipLaunchKernelGGL(refine_gather_kernel, dim3(gx, gs), dim3(kThreads), 0, st, (const float2*)gamma, ch,

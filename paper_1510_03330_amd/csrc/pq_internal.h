@@ -145,6 +145,9 @@ struct BseTiming {
   hipEvent_t* ev;     // 2 * cap events
   int cap, used;
   int kind[256];
+  hipEvent_t from[256], to[256];   // of each launch: its start may be the end of the one before
+  hipEvent_t mark;                 // an event on mark_stream with no launch after it, or null
+  hipStream_t mark_stream;
   double update_flops;
 };
 // Look-ahead of the BSE elimination: a second stream and two events (created

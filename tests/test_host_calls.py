@@ -115,3 +115,24 @@ def test_perceptron_grids(fake_hip, batch, widths):
         for d, need in zip(got, fwd + bwd):
             assert need <= d[0] * d[1] <= need + d[0], (d, need)       # one more: the loss
     """)
+
+
+@pytest.mark.parametrize("fill,status", [(255, "PQ_ERR_NONFINITE"), (1, "PQ_ERR_SINGULAR")])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_times_of_an_iteration_that_fails(fake_hip, fill, status, prec):
+    """A call that an error ends before its last iteration reports that iteration's
+    times (1 ms an event pair here). fill: the results' bytes, NaN or a positive
+    count of unresolved blocks."""
+    run(fake_hip, f"""
+        setting("fake_host_fill").value = {fill}
+        pp = N.make_params(ModelParams(Lx=2, Ly=1, Nv=4, U=1.0, beta=2.0, mu_mode=0, alpha=0.6), "{prec}")
+        need, c, done, st = c_size_t(), c_void_p(), c_int32(), N.PqIterStats()
+        N.check(lib.parquet_query_workspace(byref(pp), byref(need)))
+        ws = room(need.value)
+        N.check(lib.parquet_init(byref(pp), ws, need, c_void_p(16), byref(c)))
+        assert lib.parquet_iterate(c, 3, 0.0, byref(st), byref(done), None) == N.{status}
+        assert done.value == 1 and st.iteration == 1
+        assert st.ms_total == 1.0 and [st.ms_stage[i] for i in (0, 1, 3, 4, 5, 6)] == [1.0] * 6
+        assert sum(st.n_bse_launch) > 0 and sum(st.ms_bse_kernel) == 0.25 * sum(st.n_bse_launch)
+        N.check(lib.parquet_destroy(c))
+    """)
