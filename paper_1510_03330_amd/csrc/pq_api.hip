@@ -82,7 +82,7 @@ bool make_dims(const pq_params* p, Dims* d) {
   x.cs = (long long)x.Nq * x.n * x.n;
   if (x.n > 4096) { set_error("BSE dimension %d above 4096", x.n); return false; }
   const double E = x.Nk == 1 ? p->D : 2.0 * max_abs_eps(*p, x);
-  x.ntau = 8 * x.f * x.Nv + 64 + 4 * (int)ceil(p->beta * E);
+  x.ntau = 8 * x.f * x.Nv + 64 + 4 * (int)ceil(p->beta * E);     // even: the nodes come in pairs
   *d = x;
   return true;
 }
@@ -470,7 +470,7 @@ CtxLayout ctx_layout(const pq_params& p, const Dims& d, bool four) {
   L.four = L.bse_bytes > 0;
   if (!L.four) L.bse_bytes = bse_ws_bytes(p, d, p.precision);
   L.bse = take(L.bse_bytes);
-  L.sig_bytes = sigma_ws_bytes(d);
+  L.sig_bytes = sigma_scratch_bytes(d);
   L.sig = take(L.sig_bytes);
   L.bstats = take(sizeof(pq_bse_block_stats) * 4 * (size_t)d.Nq);
   L.total = off;

@@ -96,7 +96,7 @@ BatchLayout batch_layout(const pq_params* ps, const std::vector<Dims>& dims, boo
   if (!L.four) L.bse_bytes = bse_ws_bytes(p, dk, p.precision);
   L.bse = take(L.bse_bytes);
   size_t sb = 0;
-  for (int i = 0; i < K; ++i) sb = std::max(sb, sigma_ws_bytes(dims[i]));
+  for (int i = 0; i < K; ++i) sb = std::max(sb, sigma_scratch_bytes(dims[i]));
   L.sig_bytes = sb;
   L.sig = take(sb);
   L.dn = take(sizeof(double) * kDn * (size_t)K);

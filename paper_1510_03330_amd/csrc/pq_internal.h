@@ -69,7 +69,7 @@ struct StageIn {
   const void* phi;
   const double2 *k1, *k2;
   double2* sigma_new;
-  void* sig_ws;          // scratch of its own (sigma_ws_bytes)
+  void* sig_ws;          // scratch of its own (sigma_scratch_bytes)
 };
 struct MixIn {
   const double2* snew;
@@ -127,7 +127,8 @@ hipError_t launch_mlp_expand(const float* q, int rows, size_t len, const float* 
                              const float* scale, double* out, hipStream_t s);
 hipError_t launch_phi_from_kernels(const pq_params& p, const Dims& d, const double2* k1, const double2* k2,
                                    void* phi, hipStream_t s);
-size_t sigma_ws_bytes(const Dims& d);
+size_t sigma_ws_bytes(const Dims& d);        // what the stage's entry points ask of callers
+size_t sigma_scratch_bytes(const Dims& d);   // what the stage uses, at most that
 // Device address of the static scratch of sigma_sde_no_alloc on the current
 // device (looked up once per device, then cached).
 constexpr size_t kStaticScratchBytes = size_t(64) << 20;

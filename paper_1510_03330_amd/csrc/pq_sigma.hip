@@ -99,7 +99,7 @@ struct S1Args {
 // need N-long serial recurrences per Newton step: 103-223 us a call measured,
 // against a few cosines per node here.)
 //
-// One workgroup per pair (j, N-1-j), so that G(R, tau_j) and G(-R, beta - tau_j)
+// One workgroup per pair (j, N-1-j) (N is even), so that G(R, tau_j) and G(-R, beta - tau_j)
 // meet in one workgroup: dG = G - G_pole on the extended box, the imaginary-time
 // sums over its frequencies (exp(-i nu (beta - tau)) = -exp(i nu tau): one phase
 // serves both nodes), the lattice transform and the product, which kernels of
@@ -111,7 +111,7 @@ struct S1Args {
 template <int N>
 __global__ __launch_bounds__(kThreads) void s1_tau_kernel(Many<S1Args, N> m) {
   const S1Args& a = m.a[N == 1 ? 0 : blockIdx.z];
-  if ((int)blockIdx.x >= (a.d.ntau + 1) / 2) return;     // an instance of fewer nodes than the launch's most
+  if ((int)blockIdx.x >= a.d.ntau / 2) return;           // an instance of fewer nodes than the launch's most
   __shared__ double2 ph[kThreads];
   __shared__ double2 red[2][kThreads];
   __shared__ double2 gk[2][kMaxNk];
@@ -299,7 +299,7 @@ struct S2Args {
   const double2* g;
   const double2* k1;     // [4][Nq]
   const double2* k2;     // [4][Nq][n]
-  double2* tab;          // [Nve][5][Nq]  A16, A25, A34, B1, B3 per (n_k, p) (room for NG >= Nve)
+  double2* tab;          // [Nve][5][Nq]  A16, A25, A34, B1, B3 per (n_k, p)
 };
 
 __device__ inline double ind(bool b) { return b ? 1.0 : 0.0; }
@@ -742,8 +742,6 @@ __global__ __launch_bounds__(kThreads) void s2box_kernel(S2BoxArgs a) {
   if (threadIdx.x == 0) a.out[kid] = mk(a.cfac * tr, a.cfac * ti);
 }
 
-// (the size is part of what callers see, sigma_sde_workspace and the limit of
-// sigma_sde_no_alloc, so it stays; the space before srt is not used)
 struct WsLayout {
   size_t srt, s1, tab, part, lb1, lb2, lpart, sq, total;
 };
@@ -752,15 +750,9 @@ WsLayout ws_layout(const Dims& d) {
   WsLayout L{};
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
-  take(sizeof(double) * d.ntau);
-  take(sizeof(double) * d.ntau);
-  take(sizeof(double2) * d.Nve * d.Nk);
-  take(sizeof(double2) * (size_t)d.ntau * d.Nk);
   L.srt = take(sizeof(double2) * (size_t)d.ntau * d.Nk);
-  take(sizeof(double2) * d.Nve * d.Nk);
   L.s1 = take(sizeof(double2) * d.Nve * d.Nk);
-  take(sizeof(double2) * d.Nve * d.Nk);
-  L.tab = take(sizeof(double2) * 5 * (size_t)d.NG * d.Nq);
+  L.tab = take(sizeof(double2) * 5 * (size_t)d.Nve * d.Nq);
   L.part = take(sizeof(double2) * (size_t)d.n * d.NW);
   L.lb1 = take(sizeof(double2) * (size_t)d.Nv * d.NW * d.Nk);
   L.lb2 = take(sizeof(double2) * (size_t)d.Nv * d.NW * d.Nk);
@@ -782,7 +774,7 @@ hipError_t run_sigma1(G&& args, int count, hipStream_t s) {
     constexpr int N = sizeof(m.a) / sizeof(m.a[0]);
     int nt = 0;
     for (int i = 0; i < n; ++i) nt = std::max(nt, m.a[i].d.ntau);
-    hipLaunchKernelGGL(s1_tau_kernel<N>, dim3((nt + 1) / 2, 1, n), dim3(kThreads), 0, s, m);
+    hipLaunchKernelGGL(s1_tau_kernel<N>, dim3(nt / 2, 1, n), dim3(kThreads), 0, s, m);
     hipLaunchKernelGGL(s1_row_kernel<N>, dim3(m.a[0].d.Nve, 1, n), dim3(kRowThreads), 0, s, m);
   });
   return hipGetLastError();
@@ -790,7 +782,16 @@ hipError_t run_sigma1(G&& args, int count, hipStream_t s) {
 
 }  // namespace
 
-size_t sigma_ws_bytes(const Dims& d) { return ws_layout(d).total; }
+size_t sigma_scratch_bytes(const Dims& d) { return ws_layout(d).total; }
+
+// Above the scratch by what an earlier form of the stage kept beside it (two arrays
+// of nodes, one of ntau Nk and three of Nve Nk values, a table over NG frequencies):
+// callers see this size, and sigma_sde_no_alloc's limit is one on it.
+size_t sigma_ws_bytes(const Dims& d) {
+  const size_t row = sizeof(double2) * (size_t)d.Nk, tab = sizeof(double2) * 5 * (size_t)d.Nq;
+  return ws_layout(d).total + 2 * align256(sizeof(double) * d.ntau) + align256(row * d.ntau) + 3 * align256(row * d.Nve) +
+         align256(tab * d.NG) - align256(tab * d.Nve);
+}
 
 // ------------------------------------------------------ static scratch
 // Workspace of sigma_sde_no_alloc: a file-scope device array, one copy per

@@ -1,6 +1,7 @@
 """Workspace sizes and what the callers make of them, on the CPU (the queries are
 host code; allocations and contexts are stand-ins)."""
 import ctypes
+import random
 import types
 
 import pytest
@@ -128,3 +129,22 @@ def test_batch_on_a_device_short_of_memory(monkeypatch, prec, p, count):
         else:
             ops.Batch([p] * count, prec, max_bytes=bound)
             assert dev.sizes == [size]
+
+
+def test_sums_scratch_holds_one_array_of_nodes():
+    """A context's workspace grows with the quadrature nodes by the one array over
+    them that is used; their number is even, as the launches by pairs need."""
+    def up(x):
+        return (x + 255) // 256 * 256
+
+    rng = random.Random(7)
+    for _ in range(200):
+        lx, ly = rng.choice([(1, 1), (2, 1), (3, 3), (1, 5), (4, 4), (7, 1)])
+        p = box(lx, ly, 2 * rng.randint(1, 6), f_ext=rng.randint(1, 5), D=rng.uniform(0.1, 3.0), tp=rng.uniform(-1.0, 1.0))
+        nodes, bytes_ = [], []
+        for beta in (rng.uniform(0.1, 5.0), rng.uniform(5.0, 80.0)):
+            q = p.replace(beta=beta)
+            nodes.append(N.dims(N.make_params(q, "fp64")).ntau)
+            bytes_.append(least(q, "fp64"))
+        assert nodes[0] % 2 == nodes[1] % 2 == 0
+        assert bytes_[1] - bytes_[0] == up(16 * nodes[1] * lx * ly) - up(16 * nodes[0] * lx * ly)
