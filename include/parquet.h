@@ -485,8 +485,9 @@ pq_status parquet_destroy(pq_ctx* ctx);
  * instance). count * Nq <= 16384.
  *
  * The reducible vertices live in one arena [4][count][Nq][n][n], so the BSE of
- * one channel (Eq. PA_F_Phi) is one launch sequence over every (instance, q)
- * block; the other stages run instance after instance around it, and one
+ * one channel (Eq. PA_F_Phi), or of all four for small boxes, is one launch
+ * sequence over every (instance, q) block; of the other stages the small ones are
+ * launched over the instances too, the rest instance after instance, and one
  * round (an iteration of every active instance) is one HIP graph.
  * Each instance keeps its own convergence history and test (tol as in
  * parquet_iterate); an instance that converges, whose Sigma is not finite,
@@ -497,8 +498,8 @@ pq_status parquet_destroy(pq_ctx* ctx);
  * parquet_batch_init starts every instance from the bare vertex; with
  * autotune != 0 and complex64 products (FP32 or BF16x3) it first times both update tiles
  * (pq_params.bse_tile) of the batch's BSE on its own block count and keeps the
- * faster (parquet_batch_tile reports the choice and the times, ms per launch
- * sequence of one channel). ws: parquet_batch_query_workspace bytes, owned by
+ * faster (parquet_batch_tile reports the choice and the times, ms for the
+ * four channels). ws: parquet_batch_query_workspace bytes, owned by
  * the caller; for small boxes they include room for the four channels' BSE in
  * shared launches, and parquet_batch_query_workspace_min tells the least that is
  * taken, with room for one channel's. stream: a created stream (not the null stream; the rounds are

@@ -383,10 +383,10 @@ namespace {
 // Results of an iteration (kResults doubles: the norm, the BSE summary
 // (bse_summary), max |Sigma|, mu~), written by its last kernel into pinned host
 // memory, so that the host reads them after its one wait. Copies to pageable
-// memory made it wait twice: one momentum Nv = 32, an iteration 206 us with two,
-// 190 with one, 171 this way. Slots of a page that all contexts of the process
-// share (a page of its own would cost each context its allocation); it is freed
-// with its last slot. Contexts beyond kSlots copy.
+// memory made it wait twice: one momentum Nv = 32, an iteration 35 us longer with
+// two, 19 with one. Slots of a page that all contexts of the process share (a page
+// of its own would cost each context its allocation); it is freed with its last
+// slot. Contexts beyond kSlots copy.
 constexpr int kResults = 7;
 
 class HostSlots {

@@ -200,8 +200,8 @@ hipError_t enqueue_pre(pq_batch* b, int nactive, const char** where) {
 
 // The BSE of every active block, on the main stream: the four channels in one
 // launch sequence where the workspace holds them (four rounds of eight instances,
-// complex128, against a sequence each: 4x4, Nv = 8: 15.0 and 16.2 ms, 2x2 1.48 and
-// 1.79).
+// complex128, against a sequence each: 4x4, Nv = 8: 14.7 and 15.9 ms, 2x2 1.16 and
+// 1.43).
 hipError_t enqueue_bse(pq_batch* b, int nactive, const char** where) {
   const Dims& d = b->d0;
   Dims r = d;

@@ -2702,12 +2702,11 @@ hipError_t launch_bse(const pq_params& p, const Dims& d, int channel, int precis
 // Four channels in one launch sequence: a box of few or small blocks does not fill
 // the chip with one channel's, and a channel's 4 to 60 launches cost more than
 // their work. An iteration, four channels together and one by one: one momentum
-// Nv = 32 complex128 202 and 334 us, 2x2 Nv = 32 complex64 0.54 and 1.04 ms, 4x4
-// Nv = 8 complex128 0.72 and 1.13 ms, 4x4 Nv = 16 complex64 3.18 and 3.87 ms, 6x6
-// Nv = 8 complex64 5.8 and 7.2 ms. The workspace is that of 4 Nq blocks (at most
-// four times one channel's), so what ends it is memory: kFourBytes, 3 % of the card's,
-// beyond which a channel's launches are long enough (8x8 Nv = 16 BF16x3: 52 ms of
-// work a channel). complex64 only where every flagged block has its re-solve slot
+// Nv = 32 complex128 127 and 230 us, 2x2 Nv = 32 complex64 0.45 and 0.89 ms, 4x4
+// Nv = 8 complex128 0.60 and 0.89 ms, 4x4 Nv = 16 complex64 2.96 and 3.63 ms. The
+// workspace is that of 4 Nq blocks (at most four times one channel's), so what
+// ends it is memory: kFourBytes, 3 % of the card's, beyond which a channel's
+// launches are long enough (8x8 Nv = 16 BF16x3: 52 ms of work a channel). complex64 only where every flagged block has its re-solve slot
 // (a limit on the slots is per channel).
 constexpr size_t kFourBytes = size_t(8) << 30;
 

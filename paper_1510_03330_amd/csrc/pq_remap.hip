@@ -185,7 +185,7 @@ __constant__ float kCoef[2][4][2] = {
 // in flight; small tiles need several per step to cover the two barriers and the
 // memory latency (5x7, Nv = 10: 1.57 -> 1.30 ms complex128, complex64 with the
 // kernel functions 1.22 -> 0.81 ms; 8x8, Nv = 16, complex64 stays at one tile per
-// step, 12.6 ms).
+// step, 13 to 14 ms).
 template <typename C, int EPT, int NT, int TPS>
 __global__ __launch_bounds__(NT) void remap_kernel(RemapArgs<C> a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(kThreads) void remap_direct_kernel(RemapArgs<C> a) 
   const int total = d.Nv * Nk * Nk;
   const bool lines = stream_rows<C>(Nk);
   for (int i = threadIdx.x; i < total; i += kThreads) {
-        const int r_ = i / Nk, Kp = i - r_ * Nk, in2 = r_ / Nk, Q = r_ - in2 * Nk, n2 = in2 - hv;
+    const int r_ = i / Nk, Kp = i - r_ * Nk, in2 = r_ / Nk, Q = r_ - in2 * Nk, n2 = in2 - hv;
     // geometries: ph-bar, pp, st-1, st-2
     const int kpk = ksub(Kp, K, Lx, Ly), kq = kadd(K, Q, Lx, Ly);
     const int mp[4] = {n2 - nk, nk + n2 + m + 1, n2 - nk, m - nk - n2 - 1};
@@ -435,7 +435,7 @@ hipError_t dispatch_remap(const Dims& d, const double lam[4], const double2* lam
   constexpr bool c64 = sizeof(C) == sizeof(float2);
   // Up to 12 momenta gather directly (2x3, Nv = 16, complex128 with the kernel
   // functions: 32 us, tiled 75; 3x4, Nv = 24, complex64: 645 against 674); at 16
-  // the tiles win (4x4, Nv = 16, complex64: 271 against 314, start 655). The
+  // the tiles win (4x4, Nv = 16, complex64: 271 against 314). The
   // tiles per step are what the LDS of two workgroups or more holds.
   if (d.Nk <= kDirectNk) {
     hipLaunchKernelGGL(remap_direct_kernel<C>, dim3(d.n * d.NW), dim3(kThreads), 0, s, a);

@@ -619,7 +619,7 @@ void launch_sigmab(const SBArgs<C>& a, hipStream_t s) {
 //   B2(n', m; Q) = sum_K' G(m-n'-1, Q-K') G(n', K'),
 // and Sigma_box(n, K) gains
 //   sum_{n', m} [dLambda_dm sum_Q G(n+m, K+Q) B1 + dLambda_st sum_Q G(m-n-1, Q-K) B2]
-// (times the Schwinger-Dyson constant, applied in combine_kernel).
+// (times the Schwinger-Dyson constant, applied in sigma2_kernel).
 struct LamArgs {
   Dims d;
   double U;
